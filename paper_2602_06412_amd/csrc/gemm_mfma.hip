@@ -373,7 +373,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(
       if (row >= M) continue;
       const float g = acc[0][0][v];
       const float u = NBW == 1 ? up_sh[((wave >> 1) * 16 + v) * 64 + lane] : acc[0][NBW - 1][v];
-      Cb[afrag_index(row, c, (int)ldc)] = (bf16_t)(g / (1.0f + expf(-g)) * u);
+      Cb[afrag_index(row, c, (int)ldc)] = (bf16_t)silu_mul(g, u);
     }
     return;
   }
