@@ -294,21 +294,18 @@ static int run_layers(sl_ctx* ctx, hipStream_t s, const Workspace& ws, const int
       continue;
     }
     // Q, K, V projections of the active rows (fp32 results side by side)
-    SL_RUN(ctx, s, SL_PROF_GEMM_QKV, slk_gemm_generic(s, dt, ws.h, L.wq, m_dev, mu, hd, d, ws.f32, nullptr, nullptr, 3 * (size_t)hd));
-    SL_RUN(ctx, s, SL_PROF_GEMM_QKV, slk_gemm_generic(s, dt, ws.h, L.wk, m_dev, mu, hd, d, ws.f32 + hd, nullptr, nullptr, 3 * (size_t)hd));
-    SL_RUN(ctx, s, SL_PROF_GEMM_QKV, slk_gemm_generic(s, dt, ws.h, L.wv, m_dev, mu, hd, d, ws.f32 + 2 * hd, nullptr, nullptr, 3 * (size_t)hd));
+    const void* qkv[3] = {L.wq, L.wk, L.wv};
+    SL_RUN(ctx, s, SL_PROF_GEMM_QKV, slk_gemm_generic(s, dt, ws.h, qkv, 3, m_dev, mu, hd, d, ws.f32, nullptr, nullptr, 3 * (size_t)hd));
     // RoPE; live K/V overwrite the rows' own cache slots (locked slots are never touched)
     SL_RUN(ctx, s, SL_PROF_ROPE_KV, slk_rope_kv_write(s, dt, ws.f32, 1, 0, active_idx, m_dev, mu, H, dh, ctx->n_seq, ctx->n_pad, rope_tab, ws.q,
                              ctx->probe_read_only ? nullptr : kv_k_layer(ctx, l),
                              ctx->probe_read_only ? nullptr : kv_v_layer(ctx, l), 0));
     SL_RUN(ctx, s, SL_PROF_ATTENTION, slk_attention_generic(s, dt, ws.q, kv_k_layer(ctx, l), kv_v_layer(ctx, l), active_idx, m_dev, mu, H, dh,
                                  ctx->n_seq, ctx->n_pad, ws.o));
-    SL_RUN(ctx, s, SL_PROF_GEMM_OUT, slk_gemm_generic(s, dt, ws.o, L.wo, m_dev, mu, d, hd, ws.f32, nullptr, nullptr, d));
+    SL_RUN(ctx, s, SL_PROF_GEMM_OUT, slk_gemm_generic(s, dt, ws.o, &L.wo, 1, m_dev, mu, d, hd, ws.f32, nullptr, nullptr, d));
     SL_RUN(ctx, s, SL_PROF_ADD_NORM, slk_add_rmsnorm(s, dt, ws.x, ws.f32, 1, 0, m_dev, mu, d, L.ffn_norm, c.rms_eps, ws.h, 0));
-    SL_RUN(ctx, s, SL_PROF_GEMM_GATE_UP, slk_gemm_generic(s, dt, ws.h, L.w_gate, m_dev, mu, dff, d, ws.f32, nullptr, nullptr, 2 * (size_t)dff));
-    SL_RUN(ctx, s, SL_PROF_GEMM_GATE_UP, slk_gemm_generic(s, dt, ws.h, L.w_up, m_dev, mu, dff, d, ws.f32 + dff, nullptr, nullptr, 2 * (size_t)dff));
-    SL_RUN(ctx, s, SL_PROF_SWIGLU, slk_swiglu(s, dt, ws.f32, 1, 0, m_dev, mu, dff, ws.a, 0, 0));
-    SL_RUN(ctx, s, SL_PROF_GEMM_DOWN, slk_gemm_generic(s, dt, ws.a, L.w_down, m_dev, mu, d, dff, ws.f32, nullptr, nullptr, d));
+    SL_RUN(ctx, s, SL_PROF_GEMM_GATE_UP, slk_gemm_generic_swiglu(s, dt, ws.h, L.w_gate, L.w_up, m_dev, mu, dff, d, ws.a));
+    SL_RUN(ctx, s, SL_PROF_GEMM_DOWN, slk_gemm_generic(s, dt, ws.a, &L.w_down, 1, m_dev, mu, d, dff, ws.f32, nullptr, nullptr, d));
     SL_RUN(ctx, s, SL_PROF_ADD_NORM, slk_add_rmsnorm(s, dt, ws.x, ws.f32, 1, 0, m_dev, mu, d, next_gain, c.rms_eps, ws.h, 0));
   }
   return SL_OK;
@@ -540,7 +537,7 @@ static int step_impl(sl_ctx* ctx, void* stream, int32_t* tokens, uint8_t* masked
   if (ctx->use_mfma)
     SL_RUN(ctx, s, SL_PROF_LM_HEAD, sl_mfma_lm_head(ctx, s, ws.h, active_idx, m_dev, m_upper, cur));
   else
-    SL_RUN(ctx, s, SL_PROF_LM_HEAD, slk_gemm_generic(s, c.dtype, ws.h, ctx->plain.lm_head, m_dev, m_upper, c.vocab, c.d_model, nullptr, cur,
+    SL_RUN(ctx, s, SL_PROF_LM_HEAD, slk_gemm_generic(s, c.dtype, ws.h, &ctx->plain.lm_head, 1, m_dev, m_upper, c.vocab, c.d_model, nullptr, cur,
                             active_idx, c.vocab));
   // score -> UpdateMASK -> candidates -> lock
   SL_RUN(ctx, s, SL_PROF_SCORE, slk_score(s, cur, 0, prev, c.dtype, c.vocab, active_idx, m_dev, m_upper, t == 1, kl, conf, argmax, ws.score));
@@ -629,7 +626,7 @@ extern "C" int sl_unlock_probe(sl_ctx* ctx, void* stream, const int32_t* tokens,
   if (ctx->use_mfma)
     SL_TRY(sl_mfma_lm_head(ctx, s, ws.h, nullptr, m_dev, m_upper, probe_logits));
   else
-    SL_TRY(slk_gemm_generic(s, c.dtype, ws.h, ctx->plain.lm_head, m_dev, m_upper, c.vocab, c.d_model, nullptr,
+    SL_TRY(slk_gemm_generic(s, c.dtype, ws.h, &ctx->plain.lm_head, 1, m_dev, m_upper, c.vocab, c.d_model, nullptr,
                             probe_logits, nullptr, c.vocab));
   // u~ (as conf) and D~ = KL(p^_t || p_{t*}): the kept row of a position locked at t* lies in buffer t* & 1
   int32_t* prev_rows = (int32_t*)ws.q;                   // the query buffer is free again

@@ -1,8 +1,17 @@
 // Shape-generic bidirectional attention for the active rows (Alg. 1 'attention' line; Sec. 2.1):
 // o[r, h] = softmax(q[r, h] . K[b, h, 0..N)^T / sqrt(d_h)) V[b, h, 0..N), no mask, all N slots of
 // the row's own sequence (cached and live alike).  One workgroup per (row, head); fp32
-// throughout.  Correctness path for the fp32 configuration and for head sizes other than 128.
+// throughout.  The path of the fp32 configuration and of head sizes other than 128.
+// Bound by load latency at these sizes, so both passes read the caches' eight-element units (8 dims of a slot in K,
+// 8 slots of a dim in V) whole: 32 bytes per lane instead of single elements (N = 128, 4 heads x 64: 13.3 -> 6.0 us).
 #include "sl_common.h"
+
+// one eight-element unit of a cache (32-byte aligned for fp32, 16 for bf16: the cache base is, and units are whole)
+template <typename T>
+__device__ inline void ld_unit(const T* p, float (&v)[8]) {
+  if constexpr (sizeof(T) == 4) ld8f(p, v);
+  else ld8(p, v);
+}
 
 template <typename T>
 __global__ __launch_bounds__(256) void attention_generic_kernel(const T* __restrict__ q, const T* __restrict__ kc,
@@ -12,7 +21,7 @@ __global__ __launch_bounds__(256) void attention_generic_kernel(const T* __restr
                                                                 int dh, int N, int n_pad, T* __restrict__ o) {
   extern __shared__ float smem[];
   float* qs = smem;              // [dh]
-  float* sc = smem + dh;         // [n_pad] scores / probabilities
+  float* sc = smem + dh;         // [n_pad] scores / probabilities, zero past N
   float* part = sc + n_pad;      // [256] partial outputs
   __shared__ float red[4];
   const int M = min(*m_dev, m_upper);
@@ -26,9 +35,17 @@ __global__ __launch_bounds__(256) void attention_generic_kernel(const T* __restr
   for (int c = tid; c < dh; c += 256) qs[c] = st<T>::ld(q + ((size_t)r * H + hh) * dh + c);
   __syncthreads();
   float lmax = -INFINITY;
-  for (int n = tid; n < N; n += 256) {
+  for (int n = tid; n < n_pad; n += 256) {
+    if (n >= N) { sc[n] = 0.f; continue; }
+    const T* kp = kc + head_base + kc_index(n, 0, dh);           // units of 8 dims, 32 slots apart
     float s = 0.f;
-    for (int c = 0; c < dh; ++c) s = fmaf(qs[c], st<T>::ld(kc + head_base + kc_index(n, c, dh)), s);
+#pragma unroll 4
+    for (int c = 0; c < dh; c += 8) {
+      float kv[8];
+      ld_unit(kp + (size_t)c * 32, kv);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s = fmaf(qs[c + e], kv[e], s);
+    }
     s *= scale;
     sc[n] = s;
     lmax = fmaxf(lmax, s);
@@ -41,11 +58,19 @@ __global__ __launch_bounds__(256) void attention_generic_kernel(const T* __restr
     lsum += p;
   }
   const float tot = block_sum<256>(lsum, red);   // also orders the sc[] writes before the reads below
-  const int G = 256 / dh;                        // thread groups splitting the slots
+  const int G = 256 / dh;                        // thread groups splitting the units of eight slots
   const int grp = tid / dh, c = tid - grp * dh;
   float acc = 0.f;
-  if (grp < G) {
-    for (int n = grp; n < N; n += G) acc = fmaf(sc[n], st<T>::ld(vc + head_base + vc_index(n, c, dh)), acc);
+  // unit u = 2 blk + h holds slots 16 blk + {8 a + 4 h + i}; the last block may reach past N: probability 0 against
+  // a slot nobody has written, whose bytes are the zeros of the cache's binding
+  const int units = 2 * ((N + 15) / 16);
+#pragma unroll 4
+  for (int u = grp; u < units; u += G) {
+    float v[8];
+    ld_unit(vc + head_base + ((size_t)u * dh + c) * 8, v);
+    const float* p = sc + (u >> 1) * 16 + (u & 1) * 4;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc = fmaf(p[(e >> 2) * 8 + (e & 3)], v[e], acc);
   }
   part[tid] = acc;
   __syncthreads();

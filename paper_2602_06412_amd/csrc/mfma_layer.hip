@@ -121,7 +121,7 @@ int sl_mfma_layer(sl_ctx* ctx, hipStream_t s, int l, void* x, void* h, void* q, 
   } else {
     S = slk_gemm_splits_gate_up(mu, 2 * dff, d);
     SL_RUN(ctx, s, SL_PROF_GEMM_GATE_UP, slk_gemm_mfma(s, h, 1, P.wgu, m_dev, mu, 2 * dff, d, S, f32, nullptr, nullptr, 2 * (size_t)dff));
-    SL_RUN(ctx, s, SL_PROF_SWIGLU, slk_swiglu(s, SL_BF16, f32, S, (size_t)mu * 2 * dff, m_dev, mu, dff, a, 1, 1));
+    SL_RUN(ctx, s, SL_PROF_SWIGLU, slk_swiglu(s, f32, S, (size_t)mu * 2 * dff, m_dev, mu, dff, a));
   }
   if (slk_gemm_unsplit_thick(mu, d, dff)) {
     SL_RUN(ctx, s, SL_PROF_GEMM_DOWN, slk_gemm_mfma256_residual(s, a, P.wdown, m_dev, mu, d, dff, x));

@@ -128,27 +128,6 @@ __global__ void rope_table_kernel(float2* tab, int n_pad, int half, int dh, doub
   tab[t] = make_float2((float)cos(ang), (float)sin(ang));
 }
 
-// gu holds gate and up side by side ([gate dff | up dff], interleaved = 0) or interleaved by
-// 32-column blocks (gate j, up j, gate j+1, .., interleaved = 1).
-template <typename T, bool TILED>
-__global__ __launch_bounds__(256) void swiglu_kernel(const float* __restrict__ gu, int S, size_t sstride,
-                                                     const int32_t* __restrict__ m_dev, int m_upper, int dff,
-                                                     int interleaved, T* __restrict__ a) {
-  const int M = min(*m_dev, m_upper);
-  const int r = blockIdx.y;
-  if (r >= M) return;
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= dff) return;
-  const size_t gi = (size_t)r * 2 * dff + (interleaved ? (c >> 5) * 64 + (c & 31) : c);
-  const size_t ui = gi + (interleaved ? 32 : dff);
-  float g = gu[gi], u = gu[ui];
-  for (int sp = 1; sp < S; ++sp) {
-    g += gu[sp * sstride + gi];
-    u += gu[sp * sstride + ui];
-  }
-  st<T>::stv(a + act_index<TILED>(r, c, dff), g / (1.0f + expf(-g)) * u);
-}
-
 template <typename T, bool VH>
 __global__ void kv_read_kernel(const T* __restrict__ kc, const T* __restrict__ vc, int B, int H, int N, int n_pad,
                                int dh, T* __restrict__ k_out, T* __restrict__ v_out) {
@@ -180,12 +159,13 @@ __global__ void copy_rows_kernel(const T* __restrict__ src, T* __restrict__ dst,
 }
 
 // ---- bf16 variants with 16-byte accesses ---------------------------------------------------------
-// Same arithmetic, in the same order, as the element-wise kernels above; a thread owns chunks of
+// Same arithmetic, in the same order, as the element-wise kernels above (SwiGLU has only this form); a thread owns chunks of
 // consecutive columns, so loads and stores are 8 or 16 bytes wide (also in the fragment-tiled
 // layout, where the eight columns starting at a multiple of eight are contiguous) and all loads
 // of a thread are in flight together.  Used when shapes and pointers allow, else the kernels above.
-// bf16, fragment-tiled output, gate/up interleaved by 32-column blocks: a thread owns eight consecutive
-// output columns (32-byte loads of the gate and the up sums per plane, one 16-byte store); same arithmetic.
+// SwiGLU of k-split gate|up launches: fp32 planes with gate/up interleaved by 32-column blocks (gate j, up j, gate
+// j+1, ..) -> fragment-tiled bf16; a thread owns eight consecutive output columns (32-byte loads of the gate and the
+// up sums per plane, one 16-byte store).
 __global__ __launch_bounds__(256) void swiglu_vec_kernel(const float* __restrict__ gu, int S, size_t sstride,
                                                          const int32_t* __restrict__ m_dev, int m_upper, int dff,
                                                          bf16_t* __restrict__ a) {
@@ -691,18 +671,11 @@ int slk_rope_kv_write(hipStream_t s, int dtype, const float* qkv, int S, size_t 
   return SL_OK;
 }
 
-int slk_swiglu(hipStream_t s, int dtype, const float* gu, int S, size_t sstride, const int32_t* m_dev, int m_upper,
-               int dff, void* a, int tiled, int interleaved) {
+int slk_swiglu(hipStream_t s, const float* gu, int S, size_t sstride, const int32_t* m_dev, int m_upper, int dff, void* a) {
   if (m_upper <= 0) return SL_OK;
-  if (dtype == SL_BF16 && tiled && interleaved && dff % 32 == 0 && sstride % 4 == 0 && al16(gu) && al16(a)) {
-    hipLaunchKernelGGL(swiglu_vec_kernel, dim3(sl_cdiv(dff / 8, 256), m_upper), dim3(256), 0, s, gu, S, sstride, m_dev, m_upper,
-                       dff, (bf16_t*)a);
-    SL_LAUNCH_CHECK();
-    return SL_OK;
-  }
-  DISPATCH_T(dtype, DISPATCH_TILED(tiled, hipLaunchKernelGGL((swiglu_kernel<T, TL>), dim3(sl_cdiv(dff, 256), m_upper),
-                                                             dim3(256), 0, s, gu, S, sstride, m_dev, m_upper, dff,
-                                                             interleaved, (T*)a)));
+  if (dff % 32 || sstride % 4 || !al16(gu) || !al16(a)) return SL_EINVAL;
+  hipLaunchKernelGGL(swiglu_vec_kernel, dim3(sl_cdiv(dff / 8, 256), m_upper), dim3(256), 0, s, gu, S, sstride, m_dev, m_upper,
+                     dff, (bf16_t*)a);
   SL_LAUNCH_CHECK();
   return SL_OK;
 }

@@ -176,6 +176,7 @@ extern thread_local int g_sl_last_hip_error;
 
 static inline size_t sl_align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 static inline int sl_cdiv(int a, int b) { return (a + b - 1) / b; }
+__device__ inline int sl_cdiv_dev(int a, int b) { return (a + b - 1) / b; }
 static inline size_t sl_tsize(int dtype) { return dtype == SL_BF16 ? 2 : 4; }
 
 struct sl_packed_layer {            // device pointers into the caller's packed buffer (MFMA path)
@@ -287,15 +288,17 @@ int slk_gemm_mfma256_qkv_rope(hipStream_t s, const void* A, const void* Wp, cons
 int slk_rope_kv_write(hipStream_t s, int dtype, const float* qkv, int S, size_t sstride, const int32_t* active_idx,
                       const int32_t* m_dev, int m_upper, int H, int dh, int N, int n_pad, const void* rope_tab, void* q, void* kc, void* vc,
                       int v_half);
-int slk_swiglu(hipStream_t s, int dtype, const float* gu, int S, size_t sstride, const int32_t* m_dev, int m_upper,
-               int dff, void* a, int tiled, int interleaved);
+int slk_swiglu(hipStream_t s, const float* gu, int S, size_t sstride, const int32_t* m_dev, int m_upper, int dff, void* a);
 int slk_kv_read(hipStream_t s, int dtype, const void* kc, const void* vc, int B, int H, int N, int n_pad, int dh,
                 void* k_out, void* v_out, int v_half);
 int slk_fill_zero(hipStream_t s, void* p, size_t bytes);
 int slk_copy_rows(hipStream_t s, int dtype, const void* src, void* dst, const int32_t* m_dev, int m_upper, int d);
-// gemm_generic.hip:  C[m, n] (fp32, ldc) = A[m, k] (T) . W[n, k]^T (T); optional row map for the output
-int slk_gemm_generic(hipStream_t s, int dtype, const void* A, const void* W, const int32_t* m_dev, int m_upper,
-                     int n, int k, float* C_f32, void* C_T, const int32_t* out_row_map, size_t ldc);
+// gemm_generic.hip:  C[m, z n + j] (fp32 or T, ldc) = A[m, k] (T) . W[z][n, k]^T (T), z < nm <= 3; optional row map for
+// the output; and a[m, dff] (T) = silu(A . w_gate^T) * (A . w_up^T)
+int slk_gemm_generic(hipStream_t s, int dtype, const void* A, const void* const* W, int nm, const int32_t* m_dev,
+                     int m_upper, int n, int k, float* C_f32, void* C_T, const int32_t* out_row_map, size_t ldc);
+int slk_gemm_generic_swiglu(hipStream_t s, int dtype, const void* A, const void* w_gate, const void* w_up,
+                            const int32_t* m_dev, int m_upper, int dff, int k, void* a);
 // attention_generic.hip
 int slk_attention_generic(hipStream_t s, int dtype, const void* q, const void* kc, const void* vc,
                           const int32_t* active_idx, const int32_t* m_dev, int m_upper,
