@@ -107,7 +107,7 @@ int sl_mfma_layer(sl_ctx* ctx, hipStream_t s, int l, void* x, void* h, void* q, 
   if (slk_gemm_unsplit_thick(mu, d, hd)) {
     // thick launches: the residual add runs in the projection's epilogue, the norm reads the new x
     SL_RUN(ctx, s, SL_PROF_GEMM_OUT, slk_gemm_mfma256_residual(s, o, P.wo, m_dev, mu, d, hd, x));
-    SL_RUN(ctx, s, SL_PROF_ADD_NORM, slk_rmsnorm(s, SL_BF16, x, m_dev, mu, d, L.ffn_norm, c.rms_eps, h, 1));
+    SL_RUN(ctx, s, SL_PROF_ADD_NORM, slk_rmsnorm(s, SL_BF16, x, nullptr, m_dev, mu, d, L.ffn_norm, c.rms_eps, h, 1));
   } else {
     S = slk_gemm_splits(mu, d, hd);
     SL_RUN(ctx, s, SL_PROF_GEMM_OUT, slk_gemm_mfma(s, o, 1, P.wo, m_dev, mu, d, hd, S, f32, nullptr, nullptr, d));
@@ -125,7 +125,7 @@ int sl_mfma_layer(sl_ctx* ctx, hipStream_t s, int l, void* x, void* h, void* q, 
   }
   if (slk_gemm_unsplit_thick(mu, d, dff)) {
     SL_RUN(ctx, s, SL_PROF_GEMM_DOWN, slk_gemm_mfma256_residual(s, a, P.wdown, m_dev, mu, d, dff, x));
-    SL_RUN(ctx, s, SL_PROF_ADD_NORM, slk_rmsnorm(s, SL_BF16, x, m_dev, mu, d, next_gain, c.rms_eps, h, 1));
+    SL_RUN(ctx, s, SL_PROF_ADD_NORM, slk_rmsnorm(s, SL_BF16, x, nullptr, m_dev, mu, d, next_gain, c.rms_eps, h, 1));
   } else {
     S = slk_gemm_splits(mu, d, dff);
     SL_RUN(ctx, s, SL_PROF_GEMM_DOWN, slk_gemm_mfma(s, a, 1, P.wdown, m_dev, mu, d, dff, S, f32, nullptr, nullptr, d));

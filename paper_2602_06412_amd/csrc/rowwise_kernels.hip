@@ -36,10 +36,10 @@ __global__ __launch_bounds__(kRowThreads) void embed_rmsnorm_kernel(const T* __r
     st<T>::stv(h + act_index<TILED>(r, c, d), st<T>::ld(src + c) * rstd * st<T>::ld(gain + c));
 }
 
-// x <- rnd(x + delta) (residual add in fp32; delta may arrive as S k-split partials),
-// then h = RMSNorm of the STORED x.
+// ADD: x <- rnd(x + delta) (residual add in fp32; delta may arrive as S k-split partials), then h = RMSNorm of the
+// STORED x.  Else h = RMSNorm(src), and x, unless null, receives a copy of src (which may be x itself).
 template <typename T, bool ADD, bool TILED>
-__global__ __launch_bounds__(kRowThreads) void add_rmsnorm_kernel(T* x, const float* __restrict__ delta, int S,
+__global__ __launch_bounds__(kRowThreads) void add_rmsnorm_kernel(const T* src, T* x, const float* __restrict__ delta, int S,
                                                                   size_t sstride,
                                                                   const int32_t* __restrict__ m_dev, int m_upper,
                                                                   int d, const T* __restrict__ gain, float eps,
@@ -49,9 +49,11 @@ __global__ __launch_bounds__(kRowThreads) void add_rmsnorm_kernel(T* x, const fl
   const int r = blockIdx.x;
   if (r >= M) return;
   T* xr = x + (size_t)r * d;
+  const T* sr = ADD ? xr : src + (size_t)r * d;
   float ssq = 0.f;
   for (int c = threadIdx.x; c < d; c += kRowThreads) {
-    float v = st<T>::ld(xr + c);
+    float v = st<T>::ld(sr + c);
+    if (!ADD && x != nullptr) xr[c] = sr[c];
     if (ADD) {
       const float* dp = delta + (size_t)r * d + c;
       float dl = dp[0];
@@ -70,7 +72,7 @@ __global__ __launch_bounds__(kRowThreads) void add_rmsnorm_kernel(T* x, const fl
   ssq = block_sum<kRowThreads>(ssq, sh);
   const float rstd = 1.0f / sqrtf(ssq / (float)d + eps);
   for (int c = threadIdx.x; c < d; c += kRowThreads)   // each thread re-reads what it wrote itself
-    st<T>::stv(h + act_index<TILED>(r, c, d), st<T>::ld(xr + c) * rstd * st<T>::ld(gain + c));
+    st<T>::stv(h + act_index<TILED>(r, c, d), st<T>::ld(sr + c) * rstd * st<T>::ld(gain + c));
 }
 
 // q, k <- rnd(RoPE(q, k)) at the row's fixed slot; v <- rnd(v); k, v go to the row's own
@@ -237,8 +239,8 @@ __device__ inline void ld4(const bf16_t* p, float (&v)[4]) {
   for (int e = 0; e < 4; ++e) v[e] = (float)u[e];
 }
 template <bool ADD, bool TILED>
-__global__ __launch_bounds__(kRowThreads) void add_rmsnorm_vec_kernel(bf16_t* x, const float* __restrict__ delta, int S,
-                                                                      size_t sstride,
+__global__ __launch_bounds__(kRowThreads) void add_rmsnorm_vec_kernel(const bf16_t* src, bf16_t* x,
+                                                                      const float* __restrict__ delta, int S, size_t sstride,
                                                                       const int32_t* __restrict__ m_dev, int m_upper,
                                                                       int d, const bf16_t* __restrict__ gain,
                                                                       float eps, bf16_t* __restrict__ h) {
@@ -247,6 +249,7 @@ __global__ __launch_bounds__(kRowThreads) void add_rmsnorm_vec_kernel(bf16_t* x,
   const int r = blockIdx.x;
   if (r >= M) return;
   bf16_t* xr = x + (size_t)r * d;
+  const bf16_t* sr = ADD ? xr : src + (size_t)r * d;
   const int nch = d >> 3;
   float v[kMaxChunks][8];
   float ssq = 0.f;
@@ -254,7 +257,8 @@ __global__ __launch_bounds__(kRowThreads) void add_rmsnorm_vec_kernel(bf16_t* x,
   for (int j = 0; j < kMaxChunks; ++j) {
     const int c8 = threadIdx.x + j * kRowThreads;
     if (c8 < nch) {
-      ld8(xr + c8 * 8, v[j]);
+      ld8(sr + c8 * 8, v[j]);
+      if (!ADD && x != nullptr) st8(xr + c8 * 8, v[j]);
       if (ADD) {
         const float* dp = delta + (size_t)r * d + c8 * 8;
         float dl[8];
@@ -302,8 +306,8 @@ __global__ __launch_bounds__(kRowThreads) void add_rmsnorm_vec_kernel(bf16_t* x,
 // traffic per workgroup in the norm-only form); this one keeps a wave streaming: norm-only at 8192 rows
 // 65 -> 38 us.  Taken from 2048 rows on (at 512 rows its 128 workgroups leave half the chip idle).
 template <bool ADD, bool TILED, int CH>
-__global__ __launch_bounds__(256) void add_rmsnorm_wave_kernel(bf16_t* x, const float* __restrict__ delta, int S,
-                                                               size_t sstride, const int32_t* __restrict__ m_dev,
+__global__ __launch_bounds__(256) void add_rmsnorm_wave_kernel(const bf16_t* src, bf16_t* x,
+                                                               const float* __restrict__ delta, int S, size_t sstride, const int32_t* __restrict__ m_dev,
                                                                int m_upper, const bf16_t* __restrict__ gain, float eps,
                                                                bf16_t* __restrict__ h) {
   constexpr int d = 512 * CH;
@@ -311,12 +315,14 @@ __global__ __launch_bounds__(256) void add_rmsnorm_wave_kernel(bf16_t* x, const 
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (r >= M) return;
   bf16_t* xr = x + (size_t)r * d;
+  const bf16_t* sr = ADD ? xr : src + (size_t)r * d;
   float v[CH][8];
   float ssq = 0.f;
 #pragma unroll
   for (int j = 0; j < CH; ++j) {
     const int c8 = lane + j * 64;
-    ld8(xr + c8 * 8, v[j]);
+    ld8(sr + c8 * 8, v[j]);
+    if (!ADD && x != nullptr) st8(xr + c8 * 8, v[j]);
     if (ADD) {
       const float* dp = delta + (size_t)r * d + c8 * 8;
       float dl[8];
@@ -578,7 +584,7 @@ int slk_add_rmsnorm(hipStream_t s, int dtype, void* x, const float* delta, int S
   if (dtype == SL_BF16 && d == 4096 && m_upper >= kWaveRowsMin && sstride % 4 == 0 && al16(x) && al16(delta) && al16(gain) &&
       al16(h)) {
     DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_wave_kernel<true, TL, 8>), dim3(sl_cdiv(m_upper, 4)), dim3(256), 0, s,
-                                             (bf16_t*)x, delta, S, sstride, m_dev, m_upper, (const bf16_t*)gain, eps,
+                                             (const bf16_t*)x, (bf16_t*)x, delta, S, sstride, m_dev, m_upper, (const bf16_t*)gain, eps,
                                              (bf16_t*)h));
     SL_LAUNCH_CHECK();
     return SL_OK;
@@ -586,37 +592,37 @@ int slk_add_rmsnorm(hipStream_t s, int dtype, void* x, const float* delta, int S
   if (dtype == SL_BF16 && d % 8 == 0 && d <= 8 * kRowThreads * kMaxChunks && sstride % 4 == 0 && al16(x) && al16(delta) &&
       al16(gain) && al16(h)) {
     DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_vec_kernel<true, TL>), dim3(m_upper), dim3(kRowThreads), 0, s,
-                                             (bf16_t*)x, delta, S, sstride, m_dev, m_upper, d, (const bf16_t*)gain,
+                                             (const bf16_t*)x, (bf16_t*)x, delta, S, sstride, m_dev, m_upper, d, (const bf16_t*)gain,
                                              eps, (bf16_t*)h));
     SL_LAUNCH_CHECK();
     return SL_OK;
   }
   DISPATCH_T(dtype, DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_kernel<T, true, TL>), dim3(m_upper),
-                                                             dim3(kRowThreads), 0, s, (T*)x, delta, S, sstride,
+                                                             dim3(kRowThreads), 0, s, (const T*)x, (T*)x, delta, S, sstride,
                                                              m_dev, m_upper, d, (const T*)gain, eps, (T*)h)));
   SL_LAUNCH_CHECK();
   return SL_OK;
 }
 
-int slk_rmsnorm(hipStream_t s, int dtype, const void* x, const int32_t* m_dev, int m_upper, int d, const void* gain,
+int slk_rmsnorm(hipStream_t s, int dtype, const void* src, void* x, const int32_t* m_dev, int m_upper, int d, const void* gain,
                 float eps, void* h, int tiled) {
   if (m_upper <= 0) return SL_OK;
-  if (dtype == SL_BF16 && d == 4096 && m_upper >= kWaveRowsMin && al16(x) && al16(gain) && al16(h)) {
+  if (dtype == SL_BF16 && d == 4096 && m_upper >= kWaveRowsMin && al16(src) && al16(x) && al16(gain) && al16(h)) {
     DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_wave_kernel<false, TL, 8>), dim3(sl_cdiv(m_upper, 4)), dim3(256), 0,
-                                             s, (bf16_t*)const_cast<void*>(x), (const float*)nullptr, 1, (size_t)0, m_dev,
+                                             s, (const bf16_t*)src, (bf16_t*)x, (const float*)nullptr, 1, (size_t)0, m_dev,
                                              m_upper, (const bf16_t*)gain, eps, (bf16_t*)h));
     SL_LAUNCH_CHECK();
     return SL_OK;
   }
-  if (dtype == SL_BF16 && d % 8 == 0 && d <= 8 * kRowThreads * kMaxChunks && al16(x) && al16(gain) && al16(h)) {
+  if (dtype == SL_BF16 && d % 8 == 0 && d <= 8 * kRowThreads * kMaxChunks && al16(src) && al16(x) && al16(gain) && al16(h)) {
     DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_vec_kernel<false, TL>), dim3(m_upper), dim3(kRowThreads), 0, s,
-                                             (bf16_t*)const_cast<void*>(x), (const float*)nullptr, 1, (size_t)0, m_dev,
+                                             (const bf16_t*)src, (bf16_t*)x, (const float*)nullptr, 1, (size_t)0, m_dev,
                                              m_upper, d, (const bf16_t*)gain, eps, (bf16_t*)h));
     SL_LAUNCH_CHECK();
     return SL_OK;
   }
   DISPATCH_T(dtype, DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_kernel<T, false, TL>), dim3(m_upper),
-                                                             dim3(kRowThreads), 0, s, (T*)const_cast<void*>(x),
+                                                             dim3(kRowThreads), 0, s, (const T*)src, (T*)x,
                                                              (const float*)nullptr, 1, (size_t)0, m_dev, m_upper, d,
                                                              (const T*)gain, eps, (T*)h)));
   SL_LAUNCH_CHECK();

@@ -277,7 +277,8 @@ int slk_embed_rmsnorm(hipStream_t s, int dtype, const void* emb, const int32_t* 
 // delta / qkv / gu may be S k-split partials, `sstride` floats apart; they are summed in split order
 int slk_add_rmsnorm(hipStream_t s, int dtype, void* x, const float* delta, int S, size_t sstride,
                     const int32_t* m_dev, int m_upper, int d, const void* gain, float eps, void* h, int tiled);
-int slk_rmsnorm(hipStream_t s, int dtype, const void* x, const int32_t* m_dev, int m_upper, int d,
+// h = RMSNorm(src); x, unless null, receives a copy of src (x must not overlap src)
+int slk_rmsnorm(hipStream_t s, int dtype, const void* src, void* x, const int32_t* m_dev, int m_upper, int d,
                 const void* gain, float eps, void* h, int tiled);
 int slk_rope_table(hipStream_t s, void* tab, int n_pad, int dh, float theta);
 int slk_gemm_mfma256_residual(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int n, int k,
