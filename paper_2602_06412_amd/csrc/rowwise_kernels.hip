@@ -364,8 +364,8 @@ __global__ __launch_bounds__(256) void add_rmsnorm_wave_kernel(const bf16_t* src
 
 // Thin-launch variant.  One thread per (head, four rotation pairs): fp32 loads are 16 bytes and
 // those of a wave contiguous, q and K leave as 8-byte stores (consecutive dims
-// of one slot are contiguous in the K layout); V keeps 2-byte stores, its layout puts eight
-// SLOTS side by side, not eight dims.
+// of one slot are contiguous in the K layout).  Measured with four planes at 224 rows, all planes of an item in
+// flight and V by way of LDS: 12.1 -> 10.7 us.
 template <bool VH>
 __global__ __launch_bounds__(256) void rope_kv_write_vec_kernel(const float* __restrict__ qkv, int S, size_t sstride,
                                                                 const int32_t* __restrict__ active_idx,
@@ -374,41 +374,53 @@ __global__ __launch_bounds__(256) void rope_kv_write_vec_kernel(const float* __r
                                                                 const float2* __restrict__ rope_tab,
                                                                 bf16_t* __restrict__ q, bf16_t* __restrict__ kc,
                                                                 bf16_t* __restrict__ vc) {
-  const int M = min(*m_dev, m_upper);
+  // (the row's planes do not wait for the device-side count: a row past it is still inside the buffer.  Its entry of
+  // active_idx need not be, so the slot is read behind the count.)
   const int r = blockIdx.x;
-  if (r >= M) return;
-  const int g = active_idx[r];
-  const int b = g / N, i = g - b * N;
+  const int M = min(*m_dev, m_upper);
+  const int g = r < M ? active_idx[r] : 0;
   const int half = dh >> 1, hd = H * dh, per_head = half >> 2;
   const float* row = qkv + (size_t)r * 3 * hd;
+  extern __shared__ bf16_t v_sh[];                       // V of this workgroup's dims, in (head, dim) order
   // gridDim.y workgroups share a row (a launch of few rows would otherwise leave most CUs without a workgroup)
-  const int per_wg = (H * per_head + gridDim.y - 1) / gridDim.y, t_end = min(H * per_head, (int)(blockIdx.y + 1) * per_wg);
-  for (int t = blockIdx.y * per_wg + threadIdx.x; t < t_end; t += blockDim.x) {
-    const int hh = t / per_head, j = (t - hh * per_head) * 4;
+  const int per_wg = H * per_head / gridDim.y;           // a whole number of heads
+  const int t0 = blockIdx.y * per_wg;
+  for (int t = threadIdx.x; t < per_wg; t += blockDim.x) {
+    const int hh = (t0 + t) / per_head, j = (t0 + t - hh * per_head) * 4;
     const int c0 = hh * dh + j, c1 = c0 + half;
-    float q0[4], q1[4], k0[4], k1[4], v0[4], v1[4], cs0[4], cs1[4];
-    ld4f(row + c0, q0); ld4f(row + c1, q1);
-    ld4f(row + hd + c0, k0); ld4f(row + hd + c1, k1);
-    ld4f(row + 2 * hd + c0, v0); ld4f(row + 2 * hd + c1, v1);
+    const int off[6] = {c0, c1, hd + c0, hd + c1, 2 * hd + c0, 2 * hd + c1};      // q, k, v: dims j .., j + half ..
+    float a[6][4];
+#pragma unroll
+    for (int z = 0; z < 6; ++z) ld4f(row + off[z], a[z]);
+    for (int sp0 = 1; sp0 < S; sp0 += 3) {               // k-split partials, fixed order, three planes in flight
+      float p[3][6][4];
+#pragma unroll
+      for (int y = 0; y < 3; ++y)
+        if (sp0 + y < S) {
+#pragma unroll
+          for (int z = 0; z < 6; ++z) ld4f(row + (size_t)(sp0 + y) * sstride + off[z], p[y][z]);
+        }
+#pragma unroll
+      for (int y = 0; y < 3; ++y)
+        if (sp0 + y < S) {
+#pragma unroll
+          for (int z = 0; z < 6; ++z)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[z][e] += p[y][z][e];
+        }
+    }
+    if (r >= M) return;                                  // uniform over the workgroup
+    const int b = g / N, i = g - b * N;
+    float cs0[4], cs1[4], qa[4], qb[4], ka[4], kb[4];
     const float* tab = reinterpret_cast<const float*>(rope_tab + (size_t)i * half + j);   // (cos, sin) x 4
     ld4f(tab, cs0); ld4f(tab + 4, cs1);
-    for (int sp = 1; sp < S; ++sp) {                     // k-split partials, fixed order
-      const float* pr = row + sp * sstride;
-      float p[4];
-#define SL_ACC4(dst, src) do { ld4f(src, p); _Pragma("unroll") for (int e = 0; e < 4; ++e) dst[e] += p[e]; } while (0)
-      SL_ACC4(q0, pr + c0); SL_ACC4(q1, pr + c1);
-      SL_ACC4(k0, pr + hd + c0); SL_ACC4(k1, pr + hd + c1);
-      SL_ACC4(v0, pr + 2 * hd + c0); SL_ACC4(v1, pr + 2 * hd + c1);
-#undef SL_ACC4
-    }
-    float qa[4], qb[4], ka[4], kb[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const float c = e < 2 ? cs0[2 * e] : cs1[2 * (e - 2)], sn = e < 2 ? cs0[2 * e + 1] : cs1[2 * (e - 2) + 1];
-      qa[e] = q0[e] * c - q1[e] * sn;
-      qb[e] = q1[e] * c + q0[e] * sn;
-      ka[e] = k0[e] * c - k1[e] * sn;
-      kb[e] = k1[e] * c + k0[e] * sn;
+      qa[e] = a[0][e] * c - a[1][e] * sn;
+      qb[e] = a[1][e] * c + a[0][e] * sn;
+      ka[e] = a[2][e] * c - a[3][e] * sn;
+      kb[e] = a[3][e] * c + a[2][e] * sn;
     }
     st4(q + (size_t)r * hd + c0, qa);
     st4(q + (size_t)r * hd + c1, qb);
@@ -416,11 +428,22 @@ __global__ __launch_bounds__(256) void rope_kv_write_vec_kernel(const float* __r
     const size_t head_base = ((size_t)b * H + hh) * n_pad * dh;
     st4(kc + head_base + kc_index(i, j, dh), ka);
     st4(kc + head_base + kc_index(i, j + half, dh), kb);
+    bf16_t* vs = v_sh + (hh - t0 / per_head) * dh + j;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      vc[head_base + vc_index(i, j + e, dh)] = vcache_elem<VH>(v0[e]);
-      vc[head_base + vc_index(i, j + half + e, dh)] = vcache_elem<VH>(v1[e]);
+      vs[e] = vcache_elem<VH>(a[4][e]);
+      vs[half + e] = vcache_elem<VH>(a[5][e]);
     }
+  }
+  if (r >= M || kc == nullptr) return;
+  // V keeps 2-byte stores (its layout puts eight SLOTS side by side, not eight dims), but dim by dim along the lanes:
+  // a wave's store then touches 8 lines instead of 32
+  __syncthreads();
+  const int b = g / N, i = g - b * N;
+  const int h0 = t0 / per_head, dims = per_wg / per_head * dh;
+  for (int t = threadIdx.x; t < dims; t += blockDim.x) {
+    const int hh = h0 + t / dh, dd = t % dh;
+    vc[((size_t)b * H + hh) * n_pad * dh + vc_index(i, dd, dh)] = v_sh[t];
   }
 }
 
@@ -646,9 +669,10 @@ int slk_rope_kv_write(hipStream_t s, int dtype, const float* qkv, int S, size_t 
   // kc = vc = null: rotate and store the queries only (the row-per-workgroup kernels skip the cache stores)
   // thin launches are latency-bound (wide accesses, few instructions win); thick ones are bound by the
   // scattered 2-byte V stores, where the element-wise kernel's many threads per row do better
-  if ((m_upper <= 256 || kc == nullptr) && dtype == SL_BF16 && dh % 8 == 0 && sstride % 4 == 0 && al16(rope_tab) && al16(qkv) && al16(q) && al16(kc) && al16(vc)) {
-    const int per_row = H * (dh / 8), wgs = per_row >= 512 && m_upper <= 256 ? 2 : 1;   // (head, four pairs) items per row
-    hipLaunchKernelGGL(v_half ? rope_kv_write_vec_kernel<true> : rope_kv_write_vec_kernel<false>, dim3(m_upper, wgs), dim3(256), 0,
+  const int per_row = H * (dh / 8), wgs = per_row >= 512 && m_upper <= 256 && H % 2 == 0 ? 2 : 1;   // (head, four pairs) items per row
+  const size_t v_lds = kc == nullptr ? 0 : (size_t)(H / wgs) * dh * 2;     // V of a workgroup's heads on its way out
+  if ((m_upper <= 256 || kc == nullptr) && v_lds <= 64 * 1024 && dtype == SL_BF16 && dh % 8 == 0 && sstride % 4 == 0 && al16(rope_tab) && al16(qkv) && al16(q) && al16(kc) && al16(vc)) {
+    hipLaunchKernelGGL(v_half ? rope_kv_write_vec_kernel<true> : rope_kv_write_vec_kernel<false>, dim3(m_upper, wgs), dim3(256), v_lds,
                        s, qkv, S, sstride, active_idx, m_dev, m_upper, H, dh, N, n_pad, (const float2*)rope_tab, (bf16_t*)q,
                        (bf16_t*)kc, (bf16_t*)vc);
     SL_LAUNCH_CHECK();
