@@ -571,13 +571,18 @@ __global__ __launch_bounds__(256, 3) void attention_trio_kernel(const bf16_t* __
 // barrier in the loop), the next tile's fragments are requested before the current tile is computed.
 // Same fragment layouts as the kernels above; P is carried as two halves (hi + lo, 22 bits: the
 // matrix pipe idles here anyway).
+// SPLIT: as above, for sequences whose tiles are too many for four waves; each workgroup leaves its merged sums to
+// attention_merge_kernel.
 constexpr int QTT = 32;          // queries per workgroup of the thin kernel
+template <bool SPLIT>
 __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __restrict__ q,
                                                                 const bf16_t* __restrict__ kc,
                                                                 const bf16_t* __restrict__ vc,
                                                                 const int32_t* __restrict__ active_idx,
                                                                 const int32_t* __restrict__ m_dev, int m_upper, int B,
-                                                                int H, int N, int n_pad, bf16_t* __restrict__ o) {
+                                                                int H, int N, int n_pad, bf16_t* __restrict__ o,
+                                                                int tiles_per_split, float* __restrict__ part_o,
+                                                                float* __restrict__ part_ml) {
   extern __shared__ FragA lds[];             // the merge: partial O [4 waves][16][64 lanes] float4 | (m, l) [4][64]
   __shared__ int cu[kMaxBatch + 2];
   constexpr int TILE_F = KT * DH / 8;
@@ -608,7 +613,8 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
   const size_t head_base = ((size_t)b * H + hh) * n_pad * DH;
   const FragA* kg = reinterpret_cast<const FragA*>(kc + head_base) + lane;
   const FragA* vg = reinterpret_cast<const FragA*>(vc + head_base) + (lane >> 5) * DH + (lane & 31);
-  const int n_tiles = n_pad / KT;
+  const int t_lo = SPLIT ? blockIdx.z * tiles_per_split : 0;
+  const int t_hi = SPLIT ? min(n_pad / KT, t_lo + tiles_per_split) : n_pad / KT;
 
   // every wave holds the same 32 queries: lane = query (lane & 31), dims ks*16 + (lane>>5)*8 .. +7
   const int my_row = row0 + (lane & 31);
@@ -704,38 +710,38 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
   // this wave's tiles: wave, wave + 4, ..; two register sets, the next tile is requested before the current one is used
   {
     FragA k0[16], v0[16], k1[16], v1[16];
-    int t = wave;
-    if (t < n_tiles) load_kv(t, k0, v0);
-    while (t < n_tiles) {
-      if (t + 4 < n_tiles) load_kv(t + 4, k1, v1);
+    int t = t_lo + wave;
+    if (t < t_hi) load_kv(t, k0, v0);
+    while (t < t_hi) {
+      if (t + 4 < t_hi) load_kv(t + 4, k1, v1);
       tile_step(t, k0, v0);
       t += 4;
-      if (t >= n_tiles) break;
-      if (t + 4 < n_tiles) load_kv(t + 4, k0, v0);
+      if (t >= t_hi) break;
+      if (t + 4 < t_hi) load_kv(t + 4, k0, v0);
       tile_step(t, k1, v1);
       t += 4;
     }
   }
   // merge the four waves' partial results: wave w finishes dims 32 w .. 32 w + 31.  Lanes stand side by side in LDS: a
   // lane's 64 sums in a row put all lanes on the same banks, 2 us of the launch (16 rows, N = 512: 10.1 -> 8.3 us).
-  float4* part_o = reinterpret_cast<float4*>(lds);                     // [4 waves][16 pieces][64 lanes]
-  float2* part_ml = reinterpret_cast<float2*>(part_o + 4 * 16 * 64);   // [4][64]
+  float4* sh_o = reinterpret_cast<float4*>(lds);                     // [4 waves][16 pieces][64 lanes]
+  float2* sh_ml = reinterpret_cast<float2*>(sh_o + 4 * 16 * 64);   // [4][64]
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   {
-    float4* po = part_o + wave * 16 * 64 + lane;
+    float4* po = sh_o + wave * 16 * 64 + lane;
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
       for (int g = 0; g < 4; ++g)
         po[(mb * 4 + g) * 64] =
             make_float4(acc_o[mb][4 * g], acc_o[mb][4 * g + 1], acc_o[mb][4 * g + 2], acc_o[mb][4 * g + 3]);
-    part_ml[wave * 64 + lane] = make_float2(m_run * sc, l_tot);         // reference in the exp2 domain (-inf: no tile)
+    sh_ml[wave * 64 + lane] = make_float2(m_run * sc, l_tot);         // reference in the exp2 domain (-inf: no tile)
   }
   __syncthreads();
   float2 ml[4];
   float mx = -INFINITY;
 #pragma unroll
-  for (int z = 0; z < 4; ++z) { ml[z] = part_ml[z * 64 + lane]; mx = fmaxf(mx, ml[z].x); }
+  for (int z = 0; z < 4; ++z) { ml[z] = sh_ml[z * 64 + lane]; mx = fmaxf(mx, ml[z].x); }
   float num[16], den = 0.f;
 #pragma unroll
   for (int v = 0; v < 16; ++v) num[v] = 0.f;
@@ -745,12 +751,26 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
     den = fmaf(w, ml[z].y, den);
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      const float4 pz = part_o[(z * 16 + wave * 4 + g) * 64 + lane];
+      const float4 pz = sh_o[(z * 16 + wave * 4 + g) * 64 + lane];
       num[4 * g] = fmaf(w, pz.x, num[4 * g]);
       num[4 * g + 1] = fmaf(w, pz.y, num[4 * g + 1]);
       num[4 * g + 2] = fmaf(w, pz.z, num[4 * g + 2]);
       num[4 * g + 3] = fmaf(w, pz.w, num[4 * g + 3]);
     }
+  }
+  if constexpr (SPLIT) {
+    if (my_row < row_end) {
+      const size_t slot = ((size_t)blockIdx.z * m_upper + my_row) * H + hh;
+      float* po = part_o + slot * DH + wave * 32 + 4 * (lane >> 5);
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<float4*>(po + 8 * g) = make_float4(num[4 * g], num[4 * g + 1], num[4 * g + 2], num[4 * g + 3]);
+      if (wave == 0 && lane < 32) {
+        part_ml[slot * 2] = mx;
+        part_ml[slot * 2 + 1] = den;
+      }
+    }
+    return;
   }
   const float inv = 1.0f / den;
   if (my_row < row_end) {
@@ -764,24 +784,52 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
   }
 }
 
-// o[row, h, :] = sum_z 2^(m_z - m) O_z / sum_z 2^(m_z - m) l_z over the key splits z
-__global__ __launch_bounds__(128) void attention_merge_kernel(const float* __restrict__ part_o,
-                                                              const float* __restrict__ part_ml,
-                                                              const int32_t* __restrict__ m_dev, int m_upper, int H,
-                                                              int Z, bf16_t* __restrict__ o) {
+// o[row, h, :] = sum_z 2^(m_z - m) O_z / sum_z 2^(m_z - m) l_z over the key splits z.  Four dims per thread, 32 threads
+// per (row, head); a launch of few rows is one chain of memory latencies, so four splits are read at a time, sums and
+// weights together (64 rows, one dim per thread and a maximum pass first: 6.7 us; so: 4.6 us).
+constexpr int kMergeHeads = 8;      // (row, head) pairs per workgroup
+__global__ __launch_bounds__(32 * kMergeHeads) void attention_merge_kernel(const float* __restrict__ part_o,
+                                                                           const float* __restrict__ part_ml,
+                                                                           const int32_t* __restrict__ m_dev,
+                                                                           int m_upper, int H, int Z,
+                                                                           bf16_t* __restrict__ o) {
   const int M = min(*m_dev, m_upper);
-  const int row = blockIdx.x, hh = blockIdx.y, dd = threadIdx.x;
-  if (row >= M) return;
-  float mx = -INFINITY;
-  for (int z = 0; z < Z; ++z) mx = fmaxf(mx, part_ml[(((size_t)z * m_upper + row) * H + hh) * 2]);
-  float num = 0.f, den = 0.f;
-  for (int z = 0; z < Z; ++z) {
-    const size_t slot = ((size_t)z * m_upper + row) * H + hh;
-    const float w = exp2f(part_ml[slot * 2] - mx);
-    num = fmaf(w, part_o[slot * DH + dd], num);
-    den = fmaf(w, part_ml[slot * 2 + 1], den);
+  const int row = blockIdx.x, hh = blockIdx.y * kMergeHeads + (threadIdx.x >> 5), dd = (threadIdx.x & 31) * 4;
+  if (row >= M || hh >= H) return;
+  const size_t zs = (size_t)m_upper * H, slot = (size_t)row * H + hh;
+  float mx = -INFINITY, den = 0.f, num[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int z0 = 0; z0 < Z; z0 += 4) {
+    float2 ml[4];
+    float4 po[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const size_t sl = slot + (size_t)min(z0 + i, Z - 1) * zs;
+      ml[i] = *reinterpret_cast<const float2*>(part_ml + sl * 2);
+      po[i] = *reinterpret_cast<const float4*>(part_o + sl * DH + dd);
+    }
+    float m_new = mx;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) m_new = fmaxf(m_new, ml[i].x);           // finite: every split holds a real key
+    const float old = exp2f(mx - m_new);
+    den *= old;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) num[e] *= old;
+    mx = m_new;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (z0 + i < Z) {
+        const float w = exp2f(ml[i].x - mx);
+        den = fmaf(w, ml[i].y, den);
+        num[0] = fmaf(w, po[i].x, num[0]);
+        num[1] = fmaf(w, po[i].y, num[1]);
+        num[2] = fmaf(w, po[i].z, num[2]);
+        num[3] = fmaf(w, po[i].w, num[3]);
+      }
   }
-  o[afrag_index(row, hh * DH + dd, H * DH)] = (bf16_t)(num / den);
+  bf16x4 w4;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) w4[e] = (__bf16)(num[e] / den);
+  *reinterpret_cast<bf16x4*>(o + afrag_index(row, hh * DH + dd, H * DH)) = w4;
 }
 
 // Which kernel a launch of `blocks` (row tile, head) workgroups takes: the three-per-CU kernel as
@@ -789,11 +837,21 @@ __global__ __launch_bounds__(128) void attention_merge_kernel(const float* __res
 // 224 workgroups: 46 us against 62 us for the three-per-CU kernel with the keys split three ways).
 static bool attention_use_trio(int blocks) { return blocks > 256; }
 
-// The thin kernel (32 queries and one head per workgroup, key tiles split over its waves) while its
-// workgroups fit the chip in one round and a wave's share of the keys stays short.
-static bool attention_use_thin(int m_upper, int B, int H, int n_pad) {
-  const int blocks = (sl_cdiv(m_upper, QTT) + B - 1) * H;
-  return blocks <= 512 && n_pad / KT <= 16;
+// The thin kernel (32 queries and one head per workgroup, key tiles split over its waves): key splits Z of a launch,
+// 0 = another kernel.  Unsplit while its workgroups fit the chip in one round and a wave's share of the keys stays
+// short (16 tiles).  Longer sequences: up to one workgroup per CU, with as many splits as that leaves room for (a wave
+// keeps one tile at least) and at most 32 tiles per split.  Measured as one block of the layer, B = 1, the pipelined
+// kernel with its splits against this one, N = 2048: 32 rows 124.6 against 119.6 us (Z = 8), 64 rows 153.0 / 145.8 (4),
+// 128 rows 180.7 / 171.6 (2), 256 rows 228.7 / 225.4 (1); beyond one workgroup per CU it loses (384 rows 260.3 / 267.8).
+// N = 4096, 64 rows 157.9 / 151.3 (4); 256 rows (64 tiles per split) 237.5 / 237.7.
+static int attention_thin_splits(int m_upper, int B, int H, int n_pad, int* tiles_per_split) {
+  const int n_tiles = n_pad / KT, blocks = (sl_cdiv(m_upper, QTT) + B - 1) * H;
+  *tiles_per_split = n_tiles;
+  if (n_tiles <= 16) return blocks <= 512 ? 1 : 0;
+  if (blocks > 256) return 0;
+  const int Z = 256 / blocks < sl_cdiv(n_tiles, 4) ? 256 / blocks : sl_cdiv(n_tiles, 4);
+  *tiles_per_split = sl_cdiv(n_tiles, Z);
+  return *tiles_per_split <= 32 ? sl_cdiv(n_tiles, *tiles_per_split) : 0;
 }
 
 // Key-split plan for a launch bounded by m_upper rows: the keys are split just far enough to
@@ -818,6 +876,8 @@ size_t slk_attention_scratch_elems(int m_upper, int B, int H, int n_pad) {
     int tps;
     const int Z = slk_attention_splits(mu, B, H, n_pad, &tps);
     if (Z > 1 && (size_t)Z * mu * H * (DH + 2) > best) best = (size_t)Z * mu * H * (DH + 2);
+    const int Zt = attention_thin_splits(mu, B, H, n_pad, &tps);
+    if (Zt > 1 && (size_t)Zt * mu * H * (DH + 2) > best) best = (size_t)Zt * mu * H * (DH + 2);
   }
   return best;
 }
@@ -826,16 +886,27 @@ int slk_attention_mfma(hipStream_t s, const void* q, const void* kc, const void*
                        const int32_t* m_dev, int m_upper, int B, int H, int N, int n_pad, void* o, float* scratch) {
   if (m_upper <= 0) return SL_OK;
   if (B > kMaxBatch || n_pad % KT) return SL_EINVAL;
-  if (attention_use_thin(m_upper, B, H, n_pad)) {
-    const size_t sh_thin = (size_t)(4 * 64 * 64 + 4 * 64 * 2) * sizeof(float);
-    static unsigned long long lds_thin = 0;
-    SL_ALLOW_DYNAMIC_LDS(lds_thin, attention_thin_kernel, sh_thin);
-    hipLaunchKernelGGL(attention_thin_kernel, dim3(H, sl_cdiv(m_upper, QTT) + B - 1), dim3(256), sh_thin, s, (const bf16_t*)q,
-                       (const bf16_t*)kc, (const bf16_t*)vc, active_idx, m_dev, m_upper, B, H, N, n_pad, (bf16_t*)o);
+  int tps;
+  const auto merge = [&](const float* po, const float* pml, int Z) {
+    hipLaunchKernelGGL(attention_merge_kernel, dim3(m_upper, sl_cdiv(H, kMergeHeads)), dim3(32 * kMergeHeads), 0, s, po, pml,
+                       m_dev, m_upper, H, Z, (bf16_t*)o);
     SL_LAUNCH_CHECK();
     return SL_OK;
+  };
+  const int Zt = attention_thin_splits(m_upper, B, H, n_pad, &tps);
+  if (Zt == 1 || (Zt > 1 && scratch)) {
+    const size_t sh_thin = (size_t)(4 * 64 * 64 + 4 * 64 * 2) * sizeof(float);
+    static unsigned long long lds_thin[2] = {0, 0};
+    SL_ALLOW_DYNAMIC_LDS(lds_thin[0], attention_thin_kernel<false>, sh_thin);
+    SL_ALLOW_DYNAMIC_LDS(lds_thin[1], attention_thin_kernel<true>, sh_thin);
+    float* po = Zt > 1 ? scratch : nullptr;
+    float* pml = Zt > 1 ? scratch + (size_t)Zt * m_upper * H * DH : nullptr;
+    hipLaunchKernelGGL(Zt > 1 ? attention_thin_kernel<true> : attention_thin_kernel<false>,
+                       dim3(H, sl_cdiv(m_upper, QTT) + B - 1, Zt), dim3(256), sh_thin, s, (const bf16_t*)q, (const bf16_t*)kc,
+                       (const bf16_t*)vc, active_idx, m_dev, m_upper, B, H, N, n_pad, (bf16_t*)o, tps, po, pml);
+    SL_LAUNCH_CHECK();
+    return Zt > 1 ? merge(po, pml, Zt) : SL_OK;
   }
-  int tps;
   const int Z = scratch ? slk_attention_splits(m_upper, B, H, n_pad, &tps) : 1;
   dim3 grid(H, sl_cdiv(m_upper, QT) + B - 1, Z), block(256);
   const bool trio = attention_use_trio((int)(grid.x * grid.y));
@@ -858,8 +929,5 @@ int slk_attention_mfma(hipStream_t s, const void* q, const void* kc, const void*
                      (const bf16_t*)q, (const bf16_t*)kc, (const bf16_t*)vc, active_idx, m_dev, m_upper, B, H, N, n_pad,
                      (bf16_t*)o, tps, part_o, part_ml);
   SL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(attention_merge_kernel, dim3(m_upper, H), dim3(DH), 0, s, part_o, part_ml, m_dev, m_upper, H, Z,
-                     (bf16_t*)o);
-  SL_LAUNCH_CHECK();
-  return SL_OK;
+  return merge(part_o, part_ml, Z);
 }
