@@ -469,7 +469,7 @@ static GemmPlan gemm_plan(int mu, int n, int k, bool swiglu_consumer = false) {
   for (int s = 1; s <= 8; s *= 2) {
     if (k % (2 * BK * s)) break;
     if (k / (32 * s) < 8) break;
-    const double traffic_us = 2.0 * s * (double)mu * n * 4.0 / 5.0e6 * (s > 1 ? 1.0 : 0.5);
+    const double traffic_us = 2.0 * s * (double)mu * n * 4.0 / 5.5e6 * (s > 1 ? 1.0 : 0.5);
     const double fused_us = (double)mu * n / 5.0e6;      // bf16 activations of half the width, written once
     const double ring_us = slk_ring_cost(mu, n, s) * (k / (32.0 * s) + 4.0) * 0.8;
     const double t = ring_us + (swiglu_consumer && s == 1 ? fused_us : traffic_us);

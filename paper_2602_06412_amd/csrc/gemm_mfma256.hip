@@ -557,16 +557,21 @@ static int launch_ring(hipStream_t s, const void* A, int a_tiled, const void* Wp
 }
 
 // ---- tile heights of a launch ------------------------------------------------------------------
-// Cost model in units of one full-height tile's time on 256 CUs: a full round of workgroups costs 1, a
-// last partial round 0.9 whatever its fill (measured: the busy CUs of a partial round run at a higher
-// clock), a tile of TM rows kTileCost[TM / 32] of a full one.
+// Cost model in units of one full-height tile's time on 256 CUs: a full round of workgroups costs 1, a last partial
+// round nearly the same whatever its fill (measured: the busy CUs of a partial round run at a higher clock), a tile
+// of TM rows kTileCost[TM / 32] of a full one.  The constants are those for which the choices of height and split come
+// nearest to the fastest launch of each size in a sweep of 86 sizes (n = 4096 .. 126464, k = 4096 and 12288, 40 .. 2048
+// rows, weights out of HBM, every height and split): 1.7 % above it on average.  The narrow matrices take shorter tiles
+// than when a partial round cost the same at any fill: n = k = 4096, 128 rows 128 x 8 splits 20.3 us -> 64 x 8 17.6,
+// 224 rows 128 x 4 24.7 -> 64 x 4 21.4; n = 4096, k = 12288, 128 rows 36.8 -> 31.5, 1280 rows 192 x 2 118 -> 160 x 2 111.
 // A launch runs uniform tiles of one height (any multiple of 32 from 64 to 256): the smallest number of
 // row tiles that covers the rows, or more and shorter ones where that saves a round of workgroups.
 // Fewer, taller tiles win near-ties (less operand traffic per flop).
 static double ring_rounds_cost(int workgroups) {
-  return workgroups / 256 + (workgroups % 256 ? 0.9 : 0.0);
+  const int rest = workgroups % 256;
+  return workgroups / 256 + (rest ? 0.9 + 0.025 * rest / 256.0 : 0.0);
 }
-static const double kTileCost[9] = {0, 0, 0.51, 0.55, 0.565, 0.70, 0.78, 0.86, 1.0};   // by TM / 32
+static const double kTileCost[9] = {0, 0, 0.485, 0.55, 0.56, 0.70, 0.795, 0.86, 1.0};   // by TM / 32
 
 struct RingChoice {
   int tm;          // rows per tile
@@ -581,7 +586,7 @@ static RingChoice ring_choice(int mu, int n, int splits) {
     if (tm < 64) tm = 64;
     if (sl_cdiv(mu, tm) != t) continue;              // the same height with fewer tiles was already priced
     const double c = ring_rounds_cost(t * tn) * kTileCost[tm / 32];
-    if (c < 0.97 * best.cost) best = RingChoice{tm, c};
+    if (c < 0.99 * best.cost) best = RingChoice{tm, c};
   }
   return best;
 }
