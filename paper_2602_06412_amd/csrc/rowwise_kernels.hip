@@ -304,7 +304,10 @@ __global__ __launch_bounds__(kRowThreads) void add_rmsnorm_vec_kernel(const bf16
 // the row held in registers (CH chunks of 8 per lane), the sum of squares reduced by shuffles, no LDS and
 // no barrier.  With thousands of rows the block-per-row kernel is bound by workgroup turnover (8 KB of
 // traffic per workgroup in the norm-only form); this one keeps a wave streaming: norm-only at 8192 rows
-// 65 -> 38 us.  Taken from 2048 rows on (at 512 rows its 128 workgroups leave half the chip idle).
+// 65 -> 38 us.  For many rows only: at 512 its 128 workgroups leave half the chip idle (see kWaveRowsMin).
+// A row's eight-column pieces lie 512 bytes apart in the tiled layout, so a wave that stored its own row touched a 64-byte
+// segment per lane.  The four rows leave through LDS instead, four neighbouring pieces at a time, and the workgroups of
+// 32 rows, which share every 512-byte fragment half, run on one XCD: norm-only at 8192 rows 38 -> 27 us, at 4654 22.3 -> 19.4.
 template <bool ADD, bool TILED, int CH>
 __global__ __launch_bounds__(256) void add_rmsnorm_wave_kernel(const bf16_t* src, bf16_t* x,
                                                                const float* __restrict__ delta, int S, size_t sstride, const int32_t* __restrict__ m_dev,
@@ -312,8 +315,13 @@ __global__ __launch_bounds__(256) void add_rmsnorm_wave_kernel(const bf16_t* src
                                                                bf16_t* __restrict__ h) {
   constexpr int d = 512 * CH;
   const int M = min(*m_dev, m_upper);
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (r >= M) return;
+  // workgroups go to the XCDs in turn: each takes eight consecutive groups of four rows out of 256 rows
+  const int r0 = TILED ? (((blockIdx.x >> 6) << 6) + ((blockIdx.x & 7) << 3) + ((blockIdx.x >> 3) & 7)) * 4 : blockIdx.x * 4;
+  const int wave = threadIdx.x >> 6, r = min(r0 + wave, M - 1), lane = threadIdx.x & 63;
+  constexpr int RP = 64 * CH + 4;                 // pieces per staged row: four rows' reads fall on different banks
+  __shared__ uint4 rows_sh[TILED ? 4 * RP : 1];
+  if (r0 >= M || (!TILED && r0 + wave >= M)) return;
+  const bool live = r0 + wave < M;
   bf16_t* xr = x + (size_t)r * d;
   const bf16_t* sr = ADD ? xr : src + (size_t)r * d;
   float v[CH][8];
@@ -322,7 +330,7 @@ __global__ __launch_bounds__(256) void add_rmsnorm_wave_kernel(const bf16_t* src
   for (int j = 0; j < CH; ++j) {
     const int c8 = lane + j * 64;
     ld8(sr + c8 * 8, v[j]);
-    if (!ADD && x != nullptr) st8(xr + c8 * 8, v[j]);
+    if (!ADD && x != nullptr && live) st8(xr + c8 * 8, v[j]);
     if (ADD) {
       const float* dp = delta + (size_t)r * d + c8 * 8;
       float dl[8];
@@ -335,7 +343,7 @@ __global__ __launch_bounds__(256) void add_rmsnorm_wave_kernel(const bf16_t* src
       }
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[j][e] = st<bf16_t>::rnd(v[j][e] + dl[e]);
-      st8(xr + c8 * 8, v[j]);
+      if (live) st8(xr + c8 * 8, v[j]);
     }
   }
   // The sum of squares is taken in the order of the block-per-row kernels (thread t of 256 sums chunks t
@@ -358,7 +366,18 @@ __global__ __launch_bounds__(256) void add_rmsnorm_wave_kernel(const bf16_t* src
     ld8(gain + c8 * 8, g);
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] = v[j][e] * rstd * g[e];
-    st8(h + act_index<TILED>(r, c8 * 8, d), o);
+    if constexpr (TILED) st8(reinterpret_cast<bf16_t*>(rows_sh + wave * RP + c8), o);
+    else st8(h + act_index<TILED>(r, c8 * 8, d), o);
+  }
+  if constexpr (TILED) {
+    __syncthreads();
+    const int rr = threadIdx.x & 3;
+    if (r0 + rr >= M) return;
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+      const int c8 = (threadIdx.x >> 2) + j * 64;
+      *reinterpret_cast<uint4*>(h + act_index<TILED>(r0 + rr, c8 * 8, d)) = rows_sh[rr * RP + c8];
+    }
   }
 }
 
@@ -600,13 +619,17 @@ int slk_embed_rmsnorm(hipStream_t s, int dtype, const void* emb, const int32_t* 
   return SL_OK;
 }
 
-constexpr int kWaveRowsMin = 2048;     // the wave-per-row norm kernel from this many rows on (see add_rmsnorm_wave_kernel)
+// The wave-per-row norm kernel from this many rows on.  Measured as one block of the layer, block-per-row against
+// wave-per-row: 457 rows 280.0 against 286.0 us, 640 rows 339.4 / 341.2, 857 rows 414.8 / 413.3, 1024 rows 451.8 / 445.4,
+// 1280 rows 499.7 / 492.2, 2000 rows 779.6 / 758.0.
+constexpr int kWaveRowsMin = 800;
 int slk_add_rmsnorm(hipStream_t s, int dtype, void* x, const float* delta, int S, size_t sstride,
                     const int32_t* m_dev, int m_upper, int d, const void* gain, float eps, void* h, int tiled) {
   if (m_upper <= 0) return SL_OK;
   if (dtype == SL_BF16 && d == 4096 && m_upper >= kWaveRowsMin && sstride % 4 == 0 && al16(x) && al16(delta) && al16(gain) &&
       al16(h)) {
-    DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_wave_kernel<true, TL, 8>), dim3(sl_cdiv(m_upper, 4)), dim3(256), 0, s,
+    const unsigned wave_groups = (unsigned)sl_align_up(sl_cdiv(m_upper, 4), 64);    // whole rounds of the row order
+    DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_wave_kernel<true, TL, 8>), dim3(wave_groups), dim3(256), 0, s,
                                              (const bf16_t*)x, (bf16_t*)x, delta, S, sstride, m_dev, m_upper, (const bf16_t*)gain, eps,
                                              (bf16_t*)h));
     SL_LAUNCH_CHECK();
@@ -631,7 +654,8 @@ int slk_rmsnorm(hipStream_t s, int dtype, const void* src, void* x, const int32_
                 float eps, void* h, int tiled) {
   if (m_upper <= 0) return SL_OK;
   if (dtype == SL_BF16 && d == 4096 && m_upper >= kWaveRowsMin && al16(src) && al16(x) && al16(gain) && al16(h)) {
-    DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_wave_kernel<false, TL, 8>), dim3(sl_cdiv(m_upper, 4)), dim3(256), 0,
+    const unsigned wave_groups = (unsigned)sl_align_up(sl_cdiv(m_upper, 4), 64);    // whole rounds of the row order
+    DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_wave_kernel<false, TL, 8>), dim3(wave_groups), dim3(256), 0,
                                              s, (const bf16_t*)src, (bf16_t*)x, (const float*)nullptr, 1, (size_t)0, m_dev,
                                              m_upper, (const bf16_t*)gain, eps, (bf16_t*)h));
     SL_LAUNCH_CHECK();
