@@ -420,7 +420,7 @@ static int pick_bm(int mu) { return mu <= 32 ? 32 : mu <= 64 ? 64 : 128; }
 //  * thicker launches take the ring kernel (one workgroup per CU, ~0.8 us per 32-deep k-tile and round
 //    of full-height workgroups; its tile height is fitted to the rows by that launcher, whose cost
 //    model is shared here) with the split count that minimises  rounds * tile cost * (k-tiles per split
-//    + fixed) * t_tile + bytes of fp32 partials written and read back / 5 TB/s; reductions too short
+//    + fixed) * t_tile + bytes of fp32 partials written and read back / 5.5 TB/s; reductions too short
 //    for its ring (fewer than 8 k-tiles per split) go to the 128 x 256 LDS kernel (two per CU, ~1.8 us
 //    per 64-deep k-tile).
 //  The thin limit is 32 rows: from 33 rows on the ring's short tiles are ahead of the two-block
@@ -460,8 +460,8 @@ static GemmPlan gemm_plan(int mu, int n, int k, bool swiglu_consumer = false) {
     p.splits = best_s;
     return p;
   }
-  // The ring kernel wherever its k loop is long enough (at least 8 k-tiles per split); its half-height
-  // variant covers ragged and small row counts.  Measured over ragged row counts at the LLaDA-8B shapes
+  // The ring kernel wherever its k loop is long enough (at least 8 k-tiles per split); its short tiles
+  // cover ragged and small row counts.  Measured over ragged row counts at the LLaDA-8B shapes
   // the 128 x 256 LDS kernel never won where the ring was eligible (LM head at 820 rows: 1.19 ms
   // against 0.79 ms), so it is kept for short reductions only.
   double best = 1e30;
@@ -513,7 +513,7 @@ static int launch_gemm(hipStream_t s, const void* A, int a_tiled, const void* Wp
 
 // Which kernel a launch bounded by mu rows takes (one decision, shared by the launcher and by
 // sl_linear_plan): kind 0 = weight-stream kernel (rows = 32 or 64, cols = 128 or 256 per workgroup),
-// 1 = ring kernel (rows / tail as its launcher chooses), 2 = 128 x 256 LDS kernel (short reductions).
+// 1 = ring kernel (rows as its launcher chooses; tail is 0), 2 = 128 x 256 LDS kernel (short reductions).
 struct KernelPick { int kind, rows, cols, tail; };
 void slk_ring_describe(int mu, int n, int splits, int* rows, int* tail);     // gemm_mfma256.hip
 static KernelPick pick_kernel(int mu, int n, int k, int splits, bool f32_out) {

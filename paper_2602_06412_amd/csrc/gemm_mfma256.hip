@@ -560,7 +560,7 @@ static int launch_ring(hipStream_t s, const void* A, int a_tiled, const void* Wp
 // Cost model in units of one full-height tile's time on 256 CUs: a full round of workgroups costs 1, a last partial
 // round nearly the same whatever its fill (measured: the busy CUs of a partial round run at a higher clock), a tile
 // of TM rows kTileCost[TM / 32] of a full one.  The constants are those for which the choices of height and split come
-// nearest to the fastest launch of each size in a sweep of 86 sizes (n = 4096 .. 126464, k = 4096 and 12288, 40 .. 2048
+// nearest to the fastest launch of each size in a sweep of 88 sizes (n = 4096 .. 126464, k = 4096 and 12288, 40 .. 2048
 // rows, weights out of HBM, every height and split): 1.7 % above it on average.  The narrow matrices take shorter tiles
 // than when a partial round cost the same at any fill: n = k = 4096, 128 rows 128 x 8 splits 20.3 us -> 64 x 8 17.6,
 // 224 rows 128 x 4 24.7 -> 64 x 4 21.4; n = 4096, k = 12288, 128 rows 36.8 -> 31.5, 1280 rows 192 x 2 118 -> 160 x 2 111.
