@@ -871,15 +871,19 @@ int slk_attention_splits(int m_upper, int B, int H, int n_pad, int* tiles_per_sp
 
 // fp32 scratch floats the split path may need for any launch of at most m_upper rows
 size_t slk_attention_scratch_elems(int m_upper, int B, int H, int n_pad) {
-  size_t best = 0;
-  for (int mu = 1; mu <= m_upper; ++mu) {
-    int tps;
+  size_t splits_rows = 0;                    // the splits of both kernels depend on a launch's row tiles only
+  int tps;
+  for (int t = 1; (t - 1) * QT < m_upper; ++t) {
+    const int mu = t * QT < m_upper ? t * QT : m_upper;
     const int Z = slk_attention_splits(mu, B, H, n_pad, &tps);
-    if (Z > 1 && (size_t)Z * mu * H * (DH + 2) > best) best = (size_t)Z * mu * H * (DH + 2);
-    const int Zt = attention_thin_splits(mu, B, H, n_pad, &tps);
-    if (Zt > 1 && (size_t)Zt * mu * H * (DH + 2) > best) best = (size_t)Zt * mu * H * (DH + 2);
+    if (Z > 1 && (size_t)Z * mu > splits_rows) splits_rows = (size_t)Z * mu;
   }
-  return best;
+  for (int t = 1; (t - 1) * QTT < m_upper; ++t) {
+    const int mu = t * QTT < m_upper ? t * QTT : m_upper;
+    const int Z = attention_thin_splits(mu, B, H, n_pad, &tps);
+    if (Z > 1 && (size_t)Z * mu > splits_rows) splits_rows = (size_t)Z * mu;
+  }
+  return splits_rows * H * (DH + 2);
 }
 
 int slk_attention_mfma(hipStream_t s, const void* q, const void* kc, const void* vc, const int32_t* active_idx,
