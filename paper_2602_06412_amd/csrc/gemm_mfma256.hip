@@ -309,7 +309,8 @@ __device__ __forceinline__ void ring_tile(
     // kernel and would otherwise sit dirty in the memory-side cache and be written back under that kernel's reads
     // (scoring 111 -> 99 us)
     const int c0 = n0 + wave * 64 + (g4 & 1) * 16 + (g4 >> 1) * 8;
-    // where the rows go, all asked for at once (one by one, each row group waited for its own: LM head of 8192 rows 6.62 ms, 6.30 so)
+    // where the rows go, all asked for at once (when each row group waited for its own: LM head of 8192 rows 6.62 ms,
+    // 6.30 so)
     int orow[NA];
 #pragma unroll
     for (int a = 0; a < NA; ++a) {
