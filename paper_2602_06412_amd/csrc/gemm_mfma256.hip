@@ -308,26 +308,35 @@ __device__ __forceinline__ void ring_tile(
     // bf16 rows.  Streaming stores: these rows (the step's logits, 259 MB at M = 1024) are read once by the next
     // kernel and would otherwise sit dirty in the memory-side cache and be written back under that kernel's reads
     // (scoring 111 -> 99 us)
-    const int c0 = n0 + wave * 64 + (g4 & 1) * 16 + (g4 >> 1) * 8;
-    // where the rows go, all asked for at once (when each row group waited for its own: LM head of 8192 rows 6.62 ms,
-    // 6.30 so)
-    int orow[NA];
-#pragma unroll
-    for (int a = 0; a < NA; ++a) {
-      const int row = min(m0 + a * 16 + row_in, M - 1);
-      orow[a] = row_map ? row_map[row] : row;
+    // The rows leave through LDS (a wave's own corner of the drained ring), eight rows of a whole 128-byte line each per
+    // instruction: stored from the accumulators' layout, half lines at a time, the launch wrote 1.45 times its bytes.
+    // One map entry per thread, all at once.  LM head: 8192 rows 6164 -> 5878 us, 1024 rows 800 -> 781, 512 rows 489 -> 466.
+    __syncthreads();
+    int* row_sh = reinterpret_cast<int*>(lds);        // [TM] output row, -1 past M
+    {
+      const int r = threadIdx.x, row = m0 + r;
+      if (r < TM) row_sh[r] = row < M ? (row_map ? row_map[row] : row) : -1;
     }
-#pragma unroll
-    for (int a = 0; a < NA; ++a) asm volatile("" : "+v"(orow[a]));
+    __syncthreads();
+    constexpr int RS = 9;                             // 16-byte pieces per staged row: eight and one of padding
+    static_assert(TM * 4 + 4 * 2 * 16 * RS * 16 <= TC::LDS, "staging fits the ring");
+    uint4* stage = reinterpret_cast<uint4*>(row_sh + TM) + wave * 2 * 16 * RS;
+    const int wp = row_in * RS + (g4 & 1) * 2 + (g4 >> 1), rl = lane >> 3, c0 = n0 + wave * 64 + (lane & 7) * 8;
 #pragma unroll
     for (int a = 0; a < NA; ++a) {
-      if (m0 + a * 16 + row_in >= M) continue;
-      bf16_t* p = Cb + (size_t)orow[a] * ldc + c0;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) asm volatile("" : "+a"(acc[a][b]));     // read here, not all at once ahead (spills)
+      uint4* st = stage + (a & 1) * 16 * RS;
+      st[wp] = pack_swap(acc[a][0], acc[a][1]);
+      st[wp + 4] = pack_swap(acc[a][2], acc[a][3]);
+      asm volatile("" ::: "memory");                  // written by other lanes of the wave: LDS keeps a wave's order
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const uint4 v = pack_swap(acc[a][2 * h], acc[a][2 * h + 1]);
-        if (c0 + 32 * h < n) __builtin_nontemporal_store(__builtin_bit_cast(Frag, v), reinterpret_cast<Frag*>(p + 32 * h));
+        const uint4 v = st[(rl + 8 * h) * RS + (lane & 7)];
+        const int orow = row_sh[a * 16 + rl + 8 * h];
+        if (orow >= 0 && c0 < n) __builtin_nontemporal_store(__builtin_bit_cast(Frag, v), reinterpret_cast<Frag*>(Cb + (size_t)orow * ldc + c0));
       }
+      asm volatile("" ::: "memory");
     }
     if (PROBE) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // the stores have left
