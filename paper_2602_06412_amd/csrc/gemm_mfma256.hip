@@ -99,7 +99,8 @@ __device__ __forceinline__ uint4 pack_swap(const f32x4& x, const f32x4& y) {
 }
 
 // One TM x 256 output tile (rows m0 .., column tile tn) by the whole 256-thread workgroup.
-template <int OUT, int TM, bool PROBE>
+// NT: weight loads carry the non-temporal hint (see stream_weights).
+template <int OUT, int TM, bool NT, bool PROBE>
 __device__ __forceinline__ void ring_tile(
     const bf16_t* __restrict__ A, int a_tiled, const bf16_t* __restrict__ Wp, int n, int k, int k_per_split,
     const int M, int m_upper, float* __restrict__ Cf, bf16_t* __restrict__ Cb,
@@ -164,7 +165,6 @@ __device__ __forceinline__ void ring_tile(
   // between the write of M0 and the load.
   auto set_m0 = [&](int slot, int i) { asm volatile("s_mov_b32 m0, %0" ::"s"(a_lds[i] + (uint32_t)(slot * KTB)) : "m0"); };
   auto issue_a = [&](int i) { asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(a_voff[i]), "s"(pa) : "memory", "m0"); };
-  // Weight loads carry the non-temporal hint (wanted by one wave of each row tile at about the same time).
   // Register-ring contract.  The compiler cannot see that a register is still being written after the load has
   // issued, so nothing may give it a reason to touch fb between a load and the b_landed that waits for it:
   //  * the ring registers are read-write operands of both the load and the wait, i.e. one live value from the first
@@ -177,7 +177,8 @@ __device__ __forceinline__ void ring_tile(
 #pragma unroll
     for (int b = 0; b < NB; ++b) fb[u][b] = Frag{};
   auto issue_b = [&](int slot, int b) {
-    asm volatile("global_load_dwordx4 %0, %1, %2 nt" : "+v"(fb[slot][b]) : "v"(b_voff[b]), "s"(pb) : "memory");
+    if constexpr (NT) asm volatile("global_load_dwordx4 %0, %1, %2 nt" : "+v"(fb[slot][b]) : "v"(b_voff[b]), "s"(pb) : "memory");
+    else asm volatile("global_load_dwordx4 %0, %1, %2" : "+v"(fb[slot][b]) : "v"(b_voff[b]), "s"(pb) : "memory");
   };
   // next k-tile to fetch; past the end the last one again (never used)
   int kt_a = 0, kt_b = 0;
@@ -545,7 +546,7 @@ static TileMap pick_tile_map(int tiles_m, int tiles_n) {
   return TileMap{gn < cn ? gn : cn, cn};
 }
 
-template <int OUT, int TM, bool PROBE = false>
+template <int OUT, int TM, bool NT, bool PROBE = false>
 __global__ __launch_bounds__(256, 1) void gemm_mfma256_kernel(
     const bf16_t* __restrict__ A, int a_tiled, const bf16_t* __restrict__ Wp, int n, int k, int k_per_split,
     const int32_t* __restrict__ m_dev, int m_upper, float* __restrict__ Cf, bf16_t* __restrict__ Cb,
@@ -554,15 +555,28 @@ __global__ __launch_bounds__(256, 1) void gemm_mfma256_kernel(
   const int M = min(*m_dev, m_upper);
   int tm, tn;
   if (!tile_of_workgroup(tmap, tiles_m, tiles_n, tm, tn) || tm * TM >= M) return;
-  ring_tile<OUT, TM, PROBE>(A, a_tiled, Wp, n, k, k_per_split, M, m_upper, Cf, Cb, row_map, ldc, tm * TM, tn, probe, rs);
+  ring_tile<OUT, TM, NT, PROBE>(A, a_tiled, Wp, n, k, k_per_split, M, m_upper, Cf, Cb, row_map, ldc, tm * TM, tn, probe, rs);
 }
 
-template <int OUT, int TM>
-static int launch_ring(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n, int k,
+// Whether a launch's weight loads carry the non-temporal hint.  With one row tile a weight line is wanted once, and in one
+// round of workgroups the row tiles of a column want it at about the same time: the hint keeps the weights from pushing
+// activations and planes out of the caches (one row tile, LM head of 64 rows: 168 us with it, 194 without; one round, Q|K|V
+// of 576 rows: 65 and 68).  From the second round on the workgroups of a column have drifted apart and a line marked for
+// eviction is gone before the next one asks.  Short tiles live on those lines: gate|up of 576 rows 131 us with, 105 without,
+// 700 rows 143 / 117; LM head of 288 rows 329 / 275, Q|K|V of 2600 rows 293 / 226.  Taller tiles have the arithmetic to hide
+// it until more than 3072 rows share the lines: LM head of 4654 rows 3714 / 3217, of 8192 rows 5882 / 5659, gate|up 654 / 637
+// and 1111 / 1090; at 2304 rows gate|up gains 3 us and the down projection behind it loses 13, its activations evicted.
+static bool stream_weights(int tiles_m, int tiles_n, int splits, int tm) {
+  if (tiles_m == 1 || tiles_m * tiles_n * splits <= 256) return true;
+  return tm > 160 && tiles_m * tm <= 3072;
+}
+
+template <int OUT, int TM, bool NT>
+static int launch_ring_hint(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n, int k,
                        int splits, float* Cf, void* Cb, const int32_t* row_map, size_t ldc, const RopeScatter& rs) {
   const int tiles_m = sl_cdiv(mu, TM), tiles_n = sl_cdiv(n, TILE);
   const size_t sh = TileCfg<TM>::LDS;
-  auto kern = gemm_mfma256_kernel<OUT, TM>;
+  auto kern = gemm_mfma256_kernel<OUT, TM, NT>;
   static unsigned long long lds_ok = 0;              // one per kernel instantiation
   SL_ALLOW_DYNAMIC_LDS(lds_ok, kern, sh);
   const TileMap tmap = pick_tile_map(tiles_m, tiles_n);
@@ -571,6 +585,13 @@ static int launch_ring(hipStream_t s, const void* A, int a_tiled, const void* Wp
                      (bf16_t*)Cb, row_map, ldc, tiles_m, tiles_n, tmap, (long long*)nullptr, rs);
   SL_LAUNCH_CHECK();
   return SL_OK;
+}
+template <int OUT, int TM>
+static int launch_ring(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n, int k,
+                       int splits, float* Cf, void* Cb, const int32_t* row_map, size_t ldc, const RopeScatter& rs) {
+  return stream_weights(sl_cdiv(mu, TM), sl_cdiv(n, TILE), splits, TM)
+             ? launch_ring_hint<OUT, TM, true>(s, A, a_tiled, Wp, m_dev, mu, n, k, splits, Cf, Cb, row_map, ldc, rs)
+             : launch_ring_hint<OUT, TM, false>(s, A, a_tiled, Wp, m_dev, mu, n, k, splits, Cf, Cb, row_map, ldc, rs);
 }
 
 // ---- tile heights of a launch ------------------------------------------------------------------
@@ -644,14 +665,12 @@ int slk_gemm_mfma256(hipStream_t s, const void* A, int a_tiled, const void* Wp, 
 }
 
 // The LM-head launch (bf16 rows, no split) with the cycle probe switched on; probe = 8 int64 on the device.
-int slk_gemm_mfma256_probe(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n,
-                           int k, void* Cb, const int32_t* row_map, size_t ldc, long long* probe) {
-  if (mu <= 0 || !probe || !Cb) return SL_EINVAL;
-  if (n % 32 || k % BK2 || k / BK2 < 8) return SL_EINVAL;
-  if ((size_t)n * k >= ((size_t)1 << 31) * 8 || (size_t)mu * k >= ((size_t)1 << 32)) return SL_EINVAL;
+template <bool NT>
+static int launch_probe(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n, int k,
+                        void* Cb, const int32_t* row_map, size_t ldc, long long* probe) {
   const int tiles_m = sl_cdiv(mu, TILE), tiles_n = sl_cdiv(n, TILE);
   const size_t sh = TileCfg<256>::LDS;
-  auto kern = gemm_mfma256_kernel<1, 256, true>;
+  auto kern = gemm_mfma256_kernel<1, 256, NT, true>;
   static unsigned long long lds_ok = 0;
   SL_ALLOW_DYNAMIC_LDS(lds_ok, kern, sh);
   const TileMap tmap = pick_tile_map(tiles_m, tiles_n);
@@ -660,6 +679,15 @@ int slk_gemm_mfma256_probe(hipStream_t s, const void* A, int a_tiled, const void
                      (float*)nullptr, (bf16_t*)Cb, row_map, ldc, tiles_m, tiles_n, tmap, probe, RopeScatter{});
   SL_LAUNCH_CHECK();
   return SL_OK;
+}
+int slk_gemm_mfma256_probe(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n,
+                           int k, void* Cb, const int32_t* row_map, size_t ldc, long long* probe) {
+  if (mu <= 0 || !probe || !Cb) return SL_EINVAL;
+  if (n % 32 || k % BK2 || k / BK2 < 8) return SL_EINVAL;
+  if ((size_t)n * k >= ((size_t)1 << 31) * 8 || (size_t)mu * k >= ((size_t)1 << 32)) return SL_EINVAL;
+  return stream_weights(sl_cdiv(mu, TILE), sl_cdiv(n, TILE), 1, TILE)
+             ? launch_probe<true>(s, A, a_tiled, Wp, m_dev, mu, n, k, Cb, row_map, ldc, probe)
+             : launch_probe<false>(s, A, a_tiled, Wp, m_dev, mu, n, k, Cb, row_map, ldc, probe);
 }
 
 int slk_gemm_mfma256_swiglu(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int dff, int k,
