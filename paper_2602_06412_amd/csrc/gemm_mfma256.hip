@@ -113,7 +113,7 @@ __device__ __forceinline__ void ring_tile(
 
   const int n0 = tn * TILE;
   const int kbeg = blockIdx.y * k_per_split;
-  const int ktiles = k_per_split / BK2;             // even, at least RING
+  const int ktiles = k_per_split / BK2;             // even, at least RING (k_tiles_ok)
   const int last = ktiles - 1;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int K16 = k / 16, NF = n / 16;
@@ -653,10 +653,13 @@ static int launch256(hipStream_t s, const void* A, int a_tiled, const void* Wp, 
   }
 }
 
+// The k loop takes k-tiles in pairs (an odd last one would be added twice) and its prologue wants a ring of them.
+static bool k_tiles_ok(int k, int splits) { return k % (2 * BK2 * splits) == 0 && k / (BK2 * splits) >= 8; }
+
 int slk_gemm_mfma256(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n,
                      int k, int splits, float* Cf, void* Cb, const int32_t* row_map, size_t ldc) {
   if (mu <= 0) return SL_OK;
-  if (splits < 1 || n % 32 || k % (BK2 * splits) || k / (BK2 * splits) < 8) return SL_EINVAL;
+  if (splits < 1 || n % 32 || !k_tiles_ok(k, splits)) return SL_EINVAL;
   if (!Cf && splits != 1) return SL_EINVAL;
   if (Cf && ((uintptr_t)Cf % 16 || ldc % 4)) return SL_EINVAL;       // 16-byte fp32 stores
   if ((size_t)n * k >= ((size_t)1 << 31) * 8 || (size_t)mu * k >= ((size_t)1 << 32)) return SL_EINVAL;
@@ -683,7 +686,7 @@ static int launch_probe(hipStream_t s, const void* A, int a_tiled, const void* W
 int slk_gemm_mfma256_probe(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n,
                            int k, void* Cb, const int32_t* row_map, size_t ldc, long long* probe) {
   if (mu <= 0 || !probe || !Cb) return SL_EINVAL;
-  if (n % 32 || k % BK2 || k / BK2 < 8) return SL_EINVAL;
+  if (n % 32 || !k_tiles_ok(k, 1)) return SL_EINVAL;
   if ((size_t)n * k >= ((size_t)1 << 31) * 8 || (size_t)mu * k >= ((size_t)1 << 32)) return SL_EINVAL;
   return stream_weights(sl_cdiv(mu, TILE), sl_cdiv(n, TILE), 1, TILE)
              ? launch_probe<true>(s, A, a_tiled, Wp, m_dev, mu, n, k, Cb, row_map, ldc, probe)
@@ -694,20 +697,20 @@ int slk_gemm_mfma256_swiglu(hipStream_t s, const void* A, const void* Wp, const 
                             void* a) {
   if (mu <= 0) return SL_OK;
   const int n = 2 * dff;
-  if (dff % 32 || k % BK2 || k / BK2 < 8) return SL_EINVAL;
+  if (dff % 32 || !k_tiles_ok(k, 1)) return SL_EINVAL;
   if ((size_t)n * k >= ((size_t)1 << 31) * 8 || (size_t)mu * k >= ((size_t)1 << 32)) return SL_EINVAL;
   return launch256<2>(s, A, 1, Wp, m_dev, mu, n, k, 1, nullptr, a, nullptr, (size_t)dff);
 }
 
 // Q|K|V projection + RoPE + scatter in one launch: q [mu, H*128] packed bf16, K / V into the layer's
-// cache at the rows' own slots (kc = vc = null: queries only).  Unsplit only (k / 32 >= 8); H even, so
+// cache at the rows' own slots (kc = vc = null: queries only).  Unsplit only; H even, so
 // that a 256-column tile is two whole heads of q, k or v.
 int slk_gemm_mfma256_qkv_rope(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int H, int k,
                               const int32_t* active_idx, int N, int n_pad, const void* rope_tab, void* q, void* kc,
                               void* vc) {
   if (mu <= 0) return SL_OK;
   const int n = 3 * H * 128;
-  if (H < 2 || H % 2 || k % BK2 || k / BK2 < 8 || !active_idx || !rope_tab || !q) return SL_EINVAL;
+  if (H < 2 || H % 2 || !k_tiles_ok(k, 1) || !active_idx || !rope_tab || !q) return SL_EINVAL;
   if ((kc == nullptr) != (vc == nullptr)) return SL_EINVAL;
   if ((uintptr_t)q % 16 || (uintptr_t)kc % 16 || (uintptr_t)vc % 16 || (uintptr_t)rope_tab % 16) return SL_EINVAL;
   if ((size_t)n * k >= ((size_t)1 << 31) * 8 || (size_t)mu * k >= ((size_t)1 << 32)) return SL_EINVAL;
@@ -720,7 +723,7 @@ int slk_gemm_mfma256_qkv_rope(hipStream_t s, const void* A, const void* Wp, cons
 int slk_gemm_mfma256_residual(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int n, int k,
                               void* x) {
   if (mu <= 0) return SL_OK;
-  if (n % 32 || k % BK2 || k / BK2 < 8 || !x || (uintptr_t)x % 16) return SL_EINVAL;
+  if (n % 32 || !k_tiles_ok(k, 1) || !x || (uintptr_t)x % 16) return SL_EINVAL;
   if ((size_t)n * k >= ((size_t)1 << 31) * 8 || (size_t)mu * k >= ((size_t)1 << 32)) return SL_EINVAL;
   return launch256<4>(s, A, 1, Wp, m_dev, mu, n, k, 1, nullptr, x, nullptr, (size_t)n);
 }
