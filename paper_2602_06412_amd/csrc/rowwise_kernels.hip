@@ -619,10 +619,10 @@ int slk_embed_rmsnorm(hipStream_t s, int dtype, const void* emb, const int32_t* 
   return SL_OK;
 }
 
-// The wave-per-row norm kernel from this many rows on.  Measured as one block of the layer, block-per-row against
-// wave-per-row: 457 rows 280.0 against 286.0 us, 640 rows 339.4 / 341.2, 857 rows 414.8 / 413.3, 1024 rows 451.8 / 445.4,
-// 1280 rows 499.7 / 492.2, 2000 rows 779.6 / 758.0.
-constexpr int kWaveRowsMin = 800;
+// The wave-per-row norm kernel from this many rows on.  Measured inside a step (us per norm launch, mean of the two of a
+// block, both mostly adding k-split planes), block-per-row against wave-per-row: 512 rows 12.3 against 14.9, 704 rows 14.3 /
+// 15.3, 801 rows 15.7 / 16.5, 857 rows 16.1 / 15.6, 1024 rows 15.9 / 15.6, 1280 rows 20.6 / 17.8, 2000 rows 18.3 / 10.5.
+constexpr int kWaveRowsMin = 832;
 int slk_add_rmsnorm(hipStream_t s, int dtype, void* x, const float* delta, int S, size_t sstride,
                     const int32_t* m_dev, int m_upper, int d, const void* gain, float eps, void* h, int tiled) {
   if (m_upper <= 0) return SL_OK;
