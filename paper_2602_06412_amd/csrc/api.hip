@@ -476,7 +476,8 @@ extern "C" int sl_linear_plan(int32_t m_upper, int32_t n, int32_t k, int32_t* ke
                               int32_t* tile_cols, int32_t* tail_tile) {
   if (m_upper < 1 || n < 32 || k < 64 || n % 32 || k % 64) return SL_EINVAL;
   if (!kernel || !splits || !tile_rows || !tile_cols || !tail_tile) return SL_EINVAL;
-  return slk_gemm_describe(m_upper, n, k, kernel, splits, tile_rows, tile_cols, tail_tile);
+  *tail_tile = 0;
+  return slk_gemm_describe(m_upper, n, k, kernel, splits, tile_rows, tile_cols);
 }
 
 extern "C" int sl_linear_forward(void* stream, const void* x, int32_t x_tiled, const void* packed, const int32_t* m_dev,

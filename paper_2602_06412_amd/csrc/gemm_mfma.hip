@@ -513,25 +513,21 @@ static int launch_gemm(hipStream_t s, const void* A, int a_tiled, const void* Wp
 
 // Which kernel a launch bounded by mu rows takes (one decision, shared by the launcher and by
 // sl_linear_plan): kind 0 = weight-stream kernel (rows = 32 or 64, cols = 128 or 256 per workgroup),
-// 1 = ring kernel (rows as its launcher chooses; tail is 0), 2 = 128 x 256 LDS kernel (short reductions).
-struct KernelPick { int kind, rows, cols, tail; };
-void slk_ring_describe(int mu, int n, int splits, int* rows, int* tail);     // gemm_mfma256.hip
+// 1 = ring kernel (rows as its launcher chooses), 2 = 128 x 256 LDS kernel (short reductions).
+struct KernelPick { int kind, rows, cols; };
+int slk_ring_tile_rows(int mu, int n, int splits);     // gemm_mfma256.hip
 static KernelPick pick_kernel(int mu, int n, int k, int splits, bool f32_out) {
   if (mu > kThinMax && k / splits >= 256) {
     const GemmPlan plan = gemm_plan(mu, n, k);
     const bool use256 = plan.splits == splits ? plan.thick256 != 0 : true;
-    if (use256) {
-      KernelPick p{1, 256, 256, 0};
-      slk_ring_describe(mu, n, splits, &p.rows, &p.tail);
-      return p;
-    }
+    if (use256) return KernelPick{1, slk_ring_tile_rows(mu, n, splits), 256};
   }
   // the barrier-free weight stream with one 32-row block (at most 32 rows) or two (33..64 rows, reached
   // only where the reduction is too short for the ring kernel)
-  if (f32_out && mu <= 32 && thin_narrow(n, k, splits)) return KernelPick{0, 32, 128, 0};
-  if (mu <= 32 && (k / splits) % 128 == 0) return KernelPick{0, 32, 256, 0};
-  if (mu <= 64 && (k / splits) % 128 == 0) return KernelPick{0, 64, 256, 0};
-  return KernelPick{2, pick_bm(mu), 256, 0};
+  if (f32_out && mu <= 32 && thin_narrow(n, k, splits)) return KernelPick{0, 32, 128};
+  if (mu <= 32 && (k / splits) % 128 == 0) return KernelPick{0, 32, 256};
+  if (mu <= 64 && (k / splits) % 128 == 0) return KernelPick{0, 64, 256};
+  return KernelPick{2, pick_bm(mu), 256};
 }
 
 // Thin unsplit gate|up projection with SwiGLU in its epilogue: a [mu <= 32 rows, dff] bf16, fragment-tiled.
@@ -557,11 +553,11 @@ int slk_gemm_stream_swiglu_ok(int mu, int dff, int k) {
   return p.kind == 0 && p.rows == 32;
 }
 
-// kind / splits / rows / cols / tail of the launch sl_linear_forward(.., splits = 0, y_f32) would make
-int slk_gemm_describe(int mu, int n, int k, int* kind, int* splits, int* rows, int* cols, int* tail) {
+// kind / splits / rows / cols of the launch sl_linear_forward(.., splits = 0, y_f32) would make
+int slk_gemm_describe(int mu, int n, int k, int* kind, int* splits, int* rows, int* cols) {
   const int S = gemm_plan(mu, n, k).splits;
   const KernelPick p = pick_kernel(mu, n, k, S, true);
-  *kind = p.kind; *splits = S; *rows = p.rows; *cols = p.cols; *tail = p.tail;
+  *kind = p.kind; *splits = S; *rows = p.rows; *cols = p.cols;
   return SL_OK;
 }
 

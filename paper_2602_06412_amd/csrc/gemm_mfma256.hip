@@ -631,11 +631,7 @@ static RingChoice ring_choice(int mu, int n, int splits) {
 
 // cost of the cheapest ring launch for (mu rows, n columns, `splits` k-splits), in full-tile rounds
 double slk_ring_cost(int mu, int n, int splits) { return ring_choice(mu, n, splits).cost; }
-void slk_ring_describe(int mu, int n, int splits, int* rows, int* tail) {
-  const RingChoice c = ring_choice(mu, n, splits);
-  *rows = c.tm;
-  *tail = 0;
-}
+int slk_ring_tile_rows(int mu, int n, int splits) { return ring_choice(mu, n, splits).tm; }
 
 template <int OUT>
 static int launch256(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n, int k,

@@ -312,7 +312,7 @@ int slk_gemm_mfma256_probe(hipStream_t s, const void* A, int a_tiled, const void
 int slk_gemm_mfma256_swiglu(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int dff, int k,
                             void* a);
 int slk_gemm_splits(int mu, int n, int k);
-int slk_gemm_describe(int mu, int n, int k, int* kind, int* splits, int* rows, int* cols, int* tail);
+int slk_gemm_describe(int mu, int n, int k, int* kind, int* splits, int* rows, int* cols);
 // a_tiled: A is in the fragment-tiled layout (rows padded to 32) instead of row-major
 int slk_gemm_mfma(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n, int k,
                   int splits, float* Cf, void* Cb, const int32_t* row_map, size_t ldc);

@@ -19,8 +19,8 @@ CASES = [
     (1024, 4096, 64, 33),
     (4160, 1024, 128, 100),
     (4160, 512, 96, 70),
-    (4160, 1024, 320, 300),       # one full 256-row tile and a ragged one
-    (2048, 2048, 384, 200),       # the second row tile lies wholly beyond the device-side row count
+    (4160, 1024, 320, 300),       # four full row tiles and a ragged one
+    (2048, 2048, 384, 200),       # the last two row tiles lie wholly beyond the device-side row count
     (32768, 512, 300, 290),       # 128 column tiles, two row tiles
     (12288, 1536, 704, 700),
     (8192, 4096, 1024, 1000),
@@ -28,7 +28,7 @@ CASES = [
     (4096, 4096, 16, 13),         # thin launches with few column tiles: the 128-column weight-stream tiles
     (4096, 12288, 32, 32),
     (4160, 2048, 24, 20),         # ... with a column tail
-    # the ring kernel's fitted tile heights (64 .. 256 rows in steps of 32), ragged row counts
+    # the ring kernel at every multiple of 32 rows, ragged row counts (every tile height: tests/test_gpu_gemm_k_remainder.py)
     (4160, 1024, 64, 50),
     (4160, 1024, 96, 90),
     (8192, 2048, 160, 150),
@@ -49,8 +49,8 @@ CASES = [
     (12288, 4096, 390, 387),      # ring, 224-row tiles, split
     (12288, 4096, 810, 805),      # ring, 192-row tiles, unsplit
     (12288, 4096, 1140, 1140),    # ring, 256-row tiles, unsplit
-    (12288, 4096, 2578, 2570),    # ring, eleven row tiles, unsplit
-    (24576, 4096, 1140, 1135),    # ring, full-height tiles + half-height tail tile, unsplit (480 workgroups)
+    (12288, 4096, 2578, 2570),    # ring, 128-row tiles, four rounds of workgroups, unsplit
+    (24576, 4096, 1140, 1135),    # ring, 256-row tiles with a ragged last one, unsplit (480 workgroups)
     # 16 row tiles and more: an XCD walks its column tiles in bands of four (25 column tiles: one whole band,
     # seven of the eight XCDs with a tile short; 49: a whole band and a ragged one of three)
     (6400, 512, 4200, 4190),

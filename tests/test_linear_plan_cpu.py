@@ -13,11 +13,11 @@ LLADA = {"q|k|v": (3 * HD, D), "out": (D, HD), "gate|up": (2 * DFF, D), "down": 
 
 
 def _form(plan):
-    kernel, splits, rows, cols, tail = plan
+    kernel, splits, rows, cols, _ = plan
     if kernel == 0:                       # weight-stream kernel: (rows per block, columns per tile, trips: splits matter)
         return ("stream", rows, cols, splits)
-    if kernel == 1:                       # ring kernel: tile height / tail tile; any split count runs the same loop
-        return ("ring", rows, cols, "tail" if tail else "uniform", "split" if splits > 1 else "unsplit")
+    if kernel == 1:                       # ring kernel: tile height; any split count runs the same loop
+        return ("ring", rows, cols, "split" if splits > 1 else "unsplit")
     return ("lds", rows, cols, "split" if splits > 1 else "unsplit")
 
 
@@ -36,7 +36,7 @@ def test_plan_is_consistent_with_the_split_query_and_its_limits():
         for mu in (1, 16, 32, 33, 64, 200, 512, 1000, 4096):
             kernel, splits, rows, cols, tail = B.sl_linear_plan(mu, n, k)
             assert splits == B.sl_linear_splits(mu, n, k) and splits >= 1 and k % (64 * splits) == 0
-            assert kernel in (0, 1, 2) and cols in (128, 256) and tail in (0, 1)
+            assert kernel in (0, 1, 2) and cols in (128, 256) and tail == 0
             if kernel == 0:
                 assert mu <= 64 and rows in (32, 64) and rows >= min(mu, 64)
                 assert (k // splits) % (256 if cols == 128 else 128) == 0       # whole trips of the register ring
