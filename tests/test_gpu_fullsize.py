@@ -31,8 +31,8 @@ def test_c2_full_size_sampled_rows():
         rng = np.random.default_rng(0)
         prev_rows = {}
         active = np.arange(N)
-        # 820 and 300 rows: a ragged last row tile (full-height tiles + one half-height tail tile in the LM head);
-        # 420 and 213 rows: fitted tile heights of 224 and 128 rows under the fused SwiGLU and RoPE epilogues
+        # 820 and 300 rows: a ragged last row tile; 420 and 213 rows: gate|up tiles of 224 and 128 rows under the fused
+        # SwiGLU, Q|K|V once as tiles of 96 rows under the fused RoPE and once split over k
         for t, M in ((1, 1024), (2, 820), (3, 420), (4, 300), (5, 213), (6, 16)):
             # the active set only ever shrinks (locks are permanent): nested subsets
             active = active if M == len(active) else active[wl.active_positions(50 + M, len(active), M)]
@@ -158,13 +158,13 @@ def test_c2_probe_of_all_rows_reproduces_the_step():
         sess.close()
 
 
-@pytest.mark.parametrize("M", [2600, 1800])
+@pytest.mark.parametrize("M", [2600, 2300])
 def test_c2_fitted_tile_launches_agree_with_full_height_ones(M):
     """M active rows of 3 x 1024 slots: with m_upper = M the Q|K|V (fused RoPE + scatter) and gate|up (fused
-    SwiGLU) launches run row tiles fitted to M rows (2600: twelve tiles of 224 rows for gate|up, fourteen of 192
-    for Q|K|V; 1800: gate|up as seven full-height tiles plus one half-height tail tile, Q|K|V as ten of 192 rows),
-    with m_upper = 3072 (same true M) twelve full-height tiles.  An output element accumulates its k-tiles in the
-    same order whatever the tile, so the K/V cache must agree bit for bit.  The Out and down projections may be
+    SwiGLU) launches run row tiles fitted to M rows, with m_upper = 3072 (same true M) tiles of another height (the
+    plans are asked, so that a change of theirs cannot leave a launch compared with itself).  An output element
+    accumulates its k-tiles in the same order whatever the tile, so the K/V cache, which with one layer depends on
+    the Q|K|V launch alone, must agree bit for bit.  The Out and down projections may be
     split over k differently under the two bounds (another fp32 summation order), so the logits may differ by a
     rounding here and there, not more.  (Both row counts keep attention on one launch plan under either bound:
     more than 384 (row tile, head) workgroups, keys not split.  A bound that changes the key split changes
@@ -172,6 +172,9 @@ def test_c2_fitted_tile_launches_agree_with_full_height_ones(M):
     values themselves are anchored by the oracle in the tests above.  A launch repeated with the same bound must
     reproduce itself exactly."""
     shape, N, Bn = wl.C2, 1024, 3
+    for n in (3 * shape.n_heads * shape.d_head, 2 * shape.d_ff):
+        fitted, other = (B.sl_linear_plan(m_upper, n, shape.d_model) for m_upper in (M, Bn * N))
+        assert fitted[:2] == other[:2] == (1, 1) and fitted[2] != other[2], f"{n} columns: {fitted} and {other}"
     w = wl.make_weights(shape, seed=0, device="cuda", emb_std=1.0)
     sess = B.Session(shape, w, Bn, N)
     try:
