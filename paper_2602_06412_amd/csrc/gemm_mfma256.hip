@@ -558,6 +558,10 @@ __global__ __launch_bounds__(256, 1) void gemm_mfma256_kernel(
   ring_tile<OUT, TM, NT, PROBE>(A, a_tiled, Wp, n, k, k_per_split, M, m_upper, Cf, Cb, row_map, ldc, tm * TM, tn, probe, rs);
 }
 
+// Workgroup slots a launch takes on the chip's 256 CUs.  Column tiles go to the XCDs in turn, so the XCD with the most of
+// them (32 CUs) decides how many rounds there are, and the slots it leaves empty elsewhere count.
+static int ring_slots(int tiles_m, int tiles_n, int splits) { return 8 * tiles_m * sl_cdiv(tiles_n, 8) * splits; }
+
 // Whether a launch's weight loads carry the non-temporal hint.  With one row tile a weight line is wanted once, and in one
 // round of workgroups the row tiles of a column want it at about the same time: the hint keeps the weights from pushing
 // activations and planes out of the caches (one row tile, LM head of 64 rows: 168 us with it, 194 without; one round, Q|K|V
@@ -567,7 +571,7 @@ __global__ __launch_bounds__(256, 1) void gemm_mfma256_kernel(
 // it until more than 3072 rows share the lines: LM head of 4654 rows 3714 / 3217, of 8192 rows 5882 / 5659, gate|up 654 / 637
 // and 1111 / 1090; at 2304 rows gate|up gains 3 us and the down projection behind it loses 13, its activations evicted.
 static bool stream_weights(int tiles_m, int tiles_n, int splits, int tm) {
-  if (tiles_m == 1 || tiles_m * tiles_n * splits <= 256) return true;
+  if (tiles_m == 1 || ring_slots(tiles_m, tiles_n, splits) <= 256) return true;
   return tm > 160 && tiles_m * tm <= 3072;
 }
 
@@ -605,9 +609,9 @@ static int launch_ring(hipStream_t s, const void* A, int a_tiled, const void* Wp
 // A launch runs uniform tiles of one height (any multiple of 32 from 64 to 256): the smallest number of
 // row tiles that covers the rows, or more and shorter ones where that saves a round of workgroups.
 // Fewer, taller tiles win near-ties (less operand traffic per flop).
-static double ring_rounds_cost(int workgroups) {
-  const int rest = workgroups % 256;
-  return workgroups / 256 + (rest ? 0.9 + 0.025 * rest / 256.0 : 0.0);
+static double ring_rounds_cost(int slots) {
+  const int rest = slots % 256;
+  return slots / 256 + (rest ? 0.9 + 0.025 * rest / 256.0 : 0.0);
 }
 static const double kTileCost[9] = {0, 0, 0.485, 0.55, 0.56, 0.70, 0.795, 0.86, 1.0};   // by TM / 32
 
@@ -616,14 +620,13 @@ struct RingChoice {
   double cost;     // in full-tile rounds
 };
 static RingChoice ring_choice(int mu, int n, int splits) {
-  const int tn = sl_cdiv(n, TILE) * splits;
   RingChoice best{256, 1e30};
   const int t_min = sl_cdiv(mu, 256), t_max = sl_cdiv(mu, 64);
   for (int t = t_min; t <= t_max; ++t) {
     int tm = (int)sl_align_up((size_t)sl_cdiv(mu, t), 32);
     if (tm < 64) tm = 64;
     if (sl_cdiv(mu, tm) != t) continue;              // the same height with fewer tiles was already priced
-    const double c = ring_rounds_cost(t * tn) * kTileCost[tm / 32];
+    const double c = ring_rounds_cost(ring_slots(t, sl_cdiv(n, TILE), splits)) * kTileCost[tm / 32];
     if (c < 0.99 * best.cost) best = RingChoice{tm, c};
   }
   return best;

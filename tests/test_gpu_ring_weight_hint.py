@@ -17,7 +17,8 @@ def _cached(m_upper, n, k):
     """The rule, restated: more than one row tile and round, and short tiles or more than 3072 rows."""
     kernel, splits, height, cols, _ = B.sl_linear_plan(m_upper, n, k)
     tiles = -(-m_upper // height)
-    return kernel == 1 and tiles > 1 and tiles * -(-n // cols) * splits > 256 and (height <= 160 or tiles * height > 3072)
+    slots = 8 * tiles * -(-(-(-n // cols)) // 8) * splits
+    return kernel == 1 and tiles > 1 and slots > 256 and (height <= 160 or tiles * height > 3072)
 
 
 @pytest.mark.parametrize("n,k,m_upper,m", [(256 * 129 + 96, 256, 300, 281), (8192, 512, 3300, 3290)])

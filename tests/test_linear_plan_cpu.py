@@ -46,3 +46,13 @@ def test_plan_is_consistent_with_the_split_query_and_its_limits():
         B.sl_linear_plan(0, 4096, 4096)
     with pytest.raises(B.SureLockError):
         B.sl_linear_plan(16, 4096, 100)
+
+
+@pytest.mark.parametrize("m_upper,n,k", [(1024, 5632, 4096), (640, 8256, 4096), (1840, 3072, 2048), (860, 3072, 4096),
+                                         (460, 3072, 8192), (8192, 512, 1024), (4096, 1024, 1024)])
+def test_plan_counts_the_fullest_xcd(m_upper, n, k):
+    """Column tiles go to the eight XCDs (32 CUs each) in turn.  These column counts leave them uneven, and tiles chosen by
+    the chip-wide number of workgroups put 33 and more on one XCD, a second round for that alone (101 us where taller
+    tiles take 56); each of these launches fits one round."""
+    kernel, splits, rows, cols, _ = B.sl_linear_plan(m_upper, n, k)
+    assert kernel == 1 and -(-m_upper // rows) * -(-(-(-n // cols)) // 8) * splits <= 32
