@@ -14,7 +14,8 @@
 //    floor is 1024).  LDS addresses are two base registers plus immediates, global ones scalar bases.
 //  * The epilogues work on registers: two lane-group swaps give a lane eight consecutive columns, i.e. 16-byte
 //    pieces (8-byte pieces: 19000 cycles per tile; 16-byte: 10000).
-// Measured at 8192 rows (us; before = eight-wave form): 24576 x 4096 1193 -> 1138, 4096 x 12288 569 -> 530.
+// Inside a step of 8192 rows (us; eight-wave form -> this): 24576 x 4096 1188 -> 1130, 4096 x 12288 578 -> 539, the LM head
+// 6142 -> 5696.
 //
 // A short tile is bound by the rate at which one CU pulls lines that miss its L2 (about 20 B per clock, whatever
 // the depth of the ring: four or eight k-tiles in flight measure the same), so a launch wants many CUs before it
@@ -311,7 +312,8 @@ __device__ __forceinline__ void ring_tile(
     // (scoring 111 -> 99 us)
     // The rows leave through LDS (a wave's own corner of the drained ring), eight rows of a whole 128-byte line each per
     // instruction: stored from the accumulators' layout, half lines at a time, the launch wrote 1.45 times its bytes.
-    // One map entry per thread, all at once.  LM head: 8192 rows 6164 -> 5878 us, 1024 rows 800 -> 781, 512 rows 489 -> 466.
+    // One map entry per thread, all at once.  LM head, both forms of the stores on one box (weights still hinted): 8192 rows
+    // 6164 -> 5878 us, 1024 rows 800 -> 781, 512 rows 489 -> 466.
     __syncthreads();
     int* row_sh = reinterpret_cast<int*>(lds);        // [TM] output row, -1 past M
     {
