@@ -1,5 +1,5 @@
-// The projection GEMM of all launches bounded by more than 32 rows: one TM x 256 output tile per workgroup and CU,
-// TM any multiple of 32 from 64 to 256.  Four waves, one per SIMD; each owns all TM rows of 64 columns (up to 256
+// The projection GEMM of launches bounded by more than 32 rows (inside a layer more than 256, where gemm_wavek.hip takes
+// the shape): one TM x 256 output tile per workgroup and CU, TM any multiple of 32 from 64 to 256.  Four waves, one per SIMD; each owns all TM rows of 64 columns (up to 256
 // accumulator registers), so a weight fragment is wanted by exactly one wave.
 //
 //  * Weights go global -> registers: a ring of DB k-tiles (32 deep) of B fragments per wave.  They never touch LDS,
@@ -29,12 +29,7 @@
 // 32 x 16 blocks by giving every lane its own slot address; each group of 16 lanes still reads
 // 256 contiguous bytes.  The weight fragment is passed as the first operand, so a lane ends up
 // with four consecutive columns of one output row.
-#include "sl_common.h"
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef bf16x8 Frag;
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+#include "mfma_tile.h"
 
 constexpr int BK2 = 32;                   // k per k-tile: one 16x16x32 MFMA k-step
 constexpr int TILE = 256;                 // columns per tile, and rows of the full-height tile
@@ -67,16 +62,6 @@ template <int TM> struct TileCfg {
 // PROBE: one workgroup in the middle of the grid also records shader-clock cycles and 100 MHz
 // wall ticks of its prologue, k loop and epilogue into probe[0..7] (a measurement aid: the
 // clock under this kernel is set by the chip's power management, not by the nominal 2.4 GHz).
-// OUT = 3: the Q|K|V projection with RoPE and the scatter into q / the K and V caches in its epilogue
-// (the launch then replaces the projection's fp32 output and the separate RoPE + cache-write kernel).
-struct RopeScatter {
-  const int32_t* active_idx;   // [M] flat row ids
-  const float2* rope_tab;      // [n_pad][64] (cos, sin)
-  bf16_t* q;                   // [M, H*128] packed
-  bf16_t* kc;                  // this layer's K cache, or null (queries only)
-  bf16_t* vc;                  // this layer's V cache, or null
-  int N, n_pad, H;
-};
 
 // Wait until at most N younger loads are outstanding; names the registers it releases, which keeps the MFMAs that
 // read them behind it.
@@ -84,19 +69,6 @@ template <int N>
 __device__ __forceinline__ void b_landed(Frag (&b)[NB]) {
   static_assert(N >= 0 && N <= 63 && NB == 4, "vmcnt range");
   asm volatile("s_waitcnt vmcnt(%4)" : "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]) : "n"(N) : "memory");
-}
-
-// 8 consecutive columns per lane out of two 16 x 16 blocks: lane group g = l / 16 holds columns 4 g .. 4 g + 3 of
-// each; after swapping the odd groups of the first with the even groups of the second it holds columns
-// 8 (g / 2) .. + 7 of block g % 2.
-__device__ __forceinline__ uint4 pack_swap(const f32x4& x, const f32x4& y) {
-  bf16x4 vx, vy;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) { vx[e] = (bf16_t)x[e]; vy[e] = (bf16_t)y[e]; }
-  const uint2 ux = __builtin_bit_cast(uint2, vx), uy = __builtin_bit_cast(uint2, vy);
-  const auto p = __builtin_amdgcn_permlane16_swap(ux.x, uy.x, false, false);
-  const auto q = __builtin_amdgcn_permlane16_swap(ux.y, uy.y, false, false);
-  return make_uint4(p[0], q[0], p[1], q[1]);
 }
 
 // One TM x 256 output tile (rows m0 .., column tile tn) by the whole 256-thread workgroup.
@@ -411,16 +383,7 @@ __device__ __forceinline__ void ring_tile(
     // the ring is drained: its space holds each row's flat id, sequence and slot (-1 past M)
     __syncthreads();
     int* row_sh = reinterpret_cast<int*>(lds);        // [TM] flat id, [TM] sequence, [TM] slot
-    {
-      const int r = threadIdx.x, row = m0 + r;
-      if (r < TM) {
-        const int g = row < M ? rs.active_idx[row] : -1;
-        const int bb = g < 0 ? 0 : g / rs.N;
-        row_sh[r] = g;
-        row_sh[TM + r] = bb;
-        row_sh[2 * TM + r] = g - bb * rs.N;
-      }
-    }
+    scatter_rows_of_tile(row_sh, TM, m0, M, rs);
     __syncthreads();
     if (sec < 2) {
 #pragma unroll
@@ -429,42 +392,15 @@ __device__ __forceinline__ void ring_tile(
         for (int b = 0; b < NB; ++b) asm volatile("" : "+a"(acc[a][b]));     // read here, not all at once ahead (spills)
         const int r = a * 16 + row_in;
         if (row_sh[r] < 0) continue;
-        const int bb = row_sh[TM + r], i = row_sh[2 * TM + r];
-        const float4* tab = reinterpret_cast<const float4*>(rs.rope_tab + (size_t)i * 64 + j0);
-        f32x4 lo[2], hi[2];                           // dims j and j + 64
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          const float4 t0 = tab[b * 8 + 2 * g4], t1 = tab[b * 8 + 2 * g4 + 1];        // (cos, sin) pairs of 4 dims
-          const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float x = acc[a][b][e], y = acc[a][b + 2][e];
-            lo[b][e] = x * cs[e] - y * sn[e];
-            hi[b][e] = y * cs[e] + x * sn[e];
-          }
-        }
-        const uint4 o1 = pack_swap(lo[0], lo[1]), o2 = pack_swap(hi[0], hi[1]);
-        const int dim = j0 + (g4 & 1) * 16 + (g4 >> 1) * 8;
-        if (sec == 0) {
-          bf16_t* qr = rs.q + (size_t)(m0 + r) * hd + head * 128 + dim;
-          *reinterpret_cast<uint4*>(qr) = o1;
-          *reinterpret_cast<uint4*>(qr + 64) = o2;
-        } else {
-          bf16_t* kb = rs.kc + ((size_t)bb * rs.H + head) * rs.n_pad * 128;
-          *reinterpret_cast<uint4*>(kb + kc_index(i, dim, 128)) = o1;
-          *reinterpret_cast<uint4*>(kb + kc_index(i, 64 + dim, 128)) = o2;
-        }
+        float4 tab[4];
+        rope_load_row(tab, row_sh[2 * TM + r], j0, rs);
+        rope_store_row(acc[a], tab, sec, head, j0, m0 + r, row_sh[TM + r], row_sh[2 * TM + r], rs);
       }
     } else {
-      // V: the cache keeps eight slots of a dim together, so half of the tile's rows at a time go through LDS as
-      // cache elements (a wave's own corner, no barrier).  16 consecutive rows that are the 16 slots of one aligned
-      // block leave as 16-byte groups of eight slots per dim; other rows as 2-byte stores, a row per instruction.
-      constexpr int RS = 72, GR = (NA + 1) / 2;       // elements per staged row; 16-row groups per pass
-      static_assert(3 * TM * 4 + 4 * GR * 16 * RS * 2 <= TC::LDS, "staging fits the ring");
-      bf16_t* stage = reinterpret_cast<bf16_t*>(row_sh + 3 * TM) + wave * GR * 16 * RS;
-      const int dim = j0 + (lane & 31) + (lane >> 5) * 64;      // staged columns 0 .. 31: dims j0 .., 32 .. 63: the same + 64
-      bf16_t* vb = rs.vc + (size_t)head * rs.n_pad * 128;
-      const size_t seq = (size_t)rs.H * rs.n_pad * 128;
+      // half of the tile's rows at a time
+      constexpr int GR = (NA + 1) / 2;                // 16-row groups per pass
+      static_assert(3 * TM * 4 + 4 * GR * 16 * VSTAGE * 2 <= TC::LDS, "staging fits the ring");
+      bf16_t* stage = reinterpret_cast<bf16_t*>(row_sh + 3 * TM) + wave * GR * 16 * VSTAGE;
 #pragma unroll
       for (int pass = 0; pass < 2; ++pass) {
         constexpr int G0 = GR;
@@ -476,40 +412,13 @@ __device__ __forceinline__ void ring_tile(
           for (int b = 0; b < NB; ++b) {
             f32x4& c = acc[pass * GR + a < NA ? pass * GR + a : 0][b];
             asm volatile("" : "+a"(c));
-            bf16x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = vcache_half_bits(c[e]);
-            *reinterpret_cast<bf16x4*>(stage + (a * 16 + row_in) * RS + b * 16 + 4 * g4) = v;
+            v_stage_block(stage, a * 16 + row_in, b, c);
           }
         }
 #pragma unroll 1
         for (int a = 0; a < groups; ++a) {
-          const int r0 = (pass * GR + a) * 16;
-          const bf16_t* col = stage + a * 16 * RS + lane;
-          const int g0 = row_sh[r0], i0 = row_sh[2 * TM + r0];
-          const int g = row_sh[r0 + row_in], bb = row_sh[TM + r0 + row_in], i = row_sh[2 * TM + r0 + row_in];
-          if (g0 >= 0 && i0 % 16 == 0 && i0 + 16 <= rs.N && __all(g == g0 + row_in)) {
-            bf16_t* vr = vb + row_sh[TM + r0] * seq;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              bf16x8 o;
-#pragma unroll
-              for (int e = 0; e < 8; ++e) o[e] = col[((e >> 2) * 8 + 4 * h + (e & 3)) * RS];
-              *reinterpret_cast<bf16x8*>(vr + vc_index(i0 + 4 * h, dim, 128)) = o;
-            }
-          } else {
-            // lane r of the first 16 holds row r's offset; it is read across as a scalar
-            const uint64_t off = g < 0 ? 0 : (uint64_t)bb * seq + vc_index(i, 0, 128);
-            const uint32_t off_lo = (uint32_t)off, off_hi = (uint32_t)(off >> 32);
-            bf16_t v[16];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) v[r] = col[r * RS];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const uint64_t o = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(off_hi, r) << 32 | (uint32_t)__builtin_amdgcn_readlane(off_lo, r);
-              if (__builtin_amdgcn_readlane(g, r) >= 0) vb[o + (uint32_t)dim * 8] = v[r];
-            }
-          }
+          const int r = (pass * GR + a) * 16 + row_in;
+          v_store_rows(stage + a * 16 * VSTAGE, row_sh[TM + r], row_sh[2 * TM + r], head, j0, rs);
         }
       }
     }

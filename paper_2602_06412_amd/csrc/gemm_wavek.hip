@@ -1,0 +1,366 @@
+// The layer's projections of at most 256 rows: one workgroup per column slice takes ALL rows, its four waves a quarter of
+// the reduction each.
+//
+// What bounds these launches is the number of 128-byte lines a CU has under way: about 256 of them, whatever the depth of
+// the rings, so a line that misses L2 (625 ns) moves at 52 GB/s per CU, one that hits at 125, a mixture at 45 to 68.  A tile
+// of R rows and C columns pulls (R + C) k elements; the 128 x 256 tiles of the ring kernel on 192 CUs pull 3.1 MB for the
+// gate|up projection of 224 rows (70 us), 224 x 96 on 256 CUs 2.6 MB, of which only 0.8 come from HBM.
+//
+//  * With the waves along k a wave wants every activation fragment of its k-tiles and nobody else does: fragments go
+//    global -> LDS -> registers inside the wave, with no barrier in the k loop, each read from LDS once.
+//  * Weights go global -> registers, each fragment wanted by one wave of the whole launch (non-temporal).  They are asked for
+//    in one go at the end of a k-step, together with nothing else: hits queue behind misses, so misses in bursts cost one
+//    latency per 256 lines (8 misses and 20 hits a burst 68 GB/s per CU, 2 and 4: 55).
+//  * At the end the four waves' sums meet in LDS, 64 rows at a time; row block 4 p + w is added up and finished by
+//    wave w.
+#include "mfma_tile.h"
+
+constexpr int WK_WAVES = 4;
+constexpr int WK_K = 32;                              // k per MFMA step
+constexpr int WK_STEP = WK_K * WK_WAVES;              // k per step of the workgroup
+
+// NA 16-row blocks, NBK 16-column blocks; RD steps of a wave in its rings.
+template <int OUT, int NA, int NBK> struct WkCfg {
+  static constexpr int RD = NA <= 8 ? 4 : 2;
+  static constexpr int P = NA + NBK;                  // loads per wave and step
+  static constexpr int R = NA < 4 ? NA : 4;           // activation fragments read ahead
+  static constexpr int RING = WK_WAVES * RD * NA * 1024;
+  static constexpr int PASS = WK_WAVES * (WK_WAVES - 1) * NBK * 1024;       // sums that change waves in one pass of 64 rows
+  static constexpr int BUFS = NA > 4 ? 2 : 1;
+  static constexpr int EPI = BUFS * PASS + (OUT == 3 ? WK_WAVES * 16 * VUNIT * 2 : 0);
+  static constexpr int LDS = RING > EPI ? RING : EPI;
+  static_assert((OUT == 3 ? RD : RD - 1) * P <= 63 && LDS <= 160 * 1024, "wait counts, LDS");
+};
+
+template <int V> struct WkInt { static constexpr int value = V; };
+
+template <int N, int NBK>
+__device__ __forceinline__ void wk_landed(Frag (&b)[NBK]) {
+  static_assert(N >= 0 && N <= 63 && (NBK == 4 || NBK == 6), "vmcnt range");
+  if constexpr (NBK == 4)
+    asm volatile("s_waitcnt vmcnt(%4)" : "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]) : "n"(N) : "memory");
+  else
+    asm volatile("s_waitcnt vmcnt(%6)" : "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]), "+v"(b[4]), "+v"(b[5]) : "n"(N) : "memory");
+}
+
+// OUT 0: fp32 plane of the k-split (Cf [splits][m_upper][n]); 2: gate|up with SwiGLU (Cb, fragment-tiled, ldc = d_ff);
+// 3: Q|K|V with RoPE and the cache scatter.
+template <int OUT, int NA, int NBK>
+__global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp, int n, int k, int splits, const int32_t* __restrict__ m_dev,
+    int m_upper, float* __restrict__ Cf, bf16_t* __restrict__ Cb, size_t ldc, int tiles_m, int tiles_n, RopeScatter rs) {
+  typedef WkCfg<OUT, NA, NBK> WC;
+  constexpr int RD = WC::RD, P = WC::P, R = WC::R, HB = NBK / 2;
+  extern __shared__ Frag lds[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int g4 = lane >> 4, row_in = lane & 15;
+  // consecutive workgroups go to consecutive XCDs: with the split in the low bits an XCD sees one split's activations
+  // and the row tiles of one column tile stay on one XCD
+  const int split = blockIdx.x % splits, wg = blockIdx.x / splits;
+  const int tm = (wg >> 3) % tiles_m, tn = (wg >> 3) / tiles_m * 8 + (wg & 7), m0 = tm * NA * 16;
+  if (tn >= tiles_n || (tm > 0 && m0 >= *m_dev)) return;
+  const int k_split = k / splits, steps = k_split / WK_STEP;
+  const int K16 = k / 16, NF = n / 16;
+
+  // packed 16-column block of this tile's block b
+  auto col_block = [&](int b) {
+    if constexpr (OUT == 2) {                         // gate blocks, then the up blocks of the same columns
+      const int t = tn * HB + b % HB;
+      return (t >> 1) * 4 + (t & 1) + (b / HB) * 2;
+    } else if constexpr (OUT == 3) {                  // dims j .., then the dims 64 further on, of one head
+      const int u = tn * HB + b % HB;
+      return (u >> 2) * 8 + (u & 3) + (b / HB) * 4;
+    } else {
+      return tn * NBK + b;
+    }
+  };
+  // a 16 x 32 operand lies in two neighbouring 32 x 16 blocks: lane l takes row l % 16 and the 8 k of group l / 16, 256
+  // contiguous bytes per group
+  const uint32_t lane_off = ((uint32_t)(g4 >> 1) * 64u + (uint32_t)((g4 & 1) * 32 + row_in)) * 16u;
+  uint32_t b_voff[NBK];
+#pragma unroll
+  for (int b = 0; b < NBK; ++b) {
+    const int f = min(col_block(b), NF - 1);          // columns past the end: valid ones, not stored
+    b_voff[b] = (uint32_t)(f >> 1) * (uint32_t)K16 * 1024u + (uint32_t)(f & 1) * 256u + lane_off;
+  }
+  const int n_mb = (m_upper + 31) / 32;
+  uint32_t a_voff[NA];
+#pragma unroll
+  for (int a = 0; a < NA; ++a) {
+    const int ab = m0 / 16 + a;                       // rows past the end: valid ones, not stored
+    a_voff[a] = (uint32_t)min(ab >> 1, n_mb - 1) * (uint32_t)K16 * 1024u + (uint32_t)(ab & 1) * 256u + lane_off;
+  }
+  // wave w takes the k-tiles w, w + 4, ..: a workgroup reads its column blocks in contiguous 8 KiB
+  const uint32_t k_off = ((uint32_t)(split * k_split) / 16u + (uint32_t)wave * 2u) * 1024u;
+  uint64_t pa = (uint64_t)(uintptr_t)A + k_off, pb = (uint64_t)(uintptr_t)Wp + k_off;
+  constexpr uint32_t K_STEP = WK_STEP / 16 * 1024;
+  // the flat ids of the rows this lane will finish, asked for first and used after the last wait of the k loop
+  constexpr int PASSES = (NA + 3) / 4;
+  int gid[PASSES];
+  if constexpr (OUT == 3) {
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+      gid[p] = 0;
+      const uint32_t off = (uint32_t)min(m0 + (p * 4 + wave) * 16 + row_in, m_upper - 1) * 4u;
+      asm volatile("global_load_dword %0, %1, %2" : "+v"(gid[p]) : "v"(off), "s"(rs.active_idx) : "memory");
+    }
+  }
+
+  // Loads are inline assembly: the compiler would make every LDS read wait for all direct-to-LDS loads.  The register-ring
+  // contract: fb is a read-write operand of every load and of the wait that covers it, every fetched slot is consumed, and
+  // the kernel holds no spill (the build fails on scratch).
+  const uint32_t ring = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) Frag*)lds + (uint32_t)wave * (RD * NA * 1024u));
+  typedef const __attribute__((address_space(3))) Frag LFrag;
+  LFrag* ring_l = (LFrag*)lds + wave * (RD * NA * 64) + lane;
+  asm volatile("" : "+v"(ring_l));
+  auto fetch_a = [&](int slot, int a) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(ring + (uint32_t)((slot * NA + a) * 1024)),
+                 "v"(a_voff[a]), "s"(pa) : "memory", "m0");
+  };
+  Frag fb[RD][NBK];
+#pragma unroll
+  for (int u = 0; u < RD; ++u)
+#pragma unroll
+    for (int b = 0; b < NBK; ++b) fb[u][b] = Frag{};
+  auto fetch_b = [&](int slot) {
+#pragma unroll
+    for (int b = 0; b < NBK; ++b)
+      asm volatile("global_load_dwordx4 %0, %1, %2 nt" : "+v"(fb[slot][b]) : "v"(b_voff[b]), "s"(pb) : "memory");
+    pb += K_STEP;
+  };
+  f32x4 acc[NA][NBK];
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int b = 0; b < NBK; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // the first 64 accumulator blocks live in the AGPR half, the rest beside the operands
+  auto mma = [&](const Frag& w, const Frag& x, int a, int b) {
+    if (a * NBK + b < 64) asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[a][b]) : "v"(w), "v"(x));
+    else asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[a][b]) : "v"(w), "v"(x));
+  };
+  auto pin = [&](int a, int b) {
+    if (a * NBK + b < 64) asm volatile("" : "+a"(acc[a][b]));
+    else asm volatile("" : "+v"(acc[a][b]));
+  };
+
+#pragma unroll
+  for (int u = 0; u < RD; ++u) {
+    fetch_b(u);
+#pragma unroll
+    for (int a = 0; a < NA; ++a) fetch_a(u, a);
+    pa += K_STEP;
+  }
+  if constexpr (OUT == 3) {                           // older than every fragment: here before the first of them
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) asm volatile("s_waitcnt vmcnt(%1)" : "+v"(gid[p]) : "n"(RD * P) : "memory");
+  }
+  const int M = min(*m_dev, m_upper);
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int b = 0; b < NBK; ++b) pin(a, b);          // zeroed before the wait states
+  asm volatile("s_nop 7" ::: "memory");
+
+  // one step out of slot u; FETCH: each fragment's slot is asked for again as soon as its MFMAs are issued
+  Frag af[R];
+  auto step = [&](auto fetch, int u, int v) {         // activations out of slot u, weights out of slot v
+#pragma unroll
+    for (int a = 0; a < R; ++a) af[a] = ring_l[(u * NA + a) * 64];
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+#pragma unroll
+      for (int b = 0; b < NBK; ++b) mma(fb[v][b], af[a % R], a, b);
+      if (a + R < NA) af[a % R] = ring_l[(u * NA + a + R) * 64];
+      if constexpr (decltype(fetch)::value) fetch_a(u, a);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (decltype(fetch)::value) pa += K_STEP;
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto landed = [&](auto younger, int v) {
+    wk_landed<decltype(younger)::value>(fb[v]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto weights = [&](int v) {
+    fetch_b(v);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int s = 0; s + RD < steps; s += RD) {
+#pragma unroll
+    for (int u = 0; u < RD; ++u) {
+      landed(WkInt<(RD - 1) * P>{}, u);
+      step(WkInt<1>{}, u, u);
+      weights(u);
+    }
+  }
+  // the last RD steps fetch nothing; after the last wait no load is in flight
+  landed(WkInt<(RD - 1) * P>{}, 0);
+  step(WkInt<0>{}, 0, 0);
+  landed(WkInt<(RD - 2) * P>{}, 1);
+  step(WkInt<0>{}, 1, 1);
+  if constexpr (RD == 4) {
+    landed(WkInt<P>{}, 2);
+    step(WkInt<0>{}, 2, 2);
+    landed(WkInt<0>{}, 3);
+    step(WkInt<0>{}, 3, 3);
+  }
+  static_assert(RD == 2 || RD == 4, "last steps are written out");
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int b = 0; b < NBK; ++b) pin(a, b);
+
+  // the waves' sums meet in LDS: of the row blocks 4 p .. 4 p + 3 wave w keeps block 4 p + w and hands the others over
+  int seq[PASSES];
+  float4 tab[OUT == 3 ? PASSES : 1][HB][2];
+  if constexpr (OUT == 3) {
+    if (rs.kc == nullptr && tn * HB >= 4 * rs.H) return;         // queries only (uniform over the workgroup)
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+      const int row = m0 + (p * 4 + wave) * 16 + row_in;
+      seq[p] = gid[p] / rs.N;
+      gid[p] = row < M && p * 4 + wave < NA ? gid[p] - seq[p] * rs.N : -1;       // the slot
+#pragma unroll
+      for (int b = 0; b < HB; ++b) rope_load_unit(tab[p][b], max(gid[p], 0), (tn * HB + b & 3) * 16, rs);
+    }
+  }
+  __syncthreads();                                    // every wave is done with its ring
+  bf16_t* stage = reinterpret_cast<bf16_t*>(reinterpret_cast<char*>(lds) + WC::BUFS * WC::PASS) + wave * 16 * VUNIT;
+#pragma unroll
+  for (int p = 0; p < PASSES; ++p) {
+    f32x4* exch = reinterpret_cast<f32x4*>(lds) + (p % WC::BUFS) * (WC::PASS / 16);   // [to][from, less the wave itself][NBK][64]
+    f32x4 c[NBK];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int a = p * 4 + j;
+      if (a >= NA) continue;
+#pragma unroll
+      for (int b = 0; b < NBK; ++b) pin(a, b);        // read here, not all at once ahead
+      if (j == wave) {
+#pragma unroll
+        for (int b = 0; b < NBK; ++b) c[b] = acc[a][b];
+      } else {
+        f32x4* e = exch + ((j * 3 + wave - (wave > j)) * NBK) * 64 + lane;
+#pragma unroll
+        for (int b = 0; b < NBK; ++b) e[b * 64] = acc[a][b];
+      }
+    }
+    __syncthreads();                                  // also: the pass before the last has been read
+    const int a = p * 4 + wave, row = m0 + a * 16 + row_in;
+    if (a >= NA || m0 + a * 16 >= M) continue;
+    // in wave order whichever wave adds: a row's sums do not depend on where in the launch it stands
+    const f32x4* e = exch + wave * 3 * NBK * 64 + lane;
+    auto add = [&](auto own) {
+#pragma unroll
+      for (int b = 0; b < NBK; ++b) {
+        const f32x4 x = e[b * 64], y = e[(NBK + b) * 64], z = e[(2 * NBK + b) * 64];
+        if constexpr (decltype(own)::value == 0) c[b] = c[b] + x + y + z;             // wave 0 or 1
+        else if constexpr (decltype(own)::value == 2) c[b] = x + y + c[b] + z;
+        else c[b] = x + y + z + c[b];
+      }
+    };
+    if (wave < 2) add(WkInt<0>{});
+    else if (wave == 2) add(WkInt<2>{});
+    else add(WkInt<3>{});
+    if constexpr (OUT == 0) {
+#pragma unroll
+      for (int b = 0; b < NBK; ++b) {
+        const int col = (tn * NBK + b) * 16 + 4 * g4;
+        if (row < M && col < n) *reinterpret_cast<f32x4*>(Cf + ((size_t)split * m_upper + row) * ldc + col) = c[b];
+      }
+    } else if constexpr (OUT == 2) {
+#pragma unroll
+      for (int b = 0; b < HB; ++b) {
+        const int col = (tn * HB + b) * 16 + 4 * g4;
+        bf16x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (bf16_t)silu_mul(c[b][e], c[b + HB][e]);
+        if (row < M && col < (n >> 1)) *reinterpret_cast<bf16x4*>(Cb + afrag_index(row, col, (int)ldc)) = v;
+      }
+    } else {
+#pragma unroll
+      for (int b = 0; b < HB; ++b) {
+        const int u = tn * HB + b, hsec = u >> 2, sec = hsec / rs.H, head = hsec - sec * rs.H, j0 = (u & 3) * 16;
+        if (sec > 2 || (sec > 0 && rs.kc == nullptr)) continue;
+        if (sec < 2) {
+          if (gid[p] >= 0) rope_store_unit(c[b], c[b + HB], tab[p][b], sec, head, j0, row, seq[p], gid[p], rs);
+        } else {
+          v_store_unit(stage, c[b], c[b + HB], head, j0, seq[p], gid[p], rs);
+        }
+      }
+    }
+  }
+}
+
+template <int OUT, int NA, int NBK>
+static int launch_wavek(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int n, int k, int splits,
+                        float* Cf, void* Cb, size_t ldc, const RopeScatter& rs) {
+  const size_t sh = WkCfg<OUT, NA, NBK>::LDS;
+  auto kern = gemm_wavek_kernel<OUT, NA, NBK>;
+  static unsigned long long lds_ok = 0;
+  SL_ALLOW_DYNAMIC_LDS(lds_ok, kern, sh);
+  const int tiles_m = sl_cdiv(mu, NA * 16), tiles_n = sl_cdiv(n, NBK * 16);
+  hipLaunchKernelGGL(kern, dim3(8 * sl_cdiv(tiles_n, 8) * tiles_m * splits), dim3(256), sh, s, (const bf16_t*)A, (const bf16_t*)Wp, n, k,
+                     splits, m_dev, mu, Cf, (bf16_t*)Cb, ldc, tiles_m, tiles_n, rs);
+  SL_LAUNCH_CHECK();
+  return SL_OK;
+}
+
+// The smallest NA of the list that covers the rows with `tiles_m` row tiles.
+template <int OUT, int NBK>
+static int launch_rows(hipStream_t s, int tiles_m, const void* A, const void* Wp, const int32_t* m_dev, int mu, int n, int k, int splits,
+                       float* Cf, void* Cb, size_t ldc, const RopeScatter& rs = RopeScatter{}) {
+  const int na = sl_cdiv(mu, 16 * tiles_m);
+#define GO(NA) if (na <= NA) return launch_wavek<OUT, NA, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc, rs)
+  if constexpr (NBK == 4 || OUT == 2) { GO(1); GO(2); GO(3); }
+  GO(4); GO(5); GO(6); GO(7); GO(8);
+  if constexpr (NBK == 4 || OUT == 2) { GO(10); GO(12); GO(14); GO(16); }
+#undef GO
+  return SL_EINVAL;
+}
+
+// ---- which launches ---------------------------------------------------------------------------------------------
+// At most 256 rows, whole trips of the rings, 32-bit offsets; and a single round of workgroups that fills most of the chip:
+// the slices are as narrow as the epilogues allow, so fewer than 160 of them leave too many CUs idle (the other kernels then
+// choose their own tiles), and a second round would read the activations again.  Measured at the LLaDA-8B shapes, one block at
+// N = 512, us before -> with these launches (before: the weight-stream kernel up to 32 rows, the ring kernel, and the RoPE
+// and SwiGLU kernels behind them): 16 rows 110 -> 98, 48 rows 134 -> 109, 64 rows 143 -> 118, 128 rows 163 -> 149,
+// 224 rows 204 -> 187, 256 rows 210 -> 195.
+constexpr int kWavekRows = 256;
+static bool wavek_fits(int mu, int n, int k, int splits, int workgroups) {
+  return mu > 0 && mu <= kWavekRows && n % 32 == 0 && k % (WK_STEP * 4 * splits) == 0 && (size_t)n * k * 2 < ((size_t)1 << 32) &&
+         sl_align_up(mu, 32) * k * 2 < ((size_t)1 << 32) && workgroups >= 160 && workgroups <= 256;
+}
+// Q|K|V: 64 columns (two units of 16 + 16 that RoPE pairs) for all rows; from 97 rows on 96 columns for half of the rows
+// each, where (rows / 2 + 96) is less to read than (rows + 64) and 256 CUs share the work instead of 192 (128 rows 39.5 -> 35.5
+// us, 256 rows 54 -> 45; 80 rows 32.5 -> 32.7, 64 rows 29.5 -> 32.5).
+static int qkv_row_tiles(int mu, int H) { return mu > 96 && 8 * H <= 256 ? 2 : 1; }
+int slk_wavek_qkv_ok(int mu, int H, int k) {
+  return H > 0 && wavek_fits(mu, 3 * H * 128, k, 1, qkv_row_tiles(mu, H) == 2 ? 8 * H : 6 * H);
+}
+int slk_wavek_qkv_rope(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int H, int k,
+                       const int32_t* active_idx, int N, int n_pad, const void* rope_tab, void* q, void* kc, void* vc) {
+  const int n = 3 * H * 128;
+  if (!slk_wavek_qkv_ok(mu, H, k) || !active_idx || !rope_tab || !q || (kc == nullptr) != (vc == nullptr)) return SL_EINVAL;
+  if ((uintptr_t)q % 16 || (uintptr_t)kc % 16 || (uintptr_t)vc % 16 || (uintptr_t)rope_tab % 16) return SL_EINVAL;
+  const RopeScatter rs{active_idx, (const float2*)rope_tab, (bf16_t*)q, (bf16_t*)kc, (bf16_t*)vc, N, n_pad, H};
+  if (qkv_row_tiles(mu, H) == 2) return launch_rows<3, 6>(s, 2, A, Wp, m_dev, mu, n, k, 1, nullptr, nullptr, (size_t)n, rs);
+  return launch_rows<3, 4>(s, 1, A, Wp, m_dev, mu, n, k, 1, nullptr, nullptr, (size_t)n, rs);
+}
+// gate|up: 48 gate columns and their 48 up columns
+int slk_wavek_swiglu_ok(int mu, int dff, int k) { return dff > 0 && wavek_fits(mu, 2 * dff, k, 1, sl_cdiv(dff, 48)); }
+int slk_wavek_swiglu(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int dff, int k, void* a) {
+  if (!slk_wavek_swiglu_ok(mu, dff, k)) return SL_EINVAL;
+  return launch_rows<2, 6>(s, 1, A, Wp, m_dev, mu, 2 * dff, k, 1, nullptr, a, (size_t)dff);
+}
+// Out and down: 64 columns, k in four splits; the number of planes, 0 if these launches do not take the shape.  (Two row tiles
+// of 128 columns: the same from 128 rows on, slower below.)
+int slk_wavek_splits(int mu, int n, int k) { return wavek_fits(mu, n, k, 4, 4 * sl_cdiv(n, 64)) ? 4 : 0; }
+int slk_wavek_planes(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int n, int k, float* Cf) {
+  const int splits = slk_wavek_splits(mu, n, k);
+  if (!splits || !Cf || (uintptr_t)Cf % 16) return SL_EINVAL;
+  return launch_rows<0, 4>(s, 1, A, Wp, m_dev, mu, n, k, splits, Cf, nullptr, (size_t)n);
+}

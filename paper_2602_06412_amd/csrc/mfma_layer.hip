@@ -2,6 +2,8 @@
 // in which order, on which buffers.  Host code only.
 #include "sl_common.h"
 
+#include <algorithm>
+
 bool sl_mfma_supported(const sl_config* c) {
   const int hd = c->n_heads * c->d_head;
   return c->dtype == SL_BF16 && c->d_head == 128 && c->d_model % 64 == 0 && c->d_ff % 64 == 0 && hd % 64 == 0 &&
@@ -69,6 +71,7 @@ size_t sl_mfma_f32_elems(const sl_config* c, int rows) {
         const int Sg = slk_gemm_splits_gate_up(mu, sh[0], sh[1]);
         S = Sg > S ? Sg : S;
       }
+      S = std::max(S, slk_wavek_splits(mu, sh[0], sh[1]));
       const size_t e = (size_t)S * mu * sh[0];
       if (e > best) best = e;
     }
@@ -90,7 +93,10 @@ int sl_mfma_layer(sl_ctx* ctx, hipStream_t s, int l, void* x, void* h, void* q, 
   const sl_layer_weights& L = ctx->layers[l];
   void* kc_w = ctx->probe_read_only ? nullptr : kv_k(ctx, l);      // read-only probe: queries only
   void* vc_w = ctx->probe_read_only ? nullptr : kv_v(ctx, l);
-  if (H % 2 == 0 && slk_gemm_unsplit_thick(mu, 3 * hd, d)) {
+  if (slk_wavek_qkv_ok(mu, H, d)) {
+    SL_RUN(ctx, s, SL_PROF_GEMM_QKV, slk_wavek_qkv_rope(s, h, P.wqkv, m_dev, mu, H, d, active_idx, ctx->n_seq, ctx->n_pad, ctx->kv, q,
+                                                      kc_w, vc_w));
+  } else if (H % 2 == 0 && slk_gemm_unsplit_thick(mu, 3 * hd, d)) {
     // thick launches: Q | K | V projection, RoPE and the scatter into q and the caches in one kernel
     SL_RUN(ctx, s, SL_PROF_GEMM_QKV, slk_gemm_mfma256_qkv_rope(s, h, P.wqkv, m_dev, mu, H, d, active_idx, ctx->n_seq, ctx->n_pad,
                                                              ctx->kv, q, kc_w, vc_w));
@@ -103,8 +109,11 @@ int sl_mfma_layer(sl_ctx* ctx, hipStream_t s, int l, void* x, void* h, void* q, 
   }
   SL_RUN(ctx, s, SL_PROF_ATTENTION, slk_attention_mfma(s, q, kv_k(ctx, l), kv_v(ctx, l), active_idx, m_dev, mu, ctx->batch, H, ctx->n_seq,
                             ctx->n_pad, o, attn_scratch));
-  int S = 1;
-  if (slk_gemm_unsplit_thick(mu, d, hd)) {
+  int S = slk_wavek_splits(mu, d, hd);
+  if (S) {
+    SL_RUN(ctx, s, SL_PROF_GEMM_OUT, slk_wavek_planes(s, o, P.wo, m_dev, mu, d, hd, f32));
+    SL_RUN(ctx, s, SL_PROF_ADD_NORM, slk_add_rmsnorm(s, SL_BF16, x, f32, S, (size_t)mu * d, m_dev, mu, d, L.ffn_norm, c.rms_eps, h, 1));
+  } else if (slk_gemm_unsplit_thick(mu, d, hd)) {
     // thick launches: the residual add runs in the projection's epilogue, the norm reads the new x
     SL_RUN(ctx, s, SL_PROF_GEMM_OUT, slk_gemm_mfma256_residual(s, o, P.wo, m_dev, mu, d, hd, x));
     SL_RUN(ctx, s, SL_PROF_ADD_NORM, slk_rmsnorm(s, SL_BF16, x, nullptr, m_dev, mu, d, L.ffn_norm, c.rms_eps, h, 1));
@@ -113,7 +122,9 @@ int sl_mfma_layer(sl_ctx* ctx, hipStream_t s, int l, void* x, void* h, void* q, 
     SL_RUN(ctx, s, SL_PROF_GEMM_OUT, slk_gemm_mfma(s, o, 1, P.wo, m_dev, mu, d, hd, S, f32, nullptr, nullptr, d));
     SL_RUN(ctx, s, SL_PROF_ADD_NORM, slk_add_rmsnorm(s, SL_BF16, x, f32, S, (size_t)mu * d, m_dev, mu, d, L.ffn_norm, c.rms_eps, h, 1));
   }
-  if (slk_gemm_unsplit_thick(mu, 2 * dff, d)) {
+  if (slk_wavek_swiglu_ok(mu, dff, d)) {
+    SL_RUN(ctx, s, SL_PROF_GEMM_GATE_UP, slk_wavek_swiglu(s, h, P.wgu, m_dev, mu, dff, d, a));
+  } else if (slk_gemm_unsplit_thick(mu, 2 * dff, d)) {
     SL_RUN(ctx, s, SL_PROF_GEMM_GATE_UP, slk_gemm_mfma256_swiglu(s, h, P.wgu, m_dev, mu, dff, d, a));
   } else if (slk_gemm_stream_swiglu_ok(mu, dff, d)) {
     // thin launches whose gate|up projection runs unsplit: SwiGLU in the weight-stream kernel's epilogue
@@ -123,7 +134,11 @@ int sl_mfma_layer(sl_ctx* ctx, hipStream_t s, int l, void* x, void* h, void* q, 
     SL_RUN(ctx, s, SL_PROF_GEMM_GATE_UP, slk_gemm_mfma(s, h, 1, P.wgu, m_dev, mu, 2 * dff, d, S, f32, nullptr, nullptr, 2 * (size_t)dff));
     SL_RUN(ctx, s, SL_PROF_SWIGLU, slk_swiglu(s, f32, S, (size_t)mu * 2 * dff, m_dev, mu, dff, a));
   }
-  if (slk_gemm_unsplit_thick(mu, d, dff)) {
+  S = slk_wavek_splits(mu, d, dff);
+  if (S) {
+    SL_RUN(ctx, s, SL_PROF_GEMM_DOWN, slk_wavek_planes(s, a, P.wdown, m_dev, mu, d, dff, f32));
+    SL_RUN(ctx, s, SL_PROF_ADD_NORM, slk_add_rmsnorm(s, SL_BF16, x, f32, S, (size_t)mu * d, m_dev, mu, d, next_gain, c.rms_eps, h, 1));
+  } else if (slk_gemm_unsplit_thick(mu, d, dff)) {
     SL_RUN(ctx, s, SL_PROF_GEMM_DOWN, slk_gemm_mfma256_residual(s, a, P.wdown, m_dev, mu, d, dff, x));
     SL_RUN(ctx, s, SL_PROF_ADD_NORM, slk_rmsnorm(s, SL_BF16, x, nullptr, m_dev, mu, d, next_gain, c.rms_eps, h, 1));
   } else {

@@ -318,6 +318,15 @@ int slk_gemm_mfma(hipStream_t s, const void* A, int a_tiled, const void* Wp, con
                   int splits, float* Cf, void* Cb, const int32_t* row_map, size_t ldc);
 int slk_gemm_mfma256(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n,
                      int k, int splits, float* Cf, void* Cb, const int32_t* row_map, size_t ldc);
+// gemm_wavek.hip: the layer's projections of at most 256 rows (fragment-tiled activations); *_ok / splits: whether, and with how
+// many fp32 planes, a launch of that shape is taken
+int slk_wavek_qkv_ok(int mu, int H, int k);
+int slk_wavek_qkv_rope(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int H, int k,
+                       const int32_t* active_idx, int N, int n_pad, const void* rope_tab, void* q, void* kc, void* vc);
+int slk_wavek_swiglu_ok(int mu, int dff, int k);
+int slk_wavek_swiglu(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int dff, int k, void* a);
+int slk_wavek_splits(int mu, int n, int k);
+int slk_wavek_planes(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int n, int k, float* Cf);
 // attention_mfma.hip
 int slk_attention_mfma(hipStream_t s, const void* q, const void* kc, const void* vc, const int32_t* active_idx,
                        const int32_t* m_dev, int m_upper, int B, int H, int N, int n_pad, void* o, float* scratch);
