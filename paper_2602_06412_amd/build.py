@@ -23,7 +23,7 @@ FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Xclang", "-tar
 
 # Kernels whose correctness rests on registers the compiler must not spill or copy (operand rings filled by
 # inline-assembly loads and waited for with hand-counted vmcnt): any scratch use fails the build.
-NO_SCRATCH = ("gemm_stream_kernel", "gemm_mfma256_kernel", "gemm_wavek_kernel")
+NO_SCRATCH = ("gemm_stream_kernel", "gemm_mfma256_kernel", "gemm_wavek_kernel", "gemm_wave22_kernel")
 
 
 def _resource_report(out):

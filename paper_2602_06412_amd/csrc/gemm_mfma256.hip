@@ -1,4 +1,4 @@
-// The projection GEMM of launches bounded by more than 32 rows (inside a layer more than 256, where gemm_wavek.hip takes
+// The projection GEMM of launches bounded by more than 32 rows (inside a layer more than 512, where gemm_wavek.hip takes
 // the shape): one TM x 256 output tile per workgroup and CU, TM any multiple of 32 from 64 to 256.  Four waves, one per SIMD; each owns all TM rows of 64 columns (up to 256
 // accumulator registers), so a weight fragment is wanted by exactly one wave.
 //

@@ -1,5 +1,5 @@
-// The layer's projections of at most 256 rows: one workgroup per column slice takes ALL rows, its four waves a quarter of
-// the reduction each.
+// The layer's projections of at most 512 rows.  Up to 256 rows one workgroup per column slice takes ALL rows, its four waves a
+// quarter of the reduction each; above, see the second kernel.
 //
 // What bounds these launches is the number of 128-byte lines a CU has under way: about 256 of them, whatever the depth of
 // the rings, so a line that misses L2 (625 ns) moves at 52 GB/s per CU, one that hits at 125, a mixture at 45 to 68.  A tile
@@ -215,7 +215,8 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
 
   // the waves' sums meet in LDS: of the row blocks 4 p .. 4 p + 3 wave w keeps block 4 p + w and hands the others over
   int seq[PASSES];
-  float4 tab[OUT == 3 ? PASSES : 1][HB][2];
+  constexpr bool EARLY = NA <= 8;                     // all of a lane's table rows at once, where registers are free
+  float4 tab[EARLY ? PASSES : 1][HB][2];
   if constexpr (OUT == 3) {
     if (rs.kc == nullptr && tn * HB >= 4 * rs.H) return;         // queries only (uniform over the workgroup)
 #pragma unroll
@@ -223,8 +224,10 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
       const int row = m0 + (p * 4 + wave) * 16 + row_in;
       seq[p] = gid[p] / rs.N;
       gid[p] = row < M && p * 4 + wave < NA ? gid[p] - seq[p] * rs.N : -1;       // the slot
+      if constexpr (EARLY) {
 #pragma unroll
-      for (int b = 0; b < HB; ++b) rope_load_unit(tab[p][b], max(gid[p], 0), (tn * HB + b & 3) * 16, rs);
+        for (int b = 0; b < HB; ++b) rope_load_unit(tab[p][b], max(gid[p], 0), (tn * HB + b & 3) * 16, rs);
+      }
     }
   }
   __syncthreads();                                    // every wave is done with its ring
@@ -281,12 +284,16 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
         if (row < M && col < (n >> 1)) *reinterpret_cast<bf16x4*>(Cb + afrag_index(row, col, (int)ldc)) = v;
       }
     } else {
+      if constexpr (!EARLY) {
+#pragma unroll
+        for (int b = 0; b < HB; ++b) rope_load_unit(tab[0][b], max(gid[p], 0), (tn * HB + b & 3) * 16, rs);
+      }
 #pragma unroll
       for (int b = 0; b < HB; ++b) {
         const int u = tn * HB + b, hsec = u >> 2, sec = hsec / rs.H, head = hsec - sec * rs.H, j0 = (u & 3) * 16;
         if (sec > 2 || (sec > 0 && rs.kc == nullptr)) continue;
         if (sec < 2) {
-          if (gid[p] >= 0) rope_store_unit(c[b], c[b + HB], tab[p][b], sec, head, j0, row, seq[p], gid[p], rs);
+          if (gid[p] >= 0) rope_store_unit(c[b], c[b + HB], tab[EARLY ? p : 0][b], sec, head, j0, row, seq[p], gid[p], rs);
         } else {
           v_store_unit(stage, c[b], c[b + HB], head, j0, seq[p], gid[p], rs);
         }
@@ -316,30 +323,260 @@ static int launch_rows(hipStream_t s, int tiles_m, const void* A, const void* Wp
   const int na = sl_cdiv(mu, 16 * tiles_m);
 #define GO(NA) if (na <= NA) return launch_wavek<OUT, NA, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc, rs)
   if constexpr (NBK == 4 || OUT == 2) { GO(1); GO(2); GO(3); }
-  GO(4); GO(5); GO(6); GO(7); GO(8);
-  if constexpr (NBK == 4 || OUT == 2) { GO(10); GO(12); GO(14); GO(16); }
+  GO(4); GO(5); GO(6); GO(7); GO(8); GO(10); GO(12); GO(14); GO(16);
 #undef GO
   return SL_EINVAL;
 }
 
+// ---- 2 x 2 waves ------------------------------------------------------------------------------------------------
+// 257 to 512 rows: two row tiles, and with them twice as wide column slices, are too many sums for one wave.  TM = 16 NA rows x
+// 32 NBK columns per workgroup: wave w takes the k-tiles 2 s + w / 2 and the half w % 2 of the columns.  The two waves of a
+// k-tile share its activations, each fetching half of the fragments, so a step ends in a barrier; it stands R row blocks before
+// the last MFMAs, which cover it and the first LDS reads of the next step.  256 x 192 tiles of the gate|up projection fill 256
+// CUs where 256 x 256 left 64 idle: 512 rows 92 -> 82 us (loop 1970 cycles a step of 1536 MFMA cycles with weights from HBM, 1770
+// from the memory-side cache: the lines under way again, 28 bytes per cycle).
+template <int OUT, int NA, int NBK> struct W22Cfg {
+  static_assert(NA % 2 == 0, "the waves of a k-tile fetch half of its activation fragments each");
+  static constexpr int RD = 3;                        // steps in the rings: one in use, two under way
+  static constexpr int P = NBK + NA / 2;              // loads per wave and step, weights first
+  static constexpr int R = NA % 4 == 0 ? 4 : NA % 5 == 0 ? 5 : 7;       // activation fragments read ahead
+  static constexpr int BAR = NA - R;                  // row block before which the next step is published
+  static constexpr int LATE = BAR * P / NA;           // loads of a step issued before that
+  static constexpr int RING = 2 * RD * NA * 1024;
+  static constexpr int PASS = 4 * 2 * NBK * 1024;     // exchange: 2 row blocks per wave and pass
+  static constexpr int LDS = RING > 2 * PASS ? RING : 2 * PASS;
+  static_assert(NA % R == 0 && P <= 63 && LDS <= 160 * 1024, "schedule");
+};
+
+template <int OUT, int NA, int NBK>
+__global__ __launch_bounds__(256, 1) void gemm_wave22_kernel(
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp, int n, int k, int splits, const int32_t* __restrict__ m_dev,
+    int m_upper, float* __restrict__ Cf, bf16_t* __restrict__ Cb, size_t ldc, int tiles_m, int tiles_n) {
+  typedef W22Cfg<OUT, NA, NBK> WC;
+  constexpr int RD = WC::RD, P = WC::P, R = WC::R, HB = NBK / 2, TM = NA * 16;
+  extern __shared__ Frag lds[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int kg = wave >> 1, cg = wave & 1;
+  const int g4 = lane >> 4, row_in = lane & 15;
+  // XCD x owns the column tiles 8 c + x; the row tiles and splits of one column tile follow each other
+  int tm, tn, split;
+  {
+    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+    tm = j % tiles_m;
+    split = j / tiles_m % splits;
+    tn = j / (tiles_m * splits) * 8 + xcd;
+  }
+  if (tn >= tiles_n) return;
+  const int M = min(*m_dev, m_upper), m0 = tm * TM;
+  if (m0 >= M) return;
+  const int k_split = k / splits, steps = k_split / 64;
+  const int K16 = k / 16, NF = n / 16;
+  auto col_block = [&](int b) {
+    const int t = (tn * 2 + cg) * HB + b % HB;
+    if constexpr (OUT == 2) return (t >> 1) * 4 + (t & 1) + (b / HB) * 2;
+    else return (tn * 2 + cg) * NBK + b;
+  };
+  const uint32_t lane_off = ((uint32_t)(g4 >> 1) * 64u + (uint32_t)((g4 & 1) * 32 + row_in)) * 16u;
+  uint32_t b_voff[NBK];
+#pragma unroll
+  for (int b = 0; b < NBK; ++b) {
+    const int f = min(col_block(b), NF - 1);
+    b_voff[b] = (uint32_t)(f >> 1) * (uint32_t)K16 * 1024u + (uint32_t)(f & 1) * 256u + lane_off;
+  }
+  const int n_mb = (m_upper + 31) / 32;
+  uint32_t a_voff[NA / 2];                            // row blocks 2 i + cg
+#pragma unroll
+  for (int i = 0; i < NA / 2; ++i) a_voff[i] = (uint32_t)min(m0 / 32 + i, n_mb - 1) * (uint32_t)K16 * 1024u + (uint32_t)cg * 256u + lane_off;
+  const uint32_t k_off = ((uint32_t)(split * k_split) / 16u + (uint32_t)kg * 2u) * 1024u;
+  uint64_t pa = (uint64_t)(uintptr_t)A + k_off, pb = (uint64_t)(uintptr_t)Wp + k_off;
+
+  const uint32_t ring = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) Frag*)lds + (uint32_t)(kg * (RD * NA) + cg) * 1024u);
+  typedef const __attribute__((address_space(3))) Frag LFrag;
+  LFrag* ring_l = (LFrag*)lds + kg * (RD * NA * 64) + lane;
+  asm volatile("" : "+v"(ring_l));
+  auto a_frag = [&](int slot, int a) -> Frag { return ring_l[(slot * NA + a) * 64]; };
+  Frag fb[RD][NBK];
+#pragma unroll
+  for (int u = 0; u < RD; ++u)
+#pragma unroll
+    for (int b = 0; b < NBK; ++b) fb[u][b] = Frag{};
+  // load i of a step into slot `slot`: the weights, then this wave's half of the activations
+  auto fetch = [&](int slot, int i) {
+    if (i < NBK) {
+      asm volatile("global_load_dwordx4 %0, %1, %2 nt" : "+v"(fb[slot][i]) : "v"(b_voff[i]), "s"(pb) : "memory");
+    } else {
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(ring + (uint32_t)((slot * NA + 2 * (i - NBK)) * 1024)),
+                   "v"(a_voff[i - NBK]), "s"(pa) : "memory", "m0");
+    }
+  };
+  int fetched = 0;
+  auto next = [&] {                                   // past the end the last step again (never used)
+    const uint32_t d = fetched < steps - 1 ? 4096u : 0u;
+    pa += d;
+    pb += d;
+    ++fetched;
+  };
+  f32x4 acc[NA][NBK];
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int b = 0; b < NBK; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto mma = [&](const Frag& w, const Frag& x, int a, int b) {
+    if (a * NBK + b < 64) asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[a][b]) : "v"(w), "v"(x));
+    else asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[a][b]) : "v"(w), "v"(x));
+  };
+  auto pin = [&](int a, int b) {
+    if (a * NBK + b < 64) asm volatile("" : "+a"(acc[a][b]));
+    else asm volatile("" : "+v"(acc[a][b]));
+  };
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+#pragma unroll
+    for (int i = 0; i < P; ++i) fetch(u, i);
+    next();
+  }
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int b = 0; b < NBK; ++b) pin(a, b);
+  Frag af[R];
+  wk_landed<P>(fb[0]);
+  asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+  for (int a = 0; a < R; ++a) af[a] = a_frag(0, a);
+  asm volatile("s_nop 7" ::: "memory");
+
+  for (int s = 0; s < steps; s += RD) {
+#pragma unroll
+    for (int u = 0; u < RD; ++u) {
+      if (u > 0 && s + u >= steps) break;
+      const int nu = (u + 1) % RD, fu = (u + 2) % RD;
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        if (a == WC::BAR) {
+          // every wave has read the last of this step, and its own loads of the next one have landed
+          wk_landed<WC::LATE>(fb[nu]);
+          asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int b = 0; b < NBK; ++b) mma(fb[u][b], af[a % R], a, b);
+        af[a % R] = a + R < NA ? a_frag(u, a + R) : a_frag(nu, a + R - NA);
+#pragma unroll
+        for (int i = a * P / NA; i < (a + 1) * P / NA; ++i) fetch(fu, i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      next();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < RD; ++u) wk_landed<0>(fb[u]);
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int b = 0; b < NBK; ++b) pin(a, b);
+
+  // the two k-tiles' sums meet in LDS: of the row blocks 4 p .. 4 p + 3 the wave keeps those with a / 2 % 2 == kg
+  __syncthreads();
+  constexpr int PASSES = (NA + 3) / 4;
+#pragma unroll
+  for (int p = 0; p < PASSES; ++p) {
+    f32x4* exch = reinterpret_cast<f32x4*>(lds) + (p & 1) * (WC::PASS / 16);          // [cg][to kg][2][NBK][64]
+    f32x4 c[2][NBK];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int a = p * 4 + j;
+      if (a >= NA) continue;
+#pragma unroll
+      for (int b = 0; b < NBK; ++b) pin(a, b);
+      if (j >> 1 == kg) {
+#pragma unroll
+        for (int b = 0; b < NBK; ++b) c[j & 1][b] = acc[a][b];
+      } else {
+        f32x4* e = exch + ((cg * 2 + (j >> 1)) * 2 + (j & 1)) * NBK * 64 + lane;
+#pragma unroll
+        for (int b = 0; b < NBK; ++b) e[b * 64] = acc[a][b];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int a = p * 4 + kg * 2 + h, row = m0 + a * 16 + row_in;
+      if (a >= NA || m0 + a * 16 >= M) continue;
+#pragma unroll
+      for (int b = 0; b < NBK; ++b) c[h][b] += exch[(((cg * 2 + kg) * 2 + h) * NBK + b) * 64 + lane];
+      if constexpr (OUT == 0) {
+#pragma unroll
+        for (int b = 0; b < NBK; ++b) {
+          const int col = ((tn * 2 + cg) * NBK + b) * 16 + 4 * g4;
+          if (row < M && col < n) *reinterpret_cast<f32x4*>(Cf + ((size_t)split * m_upper + row) * ldc + col) = c[h][b];
+        }
+      } else if constexpr (OUT == 2) {
+#pragma unroll
+        for (int b = 0; b < HB; ++b) {
+          const int col = ((tn * 2 + cg) * HB + b) * 16 + 4 * g4;
+          bf16x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = (bf16_t)silu_mul(c[h][b][e], c[h][b + HB][e]);
+          if (row < M && col < (n >> 1)) *reinterpret_cast<bf16x4*>(Cb + afrag_index(row, col, (int)ldc)) = v;
+        }
+      }
+    }
+  }
+}
+
+template <int OUT, int NA, int NBK>
+static int launch_wave22(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int n, int k, int splits,
+                         float* Cf, void* Cb, size_t ldc) {
+  const size_t sh = W22Cfg<OUT, NA, NBK>::LDS;
+  auto kern = gemm_wave22_kernel<OUT, NA, NBK>;
+  static unsigned long long lds_ok = 0;
+  SL_ALLOW_DYNAMIC_LDS(lds_ok, kern, sh);
+  const int tiles_m = sl_cdiv(mu, NA * 16), tiles_n = sl_cdiv(n, 32 * NBK);
+  hipLaunchKernelGGL(kern, dim3(8 * sl_cdiv(tiles_n, 8) * tiles_m * splits), dim3(256), sh, s, (const bf16_t*)A, (const bf16_t*)Wp, n, k,
+                     splits, m_dev, mu, Cf, (bf16_t*)Cb, ldc, tiles_m, tiles_n);
+  SL_LAUNCH_CHECK();
+  return SL_OK;
+}
+template <int OUT, int NBK>
+static int launch22_rows(hipStream_t s, int tm, const void* A, const void* Wp, const int32_t* m_dev, int mu, int n, int k, int splits,
+                    float* Cf, void* Cb, size_t ldc) {
+  switch (tm) {
+    case 128: return launch_wave22<OUT, 8, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc);
+    case 160: return launch_wave22<OUT, 10, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc);
+    case 192: return launch_wave22<OUT, 12, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc);
+    case 224: return launch_wave22<OUT, 14, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc);
+    case 256: return launch_wave22<OUT, 16, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc);
+  }
+  return SL_EINVAL;
+}
+
 // ---- which launches ---------------------------------------------------------------------------------------------
-// At most 256 rows, whole trips of the rings, 32-bit offsets; and a single round of workgroups that fills most of the chip:
-// the slices are as narrow as the epilogues allow, so fewer than 160 of them leave too many CUs idle (the other kernels then
-// choose their own tiles), and a second round would read the activations again.  Measured at the LLaDA-8B shapes, one block at
-// N = 512, us before -> with these launches (before: the weight-stream kernel up to 32 rows, the ring kernel, and the RoPE
-// and SwiGLU kernels behind them): 16 rows 110 -> 98, 48 rows 134 -> 109, 64 rows 143 -> 118, 128 rows 163 -> 149,
-// 224 rows 204 -> 187, 256 rows 210 -> 195.
-constexpr int kWavekRows = 256;
-static bool wavek_fits(int mu, int n, int k, int splits, int workgroups) {
-  return mu > 0 && mu <= kWavekRows && n % 32 == 0 && k % (WK_STEP * 4 * splits) == 0 && (size_t)n * k * 2 < ((size_t)1 << 32) &&
+// Whole trips of the rings, 32-bit offsets; and a single round of workgroups that fills most of the chip: the slices are as
+// narrow as the epilogues allow, so fewer than 160 of them leave too many CUs idle (the other kernels then choose their own
+// tiles), and a second round would read the activations again.  Measured at the LLaDA-8B shapes, one block at N = 512, us
+// before -> with these launches (before: the weight-stream kernel up to 32 rows, the ring kernel, and the RoPE and SwiGLU
+// kernels behind them): 16 rows 110 -> 99, 48 rows 134 -> 109, 64 rows 143 -> 120, 128 rows 163 -> 149, 224 rows 204 -> 187,
+// 256 rows 210 -> 195, 320 rows 240 -> 217, 400 rows 265 -> 239, 512 rows 280 -> 258.
+static bool fits(int mu, int n, int k, int k_unit, int workgroups) {
+  return mu > 0 && n > 0 && n % 32 == 0 && k % k_unit == 0 && (size_t)n * k * 2 < ((size_t)1 << 32) &&
          sl_align_up(mu, 32) * k * 2 < ((size_t)1 << 32) && workgroups >= 160 && workgroups <= 256;
 }
-// Q|K|V: 64 columns (two units of 16 + 16 that RoPE pairs) for all rows; from 97 rows on 96 columns for half of the rows
-// each, where (rows / 2 + 96) is less to read than (rows + 64) and 256 CUs share the work instead of 192 (128 rows 39.5 -> 35.5
-// us, 256 rows 54 -> 45; 80 rows 32.5 -> 32.7, 64 rows 29.5 -> 32.5).
-static int qkv_row_tiles(int mu, int H) { return mu > 96 && 8 * H <= 256 ? 2 : 1; }
+constexpr int kWavekTrip = 4 * WK_STEP;               // k of a whole trip of the deepest ring
+constexpr int kPlanes = 4;
+
+// Q|K|V: up to 96 rows 64 columns (two units of 16 + 16 that RoPE pairs) for all rows; from 97 rows on 96 columns for half of the
+// rows each, where (rows / 2 + 96) is less to read than (rows + 64) and 256 CUs share the work instead of 192 (128 rows 39.5 ->
+// 35.5 us, 256 rows 54 -> 45; 80 rows 32.5 -> 32.7, 64 rows 29.5 -> 32.5).  Up to 384 rows: there 55 us against 62 of the
+// ring kernel's k-split with RoPE behind it, at 400 rows 60 against 59 of its fused form.
+constexpr int kWavekQkvRows = 384;
+static int qkv_row_tiles(int mu) { return mu > 96 ? 2 : 1; }
 int slk_wavek_qkv_ok(int mu, int H, int k) {
-  return H > 0 && wavek_fits(mu, 3 * H * 128, k, 1, qkv_row_tiles(mu, H) == 2 ? 8 * H : 6 * H);
+  return mu <= kWavekQkvRows && H > 0 && fits(mu, 3 * H * 128, k, kWavekTrip, qkv_row_tiles(mu) == 2 ? 8 * H : 6 * H);
 }
 int slk_wavek_qkv_rope(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int H, int k,
                        const int32_t* active_idx, int N, int n_pad, const void* rope_tab, void* q, void* kc, void* vc) {
@@ -347,20 +584,35 @@ int slk_wavek_qkv_rope(hipStream_t s, const void* A, const void* Wp, const int32
   if (!slk_wavek_qkv_ok(mu, H, k) || !active_idx || !rope_tab || !q || (kc == nullptr) != (vc == nullptr)) return SL_EINVAL;
   if ((uintptr_t)q % 16 || (uintptr_t)kc % 16 || (uintptr_t)vc % 16 || (uintptr_t)rope_tab % 16) return SL_EINVAL;
   const RopeScatter rs{active_idx, (const float2*)rope_tab, (bf16_t*)q, (bf16_t*)kc, (bf16_t*)vc, N, n_pad, H};
-  if (qkv_row_tiles(mu, H) == 2) return launch_rows<3, 6>(s, 2, A, Wp, m_dev, mu, n, k, 1, nullptr, nullptr, (size_t)n, rs);
+  if (qkv_row_tiles(mu) == 2) return launch_rows<3, 6>(s, 2, A, Wp, m_dev, mu, n, k, 1, nullptr, nullptr, (size_t)n, rs);
   return launch_rows<3, 4>(s, 1, A, Wp, m_dev, mu, n, k, 1, nullptr, nullptr, (size_t)n, rs);
 }
-// gate|up: 48 gate columns and their 48 up columns
-int slk_wavek_swiglu_ok(int mu, int dff, int k) { return dff > 0 && wavek_fits(mu, 2 * dff, k, 1, sl_cdiv(dff, 48)); }
+
+// gate|up: up to 256 rows 48 gate columns and their 48 up columns per workgroup, up to 512 rows 96 + 96 with two row tiles.
+// Four row tiles only where they are full: 992 rows 166 -> 153 us, 960 rows 145 -> 153, 857 rows 143.5 -> 143, 800 rows 124 -> 143
+// (the ring kernel's shorter tiles); three are a round and a half (700 rows 119 -> 146).
+static int wave22_tile_rows(int mu) { return (int)sl_align_up(sl_cdiv(mu, sl_cdiv(mu, 256)), 32); }
+int slk_wavek_swiglu_ok(int mu, int dff, int k) {
+  if (mu <= 256) return fits(mu, 2 * dff, k, kWavekTrip, sl_cdiv(dff, 48));
+  if (mu <= 512) return fits(mu, 2 * dff, k, 64, 2 * sl_cdiv(dff, 96));
+  const int two_rounds = 4 * sl_cdiv(dff, 96);
+  return mu > 960 && mu <= 1024 && two_rounds > 448 && fits(mu, 2 * dff, k, 64, two_rounds / 2);
+}
 int slk_wavek_swiglu(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int dff, int k, void* a) {
   if (!slk_wavek_swiglu_ok(mu, dff, k)) return SL_EINVAL;
-  return launch_rows<2, 6>(s, 1, A, Wp, m_dev, mu, 2 * dff, k, 1, nullptr, a, (size_t)dff);
+  if (mu <= 256) return launch_rows<2, 6>(s, 1, A, Wp, m_dev, mu, 2 * dff, k, 1, nullptr, a, (size_t)dff);
+  return launch22_rows<2, 6>(s, wave22_tile_rows(mu), A, Wp, m_dev, mu, 2 * dff, k, 1, nullptr, a, (size_t)dff);
 }
-// Out and down: 64 columns, k in four splits; the number of planes, 0 if these launches do not take the shape.  (Two row tiles
-// of 128 columns: the same from 128 rows on, slower below.)
-int slk_wavek_splits(int mu, int n, int k) { return wavek_fits(mu, n, k, 4, 4 * sl_cdiv(n, 64)) ? 4 : 0; }
+
+// Out and down, k in four splits: up to 256 rows 64 columns for all rows, up to 512 rows 128 columns and two row tiles (512 rows
+// down 56.5 -> 50 us, 264 rows 46.5 -> 41).  The number of planes, 0 if these launches do not take the shape.  (Two row tiles of
+// 128 columns with the waves along k: the same from 128 rows on, slower below.)
+int slk_wavek_splits(int mu, int n, int k) {
+  if (mu <= 256) return fits(mu, n, k, kPlanes * kWavekTrip, kPlanes * sl_cdiv(n, 64)) ? kPlanes : 0;
+  return mu <= 512 && fits(mu, n, k, kPlanes * 64, 2 * kPlanes * sl_cdiv(n, 128)) ? kPlanes : 0;
+}
 int slk_wavek_planes(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int n, int k, float* Cf) {
-  const int splits = slk_wavek_splits(mu, n, k);
-  if (!splits || !Cf || (uintptr_t)Cf % 16) return SL_EINVAL;
-  return launch_rows<0, 4>(s, 1, A, Wp, m_dev, mu, n, k, splits, Cf, nullptr, (size_t)n);
+  if (!slk_wavek_splits(mu, n, k) || !Cf || (uintptr_t)Cf % 16) return SL_EINVAL;
+  if (mu <= 256) return launch_rows<0, 4>(s, 1, A, Wp, m_dev, mu, n, k, kPlanes, Cf, nullptr, (size_t)n);
+  return launch22_rows<0, 4>(s, wave22_tile_rows(mu), A, Wp, m_dev, mu, n, k, kPlanes, Cf, nullptr, (size_t)n);
 }

@@ -318,7 +318,7 @@ int slk_gemm_mfma(hipStream_t s, const void* A, int a_tiled, const void* Wp, con
                   int splits, float* Cf, void* Cb, const int32_t* row_map, size_t ldc);
 int slk_gemm_mfma256(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n,
                      int k, int splits, float* Cf, void* Cb, const int32_t* row_map, size_t ldc);
-// gemm_wavek.hip: the layer's projections of at most 256 rows (fragment-tiled activations); *_ok / splits: whether, and with how
+// gemm_wavek.hip: the layer's projections of few rows (fragment-tiled activations); *_ok / splits: whether, and with how
 // many fp32 planes, a launch of that shape is taken
 int slk_wavek_qkv_ok(int mu, int H, int k);
 int slk_wavek_qkv_rope(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int H, int k,

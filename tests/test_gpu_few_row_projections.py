@@ -1,4 +1,4 @@
-"""The projections of at most 256 rows whose waves split the reduction (shapes that give 160 to 256 column slices): every
+"""The projections of at most 512 rows whose waves split the reduction (shapes that give 160 to 256 workgroups): every
 epilogue against the oracle at the edges of the row blocks, of the passes of 64 rows and of the two-row-tile form (97 rows on),
 with rows anywhere, whole aligned blocks of sixteen slots, a ragged last column slice and an odd number of heads."""
 import numpy as np
@@ -30,14 +30,23 @@ OUT_DOWN = wl.Shape("few-rows-planes", 1, 2688, 16, 128, 2048, 1056, "bf16")
     (2, 128, [128, 128]),
     (3, 120, [103, 1, 120]),
     (1, 300, [256]),
+    (1, 300, [257]),            # gate|up: two row tiles and 2 x 2 waves
+    (2, 200, [200, 184]),
+    (1, 520, [385]),            # Q|K|V: the ring kernel again
+    (1, 520, [512]),
 ])
 def test_qkv_and_gate_up(batch, N, rows):
     check_layers(QKV_GATE_UP, batch, N, rows)
 
 
-@pytest.mark.parametrize("rows", [[5], [64], [65], [129], [225], [256]])
+@pytest.mark.parametrize("rows", [[961], [1024]])
+def test_gate_up_in_two_full_rounds(rows):
+    check_layers(wl.Shape("few-rows-wide", 1, 256, 2, 128, 11008, 1056, "bf16"), 1, 1024, rows)
+
+
+@pytest.mark.parametrize("rows", [[5], [64], [65], [129], [225], [256], [257], [321], [390], [449], [512]])
 def test_out_and_down(rows):
-    check_layers(OUT_DOWN, 1, 260, rows)
+    check_layers(OUT_DOWN, 1, 260 if rows[0] <= 256 else 520, rows)
 
 
 def test_device_side_row_count_below_the_bound():
