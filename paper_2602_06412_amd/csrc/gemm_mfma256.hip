@@ -47,7 +47,9 @@ template <int TM> struct TileCfg {
   static constexpr int KT = 2;                      // k-tiles per barrier
   static constexpr int RING = 8;                    // A ring, in k-tiles; also the unroll of the loop
   static constexpr int KA = RING - KT;              // A k-tiles fetched ahead
-  static constexpr int LDS = RING * KTB;
+  // one touch of a wave lands here (never read); only short tiles touch (touches_weights)
+  static constexpr int TOUCH = TM <= 160 ? 256 : 0;
+  static constexpr int LDS = RING * KTB + 4 * TOUCH;
   // fragment registers: R row blocks, read LA ahead (R divides NA: static indices)
   static constexpr int R = NA % 8 == 0 ? 8 : NA % 7 == 0 ? 7 : NA % 6 == 0 ? 6 : NA % 5 == 0 ? 5 : 4;
   static constexpr int LA = R > 6 ? 6 : R - 1;
@@ -78,7 +80,7 @@ __device__ __forceinline__ void ring_tile(
     const bf16_t* __restrict__ A, int a_tiled, const bf16_t* __restrict__ Wp, int n, int k, int k_per_split,
     const int M, int m_upper, float* __restrict__ Cf, bf16_t* __restrict__ Cb,
     const int32_t* __restrict__ row_map, size_t ldc, const int m0, const int tn, long long* __restrict__ probe,
-    const RopeScatter& rs) {
+    const RopeScatter& rs, const int share, const int tm) {
   typedef TileCfg<TM> TC;
   constexpr int NA = TC::NA, NAD = TC::NAD, P = TC::P, DB = TC::DB, KT = TC::KT, RING = TC::RING, KA = TC::KA, KTB = TC::KTB,
                 R = TC::R, LA = TC::LA, BARG = TC::BARG, GAP = TC::GAP;
@@ -185,8 +187,30 @@ __device__ __forceinline__ void ring_tile(
   };
   Frag af[R];
 
+  // Touches (share > 1 row tiles run side by side on one XCD and want the same weights): a lane reads four bytes of a
+  // 128-byte line, a wave the 64 lines of 32 columns and four k-tiles, two such chunks ahead of the loads of the k-tile it is
+  // issued in.  Chunk p's 8 column blocks are dealt over the 4 share waves; t_x counts down to this wave's next one.
+  // They count in vmcnt like any load and make its waits, which ignore them, no looser.
+  const uint32_t t_voff = (uint32_t)lane * 128u;
+  const uint32_t t_lds = lds_base + (uint32_t)(RING * KTB) + (uint32_t)__builtin_amdgcn_readfirstlane(wave) * TC::TOUCH;
+  const int t_blocks = min(8, NF / 2 - n0 / 32);
+  int t_x = __builtin_amdgcn_readfirstlane(wave * share + tm);
+  int t_left = share > 1 ? ktiles / 4 - 1 : 0;      // whole chunks after the first, which the prologue fetches
+  uint64_t pt = pb + 8192u;
+  auto touch = [&] {
+    if (TC::TOUCH == 0 || t_left <= 0) return;
+    if (t_x < t_blocks)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(t_lds), "v"(t_voff),
+                   "s"(pt + (uint64_t)((uint32_t)t_x * (uint32_t)K16) * 1024u) : "memory", "m0");
+    t_x -= 8;
+    if (t_x < 0) t_x += 4 * share;
+    pt += 8192u;
+    --t_left;
+  };
+
   long long pc0 = 0, pw0 = 0, pc1 = 0, pw1 = 0, pc2 = 0, pw2 = 0;
   if (PROBE) { pc0 = clock64(); pw0 = wall_clock64(); }
+  touch();
   // prologue: loads in the order in which the loop would have issued them
 #pragma unroll
   for (int j = 0; j < KA; ++j) {
@@ -222,6 +246,7 @@ __device__ __forceinline__ void ring_tile(
       if (u > 0 && u % 2 == 0 && kt + u >= ktiles) break;
       const int slot_b = u % DB, fetch_b = (u + DB - 1) % DB, fetch_a = (u + KA) % RING, next = (u + 1) % RING;
       const bool publish = u % KT == KT - 1;
+      if (u % 4 == 0) touch();
       b_landed<(DB - 2) * P>(fb[slot_b]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -462,11 +487,12 @@ __global__ __launch_bounds__(256, 1) void gemm_mfma256_kernel(
     const bf16_t* __restrict__ A, int a_tiled, const bf16_t* __restrict__ Wp, int n, int k, int k_per_split,
     const int32_t* __restrict__ m_dev, int m_upper, float* __restrict__ Cf, bf16_t* __restrict__ Cb,
     const int32_t* __restrict__ row_map, size_t ldc, int tiles_m, int tiles_n, TileMap tmap,
-    long long* __restrict__ probe, RopeScatter rs) {
+    long long* __restrict__ probe, RopeScatter rs, int touches) {
   const int M = min(*m_dev, m_upper);
   int tm, tn;
   if (!tile_of_workgroup(tmap, tiles_m, tiles_n, tm, tn) || tm * TM >= M) return;
-  ring_tile<OUT, TM, NT, PROBE>(A, a_tiled, Wp, n, k, k_per_split, M, m_upper, Cf, Cb, row_map, ldc, tm * TM, tn, probe, rs);
+  ring_tile<OUT, TM, NT, PROBE>(A, a_tiled, Wp, n, k, k_per_split, M, m_upper, Cf, Cb, row_map, ldc, tm * TM, tn, probe, rs,
+                             touches ? (M + TM - 1) / TM : 0, tm);
 }
 
 // Workgroup slots a launch takes on the chip's 256 CUs.  Column tiles go to the XCDs in turn, so the XCD with the most of
@@ -486,6 +512,20 @@ static bool stream_weights(int tiles_m, int tiles_n, int splits, int tm) {
   return tm > 160 && tiles_m * tm <= 3072;
 }
 
+// Whether the row tiles of a launch touch each other's weights ahead of their loads.  A CU keeps about 256 lines under way, a
+// line that misses its L2 for 625 ns, one that hits for 250.  In one round of workgroups the R row tiles of a column run side by
+// side on one XCD, ask for a weight line together and all wait for it; with each touching 1/R of the lines a few k-tiles ahead
+// (four bytes a line) all but one find them in L2.  It pays where short tiles wait for lines and many share them.  Weights out of
+// HBM, us without -> with: down of 1024 rows (128 x 8, two splits) 94 -> 81, 2048 rows (160 x 13) 166 -> 150, Out of 857 rows
+// (128 x 7) 36.2 -> 33.6, 1400 rows (96 x 15) 55 -> 47, Q|K|V of 512 rows (128 x 4) 62 -> 58.  Not with few sharers or tall
+// tiles: Q|K|V of 544 rows (128 x 5) 63.5 -> 66, 704 rows (160 x 5) 73 -> 75, 960 rows (192 x 5) 83.5 -> 86, Out of 608 rows (160 x 4)
+// 27.5 -> 28.5, gate|up of 512 rows (256 x 2) 84 -> 92; nor 96-row tiles of four or five, where Q|K|V gains 2 to 4 us at 390 to 430
+// rows and the launches behind it lose them.  The touches carry no non-temporal hint: with it the lines are gone before they
+// are read (Q|K|V of 512 rows 69).
+static bool touches_weights(int tiles_m, int tiles_n, int splits, int tm) {
+  return ring_slots(tiles_m, tiles_n, splits) <= 256 && tm <= 160 && (tiles_m >= 6 || (tm == 128 && tiles_m == 4));
+}
+
 template <int OUT, int TM, bool NT>
 static int launch_ring_hint(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n, int k,
                        int splits, float* Cf, void* Cb, const int32_t* row_map, size_t ldc, const RopeScatter& rs) {
@@ -497,7 +537,8 @@ static int launch_ring_hint(hipStream_t s, const void* A, int a_tiled, const voi
   const TileMap tmap = pick_tile_map(tiles_m, tiles_n);
   dim3 grid(8 * tiles_m * tmap.cn, splits), block(256);
   hipLaunchKernelGGL(kern, grid, block, sh, s, (const bf16_t*)A, a_tiled, (const bf16_t*)Wp, n, k, k / splits, m_dev, mu, Cf,
-                     (bf16_t*)Cb, row_map, ldc, tiles_m, tiles_n, tmap, (long long*)nullptr, rs);
+                     (bf16_t*)Cb, row_map, ldc, tiles_m, tiles_n, tmap, (long long*)nullptr, rs,
+                     touches_weights(tiles_m, tiles_n, splits, TM) ? 1 : 0);
   SL_LAUNCH_CHECK();
   return SL_OK;
 }
@@ -589,7 +630,7 @@ static int launch_probe(hipStream_t s, const void* A, int a_tiled, const void* W
   const TileMap tmap = pick_tile_map(tiles_m, tiles_n);
   dim3 grid(8 * tiles_m * tmap.cn, 1), block(256);
   hipLaunchKernelGGL(kern, grid, block, sh, s, (const bf16_t*)A, a_tiled, (const bf16_t*)Wp, n, k, k, m_dev, mu,
-                     (float*)nullptr, (bf16_t*)Cb, row_map, ldc, tiles_m, tiles_n, tmap, probe, RopeScatter{});
+                     (float*)nullptr, (bf16_t*)Cb, row_map, ldc, tiles_m, tiles_n, tmap, probe, RopeScatter{}, 0);
   SL_LAUNCH_CHECK();
   return SL_OK;
 }

@@ -569,12 +569,12 @@ static bool fits(int mu, int n, int k, int k_unit, int workgroups) {
 constexpr int kWavekTrip = 4 * WK_STEP;               // k of a whole trip of the deepest ring
 constexpr int kPlanes = 4;
 
-// Q|K|V: up to 96 rows 64 columns (two units of 16 + 16 that RoPE pairs) for all rows; from 97 rows on 96 columns for half of the
-// rows each, where (rows / 2 + 96) is less to read than (rows + 64) and 256 CUs share the work instead of 192 (128 rows 39.5 ->
-// 35.5 us, 256 rows 54 -> 45; 80 rows 32.5 -> 32.7, 64 rows 29.5 -> 32.5).  Up to 384 rows: there 55 us against 62 of the
+// Q|K|V: up to 80 rows 64 columns (two units of 16 + 16 that RoPE pairs) for all rows; from 81 rows on 96 columns for half of the
+// rows each, where (rows / 2 + 96) is less to read than (rows + 64) and 256 CUs share the work instead of 192 (96 rows 37.7 ->
+// 35.4 us, 256 rows 56 -> 47; 80 rows 34.8 -> 34.6, 64 rows 29.5 -> 32.5).  Up to 384 rows: there 55 us against 62 of the
 // ring kernel's k-split with RoPE behind it, at 400 rows 60 against 59 of its fused form.
 constexpr int kWavekQkvRows = 384;
-static int qkv_row_tiles(int mu) { return mu > 96 ? 2 : 1; }
+static int qkv_row_tiles(int mu) { return mu > 80 ? 2 : 1; }
 int slk_wavek_qkv_ok(int mu, int H, int k) {
   return mu <= kWavekQkvRows && H > 0 && fits(mu, 3 * H * 128, k, kWavekTrip, qkv_row_tiles(mu) == 2 ? 8 * H : 6 * H);
 }
