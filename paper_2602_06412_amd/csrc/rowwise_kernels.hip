@@ -299,6 +299,73 @@ __global__ __launch_bounds__(kRowThreads) void add_rmsnorm_vec_kernel(const bf16
     }
   }
 }
+// The same for rows of 2049 .. 4096 columns and at most four planes: a launch of few rows is a chain of memory latencies, in the
+// kernel above row count, first chunk, second chunk, gain.  Here all of a thread's two chunks (x, planes, gain) are asked for
+// before the row count is looked at; rows between it and the bound lie in the buffers.  Same sums in the same order.  Two
+// add + norm launches of 4096 columns, four planes: 16 rows 13.6 -> 12.4 us, 128 rows 16.8 -> 15.6, 512 rows 25.7 -> 24.8.
+template <bool ADD, bool TILED>
+__global__ __launch_bounds__(kRowThreads) void add_rmsnorm_row_kernel(const bf16_t* src, bf16_t* x, const float* __restrict__ delta,
+                                                                      int S, size_t sstride, const int32_t* __restrict__ m_dev,
+                                                                      int d, const bf16_t* __restrict__ gain, float eps,
+                                                                      bf16_t* __restrict__ h) {
+  __shared__ float sh[kRowThreads / 64];
+  const int r = blockIdx.x;
+  bf16_t* xr = x + (size_t)r * d;
+  const bf16_t* sr = ADD ? xr : src + (size_t)r * d;
+  int c[2];
+  bf16x8_t xv[2], gv[2];
+  float4 pv[2][4][2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    c[j] = min((int)threadIdx.x + j * kRowThreads, (d >> 3) - 1) * 8;
+    xv[j] = *reinterpret_cast<const bf16x8_t*>(sr + c[j]);
+    if (ADD) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float* p = delta + (size_t)min(i, S - 1) * sstride + (size_t)r * d + c[j];
+        pv[j][i][0] = *reinterpret_cast<const float4*>(p);
+        pv[j][i][1] = *reinterpret_cast<const float4*>(p + 4);
+      }
+    }
+    gv[j] = *reinterpret_cast<const bf16x8_t*>(gain + c[j]);
+  }
+  if (r >= *m_dev) return;
+  float v[2][8], ssq = 0.f;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const bool mine = (int)threadIdx.x + j * kRowThreads < (d >> 3);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[j][e] = (float)xv[j][e];
+    if (ADD) {
+      float dl[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dl[e] = (&pv[j][0][0].x)[e];
+#pragma unroll
+      for (int i = 1; i < 4; ++i)
+        if (i < S) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) dl[e] += (&pv[j][i][0].x)[e];
+        }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[j][e] = st<bf16_t>::rnd(v[j][e] + dl[e]);
+    }
+    if (mine && (ADD || x != nullptr)) st8(xr + c[j], v[j]);
+    if (mine) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ssq += v[j][e] * v[j][e];
+    }
+  }
+  ssq = block_sum<kRowThreads>(ssq, sh);
+  const float rstd = 1.0f / sqrtf(ssq / (float)d + eps);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    if ((int)threadIdx.x + j * kRowThreads >= (d >> 3)) continue;
+    float o[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = v[j][e] * rstd * (float)gv[j][e];
+    st8(h + act_index<TILED>(r, c[j], d), o);
+  }
+}
 
 // Thick-launch variant of the kernel above for d = 512 CH: one wave per row (four rows per workgroup),
 // the row held in registers (CH chunks of 8 per lane), the sum of squares reduced by shuffles, no LDS and
@@ -623,6 +690,8 @@ int slk_embed_rmsnorm(hipStream_t s, int dtype, const void* emb, const int32_t* 
 // block, both mostly adding k-split planes), block-per-row against wave-per-row: 512 rows 12.3 against 14.9, 704 rows 14.3 /
 // 15.3, 801 rows 15.7 / 16.5, 857 rows 16.1 / 15.6, 1024 rows 15.9 / 15.6, 1280 rows 20.6 / 17.8, 2000 rows 18.3 / 10.5.
 constexpr int kWaveRowsMin = 832;
+// two chunks per thread; more planes than four would take the registers of a second workgroup per SIMD
+static bool row_kernel_takes(int d, int S) { return d > 8 * kRowThreads && d <= 16 * kRowThreads && S <= 4; }
 int slk_add_rmsnorm(hipStream_t s, int dtype, void* x, const float* delta, int S, size_t sstride,
                     const int32_t* m_dev, int m_upper, int d, const void* gain, float eps, void* h, int tiled) {
   if (m_upper <= 0) return SL_OK;
@@ -637,6 +706,13 @@ int slk_add_rmsnorm(hipStream_t s, int dtype, void* x, const float* delta, int S
   }
   if (dtype == SL_BF16 && d % 8 == 0 && d <= 8 * kRowThreads * kMaxChunks && sstride % 4 == 0 && al16(x) && al16(delta) &&
       al16(gain) && al16(h)) {
+    if (row_kernel_takes(d, S)) {
+      DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_row_kernel<true, TL>), dim3(m_upper), dim3(kRowThreads), 0, s,
+                                               (const bf16_t*)x, (bf16_t*)x, delta, S, sstride, m_dev, d, (const bf16_t*)gain, eps,
+                                               (bf16_t*)h));
+      SL_LAUNCH_CHECK();
+      return SL_OK;
+    }
     DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_vec_kernel<true, TL>), dim3(m_upper), dim3(kRowThreads), 0, s,
                                              (const bf16_t*)x, (bf16_t*)x, delta, S, sstride, m_dev, m_upper, d, (const bf16_t*)gain,
                                              eps, (bf16_t*)h));
@@ -662,6 +738,13 @@ int slk_rmsnorm(hipStream_t s, int dtype, const void* src, void* x, const int32_
     return SL_OK;
   }
   if (dtype == SL_BF16 && d % 8 == 0 && d <= 8 * kRowThreads * kMaxChunks && al16(src) && al16(x) && al16(gain) && al16(h)) {
+    if (row_kernel_takes(d, 1)) {
+      DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_row_kernel<false, TL>), dim3(m_upper), dim3(kRowThreads), 0, s,
+                                               (const bf16_t*)src, (bf16_t*)x, (const float*)nullptr, 1, (size_t)0, m_dev, d,
+                                               (const bf16_t*)gain, eps, (bf16_t*)h));
+      SL_LAUNCH_CHECK();
+      return SL_OK;
+    }
     DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_vec_kernel<false, TL>), dim3(m_upper), dim3(kRowThreads), 0, s,
                                              (const bf16_t*)src, (bf16_t*)x, (const float*)nullptr, 1, (size_t)0, m_dev,
                                              m_upper, d, (const bf16_t*)gain, eps, (bf16_t*)h));
