@@ -47,9 +47,8 @@ template <int TM> struct TileCfg {
   static constexpr int KT = 2;                      // k-tiles per barrier
   static constexpr int RING = 8;                    // A ring, in k-tiles; also the unroll of the loop
   static constexpr int KA = RING - KT;              // A k-tiles fetched ahead
-  // one touch of a wave lands here (never read); only short tiles touch (touches_weights)
-  static constexpr int TOUCH = TM <= 160 ? 256 : 0;
-  static constexpr int LDS = RING * KTB + 4 * TOUCH;
+  static constexpr int LDS = RING * KTB;
+  static constexpr int TOUCH = 256;                 // behind the ring, where a kernel touches: a wave's touches land here, never read
   // fragment registers: R row blocks, read LA ahead (R divides NA: static indices)
   static constexpr int R = NA % 8 == 0 ? 8 : NA % 7 == 0 ? 7 : NA % 6 == 0 ? 6 : NA % 5 == 0 ? 5 : 4;
   static constexpr int LA = R > 6 ? 6 : R - 1;
@@ -75,7 +74,7 @@ __device__ __forceinline__ void b_landed(Frag (&b)[NB]) {
 
 // One TM x 256 output tile (rows m0 .., column tile tn) by the whole 256-thread workgroup.
 // NT: weight loads carry the non-temporal hint (see stream_weights).
-template <int OUT, int TM, bool NT, bool PROBE>
+template <int OUT, int TM, bool NT, bool PROBE, bool TCH>
 __device__ __forceinline__ void ring_tile(
     const bf16_t* __restrict__ A, int a_tiled, const bf16_t* __restrict__ Wp, int n, int k, int k_per_split,
     const int M, int m_upper, float* __restrict__ Cf, bf16_t* __restrict__ Cb,
@@ -187,10 +186,11 @@ __device__ __forceinline__ void ring_tile(
   };
   Frag af[R];
 
-  // Touches (share > 1 row tiles run side by side on one XCD and want the same weights): a lane reads four bytes of a
+  // Touches (TCH; share > 1 row tiles run side by side on one XCD and want the same weights): a lane reads four bytes of a
   // 128-byte line, a wave the 64 lines of 32 columns and four k-tiles, two such chunks ahead of the loads of the k-tile it is
   // issued in.  Chunk p's 8 column blocks are dealt over the 4 share waves; t_x counts down to this wave's next one.
-  // They count in vmcnt like any load and make its waits, which ignore them, no looser.
+  // They count in vmcnt like any load and make its waits, which ignore them, no looser.  Kernels of their own: in the others the
+  // few scalar instructions cost (gate|up of 700 rows, 160-row tiles that never touch, 124 -> 130 us).
   const uint32_t t_voff = (uint32_t)lane * 128u;
   const uint32_t t_lds = lds_base + (uint32_t)(RING * KTB) + (uint32_t)__builtin_amdgcn_readfirstlane(wave) * TC::TOUCH;
   const int t_blocks = min(8, NF / 2 - n0 / 32);
@@ -198,14 +198,16 @@ __device__ __forceinline__ void ring_tile(
   int t_left = share > 1 ? ktiles / 4 - 1 : 0;      // whole chunks after the first, which the prologue fetches
   uint64_t pt = pb + 8192u;
   auto touch = [&] {
-    if (TC::TOUCH == 0 || t_left <= 0) return;
-    if (t_x < t_blocks)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(t_lds), "v"(t_voff),
-                   "s"(pt + (uint64_t)((uint32_t)t_x * (uint32_t)K16) * 1024u) : "memory", "m0");
-    t_x -= 8;
-    if (t_x < 0) t_x += 4 * share;
-    pt += 8192u;
-    --t_left;
+    if constexpr (TCH) {
+      if (t_left <= 0) return;
+      if (t_x < t_blocks)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(t_lds), "v"(t_voff),
+                     "s"(pt + (uint64_t)((uint32_t)t_x * (uint32_t)K16) * 1024u) : "memory", "m0");
+      t_x -= 8;
+      if (t_x < 0) t_x += 4 * share;
+      pt += 8192u;
+      --t_left;
+    }
   };
 
   long long pc0 = 0, pw0 = 0, pc1 = 0, pw1 = 0, pc2 = 0, pw2 = 0;
@@ -482,17 +484,17 @@ static TileMap pick_tile_map(int tiles_m, int tiles_n) {
   return TileMap{gn < cn ? gn : cn, cn};
 }
 
-template <int OUT, int TM, bool NT, bool PROBE = false>
+template <int OUT, int TM, bool NT, bool PROBE = false, bool TCH = false>
 __global__ __launch_bounds__(256, 1) void gemm_mfma256_kernel(
     const bf16_t* __restrict__ A, int a_tiled, const bf16_t* __restrict__ Wp, int n, int k, int k_per_split,
     const int32_t* __restrict__ m_dev, int m_upper, float* __restrict__ Cf, bf16_t* __restrict__ Cb,
     const int32_t* __restrict__ row_map, size_t ldc, int tiles_m, int tiles_n, TileMap tmap,
-    long long* __restrict__ probe, RopeScatter rs, int touches) {
+    long long* __restrict__ probe, RopeScatter rs) {
   const int M = min(*m_dev, m_upper);
   int tm, tn;
   if (!tile_of_workgroup(tmap, tiles_m, tiles_n, tm, tn) || tm * TM >= M) return;
-  ring_tile<OUT, TM, NT, PROBE>(A, a_tiled, Wp, n, k, k_per_split, M, m_upper, Cf, Cb, row_map, ldc, tm * TM, tn, probe, rs,
-                             touches ? (M + TM - 1) / TM : 0, tm);
+  ring_tile<OUT, TM, NT, PROBE, TCH>(A, a_tiled, Wp, n, k, k_per_split, M, m_upper, Cf, Cb, row_map, ldc, tm * TM, tn, probe, rs,
+                                 TCH ? (M + TM - 1) / TM : 0, tm);
 }
 
 // Workgroup slots a launch takes on the chip's 256 CUs.  Column tiles go to the XCDs in turn, so the XCD with the most of
@@ -526,25 +528,28 @@ static bool touches_weights(int tiles_m, int tiles_n, int splits, int tm) {
   return ring_slots(tiles_m, tiles_n, splits) <= 256 && tm <= 160 && (tiles_m >= 6 || (tm == 128 && tiles_m == 4));
 }
 
-template <int OUT, int TM, bool NT>
+template <int OUT, int TM, bool NT, bool TCH = false>
 static int launch_ring_hint(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n, int k,
                        int splits, float* Cf, void* Cb, const int32_t* row_map, size_t ldc, const RopeScatter& rs) {
   const int tiles_m = sl_cdiv(mu, TM), tiles_n = sl_cdiv(n, TILE);
-  const size_t sh = TileCfg<TM>::LDS;
-  auto kern = gemm_mfma256_kernel<OUT, TM, NT>;
+  const size_t sh = TileCfg<TM>::LDS + (TCH ? 4 * TileCfg<TM>::TOUCH : 0);
+  auto kern = gemm_mfma256_kernel<OUT, TM, NT, false, TCH>;
   static unsigned long long lds_ok = 0;              // one per kernel instantiation
   SL_ALLOW_DYNAMIC_LDS(lds_ok, kern, sh);
   const TileMap tmap = pick_tile_map(tiles_m, tiles_n);
   dim3 grid(8 * tiles_m * tmap.cn, splits), block(256);
   hipLaunchKernelGGL(kern, grid, block, sh, s, (const bf16_t*)A, a_tiled, (const bf16_t*)Wp, n, k, k / splits, m_dev, mu, Cf,
-                     (bf16_t*)Cb, row_map, ldc, tiles_m, tiles_n, tmap, (long long*)nullptr, rs,
-                     touches_weights(tiles_m, tiles_n, splits, TM) ? 1 : 0);
+                     (bf16_t*)Cb, row_map, ldc, tiles_m, tiles_n, tmap, (long long*)nullptr, rs);
   SL_LAUNCH_CHECK();
   return SL_OK;
 }
 template <int OUT, int TM>
 static int launch_ring(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n, int k,
                        int splits, float* Cf, void* Cb, const int32_t* row_map, size_t ldc, const RopeScatter& rs) {
+  if constexpr (TM <= 160) {                          // one round of workgroups: hinted
+    if (touches_weights(sl_cdiv(mu, TM), sl_cdiv(n, TILE), splits, TM))
+      return launch_ring_hint<OUT, TM, true, true>(s, A, a_tiled, Wp, m_dev, mu, n, k, splits, Cf, Cb, row_map, ldc, rs);
+  }
   return stream_weights(sl_cdiv(mu, TM), sl_cdiv(n, TILE), splits, TM)
              ? launch_ring_hint<OUT, TM, true>(s, A, a_tiled, Wp, m_dev, mu, n, k, splits, Cf, Cb, row_map, ldc, rs)
              : launch_ring_hint<OUT, TM, false>(s, A, a_tiled, Wp, m_dev, mu, n, k, splits, Cf, Cb, row_map, ldc, rs);
@@ -630,7 +635,7 @@ static int launch_probe(hipStream_t s, const void* A, int a_tiled, const void* W
   const TileMap tmap = pick_tile_map(tiles_m, tiles_n);
   dim3 grid(8 * tiles_m * tmap.cn, 1), block(256);
   hipLaunchKernelGGL(kern, grid, block, sh, s, (const bf16_t*)A, a_tiled, (const bf16_t*)Wp, n, k, k, m_dev, mu,
-                     (float*)nullptr, (bf16_t*)Cb, row_map, ldc, tiles_m, tiles_n, tmap, probe, RopeScatter{}, 0);
+                     (float*)nullptr, (bf16_t*)Cb, row_map, ldc, tiles_m, tiles_n, tmap, probe, RopeScatter{});
   SL_LAUNCH_CHECK();
   return SL_OK;
 }
