@@ -690,8 +690,13 @@ int slk_embed_rmsnorm(hipStream_t s, int dtype, const void* emb, const int32_t* 
 // block, both mostly adding k-split planes), block-per-row against wave-per-row: 512 rows 12.3 against 14.9, 704 rows 14.3 /
 // 15.3, 801 rows 15.7 / 16.5, 857 rows 16.1 / 15.6, 1024 rows 15.9 / 15.6, 1280 rows 20.6 / 17.8, 2000 rows 18.3 / 10.5.
 constexpr int kWaveRowsMin = 832;
-// two chunks per thread; more planes than four would take the registers of a second workgroup per SIMD
-static bool row_kernel_takes(int d, int S) { return d > 8 * kRowThreads && d <= 16 * kRowThreads && S <= 4; }
+// two chunks per thread; more planes than four would take the registers of a second workgroup per SIMD.  Past two workgroups
+// per CU the launch is no chain of latencies any more: the two norms of a block, early loads against the kernel above, us, 528
+// rows 26.9 / 27.9, 560 rows 28.8 / 29.5, 600 rows 30.7 / 29.7, 700 rows 30.6 / 29.7, 740 rows 31.2 / 30.2.
+constexpr int kRowKernelMax = 576;
+static bool row_kernel_takes(int m_upper, int d, int S) {
+  return m_upper <= kRowKernelMax && d > 8 * kRowThreads && d <= 16 * kRowThreads && S <= 4;
+}
 int slk_add_rmsnorm(hipStream_t s, int dtype, void* x, const float* delta, int S, size_t sstride,
                     const int32_t* m_dev, int m_upper, int d, const void* gain, float eps, void* h, int tiled) {
   if (m_upper <= 0) return SL_OK;
@@ -706,7 +711,7 @@ int slk_add_rmsnorm(hipStream_t s, int dtype, void* x, const float* delta, int S
   }
   if (dtype == SL_BF16 && d % 8 == 0 && d <= 8 * kRowThreads * kMaxChunks && sstride % 4 == 0 && al16(x) && al16(delta) &&
       al16(gain) && al16(h)) {
-    if (row_kernel_takes(d, S)) {
+    if (row_kernel_takes(m_upper, d, S)) {
       DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_row_kernel<true, TL>), dim3(m_upper), dim3(kRowThreads), 0, s,
                                                (const bf16_t*)x, (bf16_t*)x, delta, S, sstride, m_dev, d, (const bf16_t*)gain, eps,
                                                (bf16_t*)h));
@@ -738,7 +743,7 @@ int slk_rmsnorm(hipStream_t s, int dtype, const void* src, void* x, const int32_
     return SL_OK;
   }
   if (dtype == SL_BF16 && d % 8 == 0 && d <= 8 * kRowThreads * kMaxChunks && al16(src) && al16(x) && al16(gain) && al16(h)) {
-    if (row_kernel_takes(d, 1)) {
+    if (row_kernel_takes(m_upper, d, 1)) {
       DISPATCH_TILED(tiled, hipLaunchKernelGGL((add_rmsnorm_row_kernel<false, TL>), dim3(m_upper), dim3(kRowThreads), 0, s,
                                                (const bf16_t*)src, (bf16_t*)x, (const float*)nullptr, 1, (size_t)0, m_dev, d,
                                                (const bf16_t*)gain, eps, (bf16_t*)h));

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 SHAPE = wl.Shape("row-norm", 1, 2176, 2, 128, 1024, 1056, "bf16")
 
 
-@pytest.mark.parametrize("rows", [[1], [40], [300], [831]])
+@pytest.mark.parametrize("rows", [[1], [40], [300], [576], [577], [831]])
 def test_block(rows):
     check_layers(SHAPE, 1, 840 if rows[0] > 300 else 310, rows)
 
