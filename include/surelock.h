@@ -206,7 +206,8 @@ int sl_surelock_step_selected(sl_ctx *ctx, void *stream, int32_t *tokens, uint8_
 /* The restricted forward alone (Alg. 1, 'Compute on active positions'), layers
  * [layer_lo, layer_hi) on given block inputs: x_in [m_upper, d] (type T, packed in
  * active order) -> x_out [m_upper, d].  Writes the active rows' K/V into the cache.
- * m_dev points to the device int holding the true M (e.g. cu_active + B). */
+ * m_dev points to the device int holding the true M (e.g. cu_active + B); active_idx holds M
+ * entries (entries past M, if there are any, are not read). */
 int sl_forward_layers(sl_ctx *ctx, void *stream, const void *x_in, void *x_out,
                       const int32_t *active_idx, const int32_t *m_dev, int32_t m_upper,
                       int32_t layer_lo, int32_t layer_hi, void *workspace, size_t workspace_bytes);

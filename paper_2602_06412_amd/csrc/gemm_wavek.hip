@@ -29,7 +29,7 @@ template <int OUT, int NA, int NBK> struct WkCfg {
   static constexpr int BUFS = NA > 4 ? 2 : 1;
   static constexpr int EPI = BUFS * PASS + (OUT == 3 ? WK_WAVES * 16 * VUNIT * 2 : 0);
   static constexpr int LDS = RING > EPI ? RING : EPI;
-  static_assert((OUT == 3 ? RD : RD - 1) * P <= 63 && LDS <= 160 * 1024, "wait counts, LDS");
+  static_assert((RD - 1) * P <= 63 && LDS <= 160 * 1024, "wait counts, LDS");
 };
 
 template <int V> struct WkInt { static constexpr int value = V; };
@@ -94,18 +94,6 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
   const uint32_t k_off = ((uint32_t)(split * k_split) / 16u + (uint32_t)wave * 2u) * 1024u;
   uint64_t pa = (uint64_t)(uintptr_t)A + k_off, pb = (uint64_t)(uintptr_t)Wp + k_off;
   constexpr uint32_t K_STEP = WK_STEP / 16 * 1024;
-  // the flat ids of the rows this lane will finish, asked for first and used after the last wait of the k loop
-  constexpr int PASSES = (NA + 3) / 4;
-  int gid[PASSES];
-  if constexpr (OUT == 3) {
-#pragma unroll
-    for (int p = 0; p < PASSES; ++p) {
-      gid[p] = 0;
-      const uint32_t off = (uint32_t)min(m0 + (p * 4 + wave) * 16 + row_in, m_upper - 1) * 4u;
-      asm volatile("global_load_dword %0, %1, %2" : "+v"(gid[p]) : "v"(off), "s"(rs.active_idx) : "memory");
-    }
-  }
-
   // Loads are inline assembly: the compiler would make every LDS read wait for all direct-to-LDS loads.  The register-ring
   // contract: fb is a read-write operand of every load and of the wait that covers it, every fetched slot is consumed, and
   // the kernel holds no spill (the build fails on scratch).
@@ -151,10 +139,6 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
     for (int a = 0; a < NA; ++a) fetch_a(u, a);
     pa += K_STEP;
   }
-  if constexpr (OUT == 3) {                           // older than every fragment: here before the first of them
-#pragma unroll
-    for (int p = 0; p < PASSES; ++p) asm volatile("s_waitcnt vmcnt(%1)" : "+v"(gid[p]) : "n"(RD * P) : "memory");
-  }
   const int M = min(*m_dev, m_upper);
 #pragma unroll
   for (int a = 0; a < NA; ++a)
@@ -194,6 +178,17 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
       weights(u);
     }
   }
+  // the flat ids of the rows this lane will finish (none past the row count: the array may end there), behind the last
+  // fragments, which are waited for first; younger loads make those waits no looser
+  constexpr int PASSES = (NA + 3) / 4;
+  int gid[PASSES];
+  if constexpr (OUT == 3) {
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+      const int row = m0 + (p * 4 + wave) * 16 + row_in;
+      gid[p] = p * 4 + wave < NA && row < M ? rs.active_idx[row] : -1;
+    }
+  }
   // the last RD steps fetch nothing; after the last wait no load is in flight
   landed(WkInt<(RD - 1) * P>{}, 0);
   step(WkInt<0>{}, 0, 0);
@@ -221,9 +216,8 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
     if (rs.kc == nullptr && tn * HB >= 4 * rs.H) return;         // queries only (uniform over the workgroup)
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
-      const int row = m0 + (p * 4 + wave) * 16 + row_in;
-      seq[p] = gid[p] / rs.N;
-      gid[p] = row < M && p * 4 + wave < NA ? gid[p] - seq[p] * rs.N : -1;       // the slot
+      seq[p] = max(gid[p], 0) / rs.N;
+      gid[p] -= seq[p] * rs.N;                        // the slot, -1 past the row count
       if constexpr (EARLY) {
 #pragma unroll
         for (int b = 0; b < HB; ++b) rope_load_unit(tab[p][b], max(gid[p], 0), (tn * HB + b & 3) * 16, rs);

@@ -94,3 +94,21 @@ def test_queries_only(locked):
     assert torch.equal(sess.kv, kv)
     assert torch.equal(logits, sess.logits_view(2)[idx[:locked].long()])
     sess.close()
+
+
+@pytest.mark.parametrize("m,m_upper", [(1, 16), (40, 80), (40, 200), (100, 200), (200, 300)])
+def test_row_ids_end_at_the_count(m, m_upper):
+    """active_idx of exactly m entries under a larger bound: the same result as with an array of m_upper entries (what lies
+    behind the m-th is not the library's to read; that no lane does is shown by the code, which asks for the ids of rows
+    below the count only)."""
+    sess = B.Session(QKV_GATE_UP, weights_to_device(wl.make_weights(QKV_GATE_UP, seed=1)), 1, 300)
+    x = wl.gaussian_rows(1, m_upper, QKV_GATE_UP.d_model, "bf16").to(DEV)
+    ids = torch.as_tensor(np.sort(np.random.default_rng(m).permutation(300)[:m_upper]).astype(np.int32), device=DEV)
+    got = []
+    for idx in (ids, ids[:m].clone()):
+        out = torch.zeros_like(x)
+        B.sl_forward_layers(sess.ctx, x, out, idx, torch.tensor([m], dtype=torch.int32, device=DEV), m_upper, 0, 1, sess.workspace)
+        torch.cuda.synchronize()
+        got.append((out, sess.kv.clone()))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    sess.close()
