@@ -342,27 +342,35 @@ template <int OUT, int NA, int NBK> struct W22Cfg {
   static_assert(NA % R == 0 && P <= 63 && LDS <= 160 * 1024, "schedule");
 };
 
+// XCD x owns the column tiles 8 c + x; the row tiles and splits of one column tile follow each other.  Only row tiles that hold
+// rows are counted, so the workgroups without work are the last ones: an XCD's workgroups go to its four shader engines in turn,
+// and with every fourth one working they all went to one engine's eight CUs, two to a CU (gate|up of 16 rows bounded by 1024 116 us,
+// of 300 rows 128; now 62 and 76).  Three count as four: 600 rows 131 us, in threes 138.
+struct W22Tile { int tm, tn, split; };
+__host__ __device__ inline W22Tile w22_tile(int wg, int row_tiles, int splits) {
+  const int per = row_tiles == 3 ? 4 : row_tiles, xcd = wg & 7, j = wg >> 3, group = j / per;
+  return W22Tile{j % per, group / splits * 8 + xcd, group % splits};
+}
+void slk_wave22_tile(int wg, int row_tiles, int splits, int* out) {     // for tests
+  const W22Tile t = w22_tile(wg, row_tiles, splits);
+  out[0] = t.tm; out[1] = t.tn; out[2] = t.split;
+}
+
 template <int OUT, int NA, int NBK>
 __global__ __launch_bounds__(256, 1) void gemm_wave22_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp, int n, int k, int splits, const int32_t* __restrict__ m_dev,
-    int m_upper, float* __restrict__ Cf, bf16_t* __restrict__ Cb, size_t ldc, int tiles_m, int tiles_n) {
+    int m_upper, float* __restrict__ Cf, bf16_t* __restrict__ Cb, size_t ldc, int tiles_n) {
   typedef W22Cfg<OUT, NA, NBK> WC;
   constexpr int RD = WC::RD, P = WC::P, R = WC::R, HB = NBK / 2, TM = NA * 16;
   extern __shared__ Frag lds[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int kg = wave >> 1, cg = wave & 1;
   const int g4 = lane >> 4, row_in = lane & 15;
-  // XCD x owns the column tiles 8 c + x; the row tiles and splits of one column tile follow each other
-  int tm, tn, split;
-  {
-    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-    tm = j % tiles_m;
-    split = j / tiles_m % splits;
-    tn = j / (tiles_m * splits) * 8 + xcd;
-  }
-  if (tn >= tiles_n) return;
-  const int M = min(*m_dev, m_upper), m0 = tm * TM;
-  if (m0 >= M) return;
+  const int M = min(*m_dev, m_upper);
+  if (M <= 0) return;
+  const W22Tile tile = w22_tile(blockIdx.x, (M + TM - 1) / TM, splits);
+  const int tm = tile.tm, tn = tile.tn, split = tile.split, m0 = tm * TM;
+  if (tn >= tiles_n || m0 >= M) return;
   const int k_split = k / splits, steps = k_split / 64;
   const int K16 = k / 16, NF = n / 16;
   auto col_block = [&](int b) {
@@ -532,7 +540,7 @@ static int launch_wave22(hipStream_t s, const void* A, const void* Wp, const int
   SL_ALLOW_DYNAMIC_LDS(lds_ok, kern, sh);
   const int tiles_m = sl_cdiv(mu, NA * 16), tiles_n = sl_cdiv(n, 32 * NBK);
   hipLaunchKernelGGL(kern, dim3(8 * sl_cdiv(tiles_n, 8) * tiles_m * splits), dim3(256), sh, s, (const bf16_t*)A, (const bf16_t*)Wp, n, k,
-                     splits, m_dev, mu, Cf, (bf16_t*)Cb, ldc, tiles_m, tiles_n);
+                     splits, m_dev, mu, Cf, (bf16_t*)Cb, ldc, tiles_n);
   SL_LAUNCH_CHECK();
   return SL_OK;
 }

@@ -81,3 +81,13 @@ THIN = wl.Shape("loose-thin", 1, 512, 4, 128, 1024, 1056, "bf16")
 @pytest.mark.parametrize("N,m,m_upper", [(300, 0, 300), (300, 1, 300), (300, 33, 300), (300, 32, 64), (512, 200, 512), (2048, 40, 256)])
 def test_thin_attention(N, m, m_upper):
     check_bound(THIN, N, m, m_upper)
+
+
+# gate|up by 2 x 2 waves in four row tiles (230 column slices a round), and in two
+WIDE = wl.Shape("loose-wide", 1, 256, 2, 128, 11008, 1056, "bf16")
+
+
+@pytest.mark.parametrize("m,m_upper", [(0, 1024), (16, 1024), (256, 1024), (257, 1000), (600, 1024), (769, 1024), (0, 500), (40, 500),
+                                       (250, 500), (260, 500), (499, 500)])
+def test_two_by_two_waves(m, m_upper):
+    check_bound(WIDE, 1024, m, m_upper)
