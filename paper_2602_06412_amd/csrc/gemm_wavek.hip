@@ -310,14 +310,14 @@ static int launch_wavek(hipStream_t s, const void* A, const void* Wp, const int3
   return SL_OK;
 }
 
-// The smallest NA of the list that covers the rows with `tiles_m` row tiles.
-template <int OUT, int NBK>
-static int launch_rows(hipStream_t s, int tiles_m, const void* A, const void* Wp, const int32_t* m_dev, int mu, int n, int k, int splits,
-                       float* Cf, void* Cb, size_t ldc, const RopeScatter& rs = RopeScatter{}) {
-  const int na = sl_cdiv(mu, 16 * tiles_m);
-#define GO(NA) if (na <= NA) return launch_wavek<OUT, NA, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc, rs)
-  if constexpr (NBK == 4 || OUT == 2) { GO(1); GO(2); GO(3); }
-  GO(4); GO(5); GO(6); GO(7); GO(8); GO(10); GO(12); GO(14); GO(16);
+// A launch of `blocks` 16-row blocks per workgroup; compiled for the heights LO .. HI that its form takes (wavek_blocks).
+template <int OUT, int NBK, int LO, int HI>
+static int launch_blocks(hipStream_t s, int blocks, const void* A, const void* Wp, const int32_t* m_dev, int mu, int n, int k, int splits,
+                         float* Cf, void* Cb, size_t ldc, const RopeScatter& rs = RopeScatter{}) {
+#define GO(NA) \
+  if constexpr (NA >= LO && NA <= HI) \
+    if (blocks == NA) return launch_wavek<OUT, NA, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc, rs)
+  GO(1); GO(2); GO(3); GO(4); GO(5); GO(6); GO(7); GO(8); GO(10); GO(12); GO(14); GO(16);
 #undef GO
   return SL_EINVAL;
 }
@@ -545,14 +545,13 @@ static int launch_wave22(hipStream_t s, const void* A, const void* Wp, const int
   return SL_OK;
 }
 template <int OUT, int NBK>
-static int launch22_rows(hipStream_t s, int tm, const void* A, const void* Wp, const int32_t* m_dev, int mu, int n, int k, int splits,
-                    float* Cf, void* Cb, size_t ldc) {
-  switch (tm) {
-    case 128: return launch_wave22<OUT, 8, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc);
-    case 160: return launch_wave22<OUT, 10, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc);
-    case 192: return launch_wave22<OUT, 12, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc);
-    case 224: return launch_wave22<OUT, 14, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc);
-    case 256: return launch_wave22<OUT, 16, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc);
+static int launch22_blocks(hipStream_t s, int blocks, const void* A, const void* Wp, const int32_t* m_dev, int mu, int n, int k, int splits,
+                           float* Cf, void* Cb, size_t ldc) {
+  switch (blocks) {
+    case 10: return launch_wave22<OUT, 10, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc);
+    case 12: return launch_wave22<OUT, 12, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc);
+    case 14: return launch_wave22<OUT, 14, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc);
+    case 16: return launch_wave22<OUT, 16, NBK>(s, A, Wp, m_dev, mu, n, k, splits, Cf, Cb, ldc);
   }
   return SL_EINVAL;
 }
@@ -571,50 +570,78 @@ static bool fits(int mu, int n, int k, int k_unit, int workgroups) {
 constexpr int kWavekTrip = 4 * WK_STEP;               // k of a whole trip of the deepest ring
 constexpr int kPlanes = 4;
 
+// A launch's form: waves along k (1) or 2 x 2 waves (2), 16-row and 16-column blocks per workgroup, row tiles; kernel 0: not
+// taken.  Waves along k: the smallest compiled height that covers the rows, from `lowest` on.
+struct WkForm { int kernel, blocks, cols, tiles_m; };
+static WkForm wavek_form(int mu, int tiles_m, int cols, int lowest) {
+  int b = sl_cdiv(mu, 16 * tiles_m);
+  if (b < lowest) b = lowest;
+  if (b > 8) b = (b + 1) / 2 * 2;
+  return WkForm{1, b, cols, tiles_m};
+}
+// 2 x 2 waves: whole pairs of blocks, evenly over tiles of at most 256 rows
+static WkForm wave22_form(int mu, int cols) {
+  const int tiles_m = sl_cdiv(mu, 256);
+  return WkForm{2, (int)sl_align_up(sl_cdiv(mu, tiles_m), 32) / 16, cols, tiles_m};
+}
+
 // Q|K|V: up to 80 rows 64 columns (two units of 16 + 16 that RoPE pairs) for all rows; from 81 rows on 96 columns for half of the
 // rows each, where (rows / 2 + 96) is less to read than (rows + 64) and 256 CUs share the work instead of 192 (96 rows 37.7 ->
 // 35.4 us, 256 rows 56 -> 47; 80 rows 34.8 -> 34.6, 64 rows 29.5 -> 32.5).  Up to 384 rows: there 55 us against 62 of the
 // ring kernel's k-split with RoPE behind it, at 400 rows 60 against 59 of its fused form.
-constexpr int kWavekQkvRows = 384;
-static int qkv_row_tiles(int mu) { return mu > 80 ? 2 : 1; }
-int slk_wavek_qkv_ok(int mu, int H, int k) {
-  return mu <= kWavekQkvRows && H > 0 && fits(mu, 3 * H * 128, k, kWavekTrip, qkv_row_tiles(mu) == 2 ? 8 * H : 6 * H);
+constexpr int kWavekQkvRows = 384, kWavekQkvOneTile = 80;
+static WkForm qkv_form(int mu, int H, int k) {
+  if (mu > kWavekQkvRows || H <= 0 || !fits(mu, 3 * H * 128, k, kWavekTrip, mu > kWavekQkvOneTile ? 8 * H : 6 * H)) return WkForm{};
+  return mu > kWavekQkvOneTile ? wavek_form(mu, 2, 6, 4) : wavek_form(mu, 1, 4, 1);
 }
+int slk_wavek_qkv_ok(int mu, int H, int k) { return qkv_form(mu, H, k).kernel != 0; }
 int slk_wavek_qkv_rope(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int H, int k,
                        const int32_t* active_idx, int N, int n_pad, const void* rope_tab, void* q, void* kc, void* vc) {
   const int n = 3 * H * 128;
-  if (!slk_wavek_qkv_ok(mu, H, k) || !active_idx || !rope_tab || !q || (kc == nullptr) != (vc == nullptr)) return SL_EINVAL;
+  const WkForm f = qkv_form(mu, H, k);
+  if (!f.kernel || !active_idx || !rope_tab || !q || (kc == nullptr) != (vc == nullptr)) return SL_EINVAL;
   if ((uintptr_t)q % 16 || (uintptr_t)kc % 16 || (uintptr_t)vc % 16 || (uintptr_t)rope_tab % 16) return SL_EINVAL;
   const RopeScatter rs{active_idx, (const float2*)rope_tab, (bf16_t*)q, (bf16_t*)kc, (bf16_t*)vc, N, n_pad, H};
-  if (qkv_row_tiles(mu) == 2) return launch_rows<3, 6>(s, 2, A, Wp, m_dev, mu, n, k, 1, nullptr, nullptr, (size_t)n, rs);
-  return launch_rows<3, 4>(s, 1, A, Wp, m_dev, mu, n, k, 1, nullptr, nullptr, (size_t)n, rs);
+  if (f.tiles_m == 2) return launch_blocks<3, 6, 4, 12>(s, f.blocks, A, Wp, m_dev, mu, n, k, 1, nullptr, nullptr, (size_t)n, rs);
+  return launch_blocks<3, 4, 1, 5>(s, f.blocks, A, Wp, m_dev, mu, n, k, 1, nullptr, nullptr, (size_t)n, rs);
 }
 
 // gate|up: up to 256 rows 48 gate columns and their 48 up columns per workgroup, up to 512 rows 96 + 96 with two row tiles.
-// Four row tiles only where they are full: 992 rows 166 -> 153 us, 960 rows 145 -> 153, 857 rows 143.5 -> 143, 800 rows 124 -> 143
-// (the ring kernel's shorter tiles); three are a round and a half (700 rows 119 -> 146).
-static int wave22_tile_rows(int mu) { return (int)sl_align_up(sl_cdiv(mu, sl_cdiv(mu, 256)), 32); }
-int slk_wavek_swiglu_ok(int mu, int dff, int k) {
-  if (mu <= 256) return fits(mu, 2 * dff, k, kWavekTrip, sl_cdiv(dff, 48));
-  if (mu <= 512) return fits(mu, 2 * dff, k, 64, 2 * sl_cdiv(dff, 96));
-  const int two_rounds = 4 * sl_cdiv(dff, 96);
-  return mu > 960 && mu <= 1024 && two_rounds > 448 && fits(mu, 2 * dff, k, 64, two_rounds / 2);
+// Four row tiles where the ring kernel's best tiles, 192 rows on five row tiles, no longer cover the rows (992 rows 166 -> 153 us;
+// 960 rows 145 against 153, 857 rows 143.5 / 143, 800 rows 124 / 143), and the column slices fill the second round of workgroups
+// too; three are a round and a half (700 rows 119 against 146).
+constexpr int kRingRows5 = 5 * 192;
+static WkForm swiglu_form(int mu, int dff, int k) {
+  if (mu <= 256) return fits(mu, 2 * dff, k, kWavekTrip, sl_cdiv(dff, 48)) ? wavek_form(mu, 1, 6, 1) : WkForm{};
+  const int slices = sl_cdiv(dff, 96);
+  const bool two_tiles = mu <= 512, four_tiles = mu > kRingRows5 && mu <= 1024 && 2 * slices > 224;
+  return (two_tiles || four_tiles) && fits(mu, 2 * dff, k, 64, 2 * slices) ? wave22_form(mu, 6) : WkForm{};
 }
+int slk_wavek_swiglu_ok(int mu, int dff, int k) { return swiglu_form(mu, dff, k).kernel != 0; }
 int slk_wavek_swiglu(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int dff, int k, void* a) {
-  if (!slk_wavek_swiglu_ok(mu, dff, k)) return SL_EINVAL;
-  if (mu <= 256) return launch_rows<2, 6>(s, 1, A, Wp, m_dev, mu, 2 * dff, k, 1, nullptr, a, (size_t)dff);
-  return launch22_rows<2, 6>(s, wave22_tile_rows(mu), A, Wp, m_dev, mu, 2 * dff, k, 1, nullptr, a, (size_t)dff);
+  const WkForm f = swiglu_form(mu, dff, k);
+  if (!f.kernel) return SL_EINVAL;
+  if (f.kernel == 1) return launch_blocks<2, 6, 1, 16>(s, f.blocks, A, Wp, m_dev, mu, 2 * dff, k, 1, nullptr, a, (size_t)dff);
+  return launch22_blocks<2, 6>(s, f.blocks, A, Wp, m_dev, mu, 2 * dff, k, 1, nullptr, a, (size_t)dff);
 }
 
 // Out and down, k in four splits: up to 256 rows 64 columns for all rows, up to 512 rows 128 columns and two row tiles (512 rows
 // down 56.5 -> 50 us, 264 rows 46.5 -> 41).  The number of planes, 0 if these launches do not take the shape.  (Two row tiles of
 // 128 columns with the waves along k: the same from 128 rows on, slower below.)
-int slk_wavek_splits(int mu, int n, int k) {
-  if (mu <= 256) return fits(mu, n, k, kPlanes * kWavekTrip, kPlanes * sl_cdiv(n, 64)) ? kPlanes : 0;
-  return mu <= 512 && fits(mu, n, k, kPlanes * 64, 2 * kPlanes * sl_cdiv(n, 128)) ? kPlanes : 0;
+static WkForm planes_form(int mu, int n, int k) {
+  if (mu <= 256) return fits(mu, n, k, kPlanes * kWavekTrip, kPlanes * sl_cdiv(n, 64)) ? wavek_form(mu, 1, 4, 1) : WkForm{};
+  return mu <= 512 && fits(mu, n, k, kPlanes * 64, 2 * kPlanes * sl_cdiv(n, 128)) ? wave22_form(mu, 4) : WkForm{};
 }
+int slk_wavek_splits(int mu, int n, int k) { return planes_form(mu, n, k).kernel ? kPlanes : 0; }
 int slk_wavek_planes(hipStream_t s, const void* A, const void* Wp, const int32_t* m_dev, int mu, int n, int k, float* Cf) {
-  if (!slk_wavek_splits(mu, n, k) || !Cf || (uintptr_t)Cf % 16) return SL_EINVAL;
-  if (mu <= 256) return launch_rows<0, 4>(s, 1, A, Wp, m_dev, mu, n, k, kPlanes, Cf, nullptr, (size_t)n);
-  return launch22_rows<0, 4>(s, wave22_tile_rows(mu), A, Wp, m_dev, mu, n, k, kPlanes, Cf, nullptr, (size_t)n);
+  const WkForm f = planes_form(mu, n, k);
+  if (!f.kernel || !Cf || (uintptr_t)Cf % 16) return SL_EINVAL;
+  if (f.kernel == 1) return launch_blocks<0, 4, 1, 16>(s, f.blocks, A, Wp, m_dev, mu, n, k, kPlanes, Cf, nullptr, (size_t)n);
+  return launch22_blocks<0, 4>(s, f.blocks, A, Wp, m_dev, mu, n, k, kPlanes, Cf, nullptr, (size_t)n);
+}
+
+// for tests: the form of a layer's launch; projection 0: Q|K|V (width = heads), 1: gate|up (d_ff), 2: Out and down (columns)
+void slk_wavek_form(int projection, int mu, int width, int k, int* out) {
+  const WkForm f = projection == 0 ? qkv_form(mu, width, k) : projection == 1 ? swiglu_form(mu, width, k) : planes_form(mu, width, k);
+  out[0] = f.kernel; out[1] = f.blocks; out[2] = f.cols; out[3] = f.tiles_m;
 }
