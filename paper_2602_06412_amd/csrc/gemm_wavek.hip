@@ -140,6 +140,16 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
     pa += K_STEP;
   }
   const int M = min(*m_dev, m_upper);
+  if (M <= 0) {                                       // uniform; nothing of the prologue's may still be on its way
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    return;
+  }
+  // 16-row blocks past the count: from here on the tile's first block in their place (lines that are on their way anyway), so
+  // that a bound above the count costs no more reads (one block at N = 512, bound 160: 1 row 136 -> 115 us, 33 rows 141 -> 124; bound
+  // 256: no row 141 -> 32, 33 rows 161 -> 143; tight bounds the same within 0.5 %)
+#pragma unroll
+  for (int a = 1; a < NA; ++a)
+    if (m0 + a * 16 >= M) a_voff[a] = a_voff[0];
 #pragma unroll
   for (int a = 0; a < NA; ++a)
 #pragma unroll

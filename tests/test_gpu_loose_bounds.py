@@ -91,3 +91,15 @@ WIDE = wl.Shape("loose-wide", 1, 256, 2, 128, 11008, 1056, "bf16")
                                        (250, 500), (260, 500), (499, 500)])
 def test_two_by_two_waves(m, m_upper):
     check_bound(WIDE, 1024, m, m_upper)
+
+
+# every projection of at most 512 rows by the few-row kernels, with two and more trips of their rings: 16-row blocks past the
+# count are read from the first block's place, and no row at all ends the launch after its first loads
+FEW = wl.Shape("loose-few", 1, 2560, 32, 128, 10240, 1056, "bf16")
+
+
+@pytest.mark.parametrize("m,m_upper", [(0, 16), (0, 80), (1, 80), (16, 80), (17, 80), (63, 80), (0, 128), (1, 128), (33, 112), (0, 200),
+                                       (16, 160), (40, 192), (112, 224), (0, 256), (1, 256), (130, 256), (255, 256), (100, 320), (1, 384),
+                                       (193, 384)])
+def test_few_row_projections(m, m_upper):
+    check_bound(FEW, 400, m, m_upper)
