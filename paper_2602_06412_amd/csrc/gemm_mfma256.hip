@@ -186,7 +186,7 @@ __device__ __forceinline__ void ring_tile(
   };
   Frag af[R];
 
-  // Touches (TCH; share > 1 row tiles run side by side on one XCD and want the same weights): a lane reads four bytes of a
+  // Touches (TCH; share > 2 row tiles that hold rows run side by side on one XCD and want the same weights): a lane reads four bytes of a
   // 128-byte line, a wave the 64 lines of 32 columns and four k-tiles, two such chunks ahead of the loads of the k-tile it is
   // issued in.  Chunk p's 8 column blocks are dealt over the 4 share waves; t_x counts down to this wave's next one.
   // They count in vmcnt like any load and make its waits, which ignore them, no looser.  Kernels of their own: in the others the
@@ -195,7 +195,9 @@ __device__ __forceinline__ void ring_tile(
   const uint32_t t_lds = lds_base + (uint32_t)(RING * KTB) + (uint32_t)__builtin_amdgcn_readfirstlane(wave) * TC::TOUCH;
   const int t_blocks = min(8, NF / 2 - n0 / 32);
   int t_x = __builtin_amdgcn_readfirstlane(wave * share + tm);
-  int t_left = share > 1 ? ktiles / 4 - 1 : 0;      // whole chunks after the first, which the prologue fetches
+  // Two under a larger bound lose by it (a block with cold weights: 140 and 224 rows bounded by 896 + 1 %, by 2048 + 2 %), three do not
+  // (300 rows bounded by 2048 - 3 %).
+  int t_left = share > 2 ? ktiles / 4 - 1 : 0;      // whole chunks after the first, which the prologue fetches
   uint64_t pt = pb + 8192u;
   auto touch = [&] {
     if constexpr (TCH) {
@@ -518,14 +520,22 @@ static bool stream_weights(int tiles_m, int tiles_n, int splits, int tm) {
 // line that misses its L2 for 625 ns, one that hits for 250.  In one round of workgroups the R row tiles of a column run side by
 // side on one XCD, ask for a weight line together and all wait for it; with each touching 1/R of the lines a few k-tiles ahead
 // (four bytes a line) all but one find them in L2.  It pays where short tiles wait for lines and many share them.  Weights out of
-// HBM, us without -> with: down of 1024 rows (128 x 8, two splits) 94 -> 81, 2048 rows (160 x 13) 166 -> 150, Out of 857 rows
-// (128 x 7) 36.2 -> 33.6, 1400 rows (96 x 15) 55 -> 47, Q|K|V of 512 rows (128 x 4) 62 -> 58.  Not with few sharers or tall
-// tiles: Q|K|V of 544 rows (128 x 5) 63.5 -> 66, 704 rows (160 x 5) 73 -> 75, 960 rows (192 x 5) 83.5 -> 86, Out of 608 rows (160 x 4)
-// 27.5 -> 28.5, gate|up of 512 rows (256 x 2) 84 -> 92; nor 96-row tiles of four or five, where Q|K|V gains 2 to 4 us at 390 to 430
-// rows and the launches behind it lose them.  The touches carry no non-temporal hint: with it the lines are gone before they
-// are read (Q|K|V of 512 rows 69).
-static bool touches_weights(int tiles_m, int tiles_n, int splits, int tm) {
-  return ring_slots(tiles_m, tiles_n, splits) <= 256 && tm <= 160 && (tiles_m >= 6 || (tm == 128 && tiles_m == 4));
+// HBM, us without -> with: down of 1024 rows (128 x 8, two splits) 95 -> 86, 2048 rows (128 x 16) 164 -> 149, Out of 768 rows
+// (128 x 6) 34.2 -> 32.0, 1536 rows (128 x 12) 55 -> 48; 202 launches of six and more row tiles (n = 1024 .. 8192, k = 512 .. 12288,
+// 576 .. 2048 rows) gain 6 % on average, up to 23 %.  Four tiles of 128 rows gain as well (n = 3072 .. 16384, k = 2048 .. 12288: 4 % on
+// average, Q|K|V of 512 rows 58 -> 51), other heights and fewer sharers do not: Q|K|V of 544 rows (128 x 5) 63.5 -> 66, 704 rows
+// (160 x 5) 73 -> 75, 960 rows (192 x 5) 83.5 -> 86, gate|up of 512 rows (256 x 2) 84 -> 92; 96-row tiles of four or five gain 2 to 4 us in
+// Q|K|V of 390 to 430 rows and the launches behind them lose it.  Tall tiles have fewer lines to wait for per MFMA and gain only in
+// long reductions: 160 x 8 k = 512 to 2048 14.3 -> 14.9 to 36.3 -> 36.9, Out of 1280 rows 40.7 -> 41.7; down of 1280 rows 103 -> 101.
+// 128-row tiles over a short reduction, split so that they fill the chip, lose too: n = 4096, k = 2048 in two of 1024 rows 22.7 -> 23.9,
+// n = 7168 of 416 rows 21.1 -> 22.4, n = 3072 in four 15.8 -> 16.7; with fewer workgroups they gain (n = 5120 in two, 512 rows 21.5 ->
+// 20.7), and so do shorter tiles (n = 2048 in two, 64 x 14 16.7 -> 15.0).
+// The touches carry no non-temporal hint: with it the lines are gone before they are read (Q|K|V of 512 rows 69).
+static bool touches_weights(int tiles_m, int tiles_n, int splits, int tm, int k) {
+  if (ring_slots(tiles_m, tiles_n, splits) > 256) return false;
+  if (tm == 128 && splits > 1 && k / splits <= 1024 && tiles_m * tiles_n * splits >= 192) return false;
+  if (tm == 160) return tiles_m >= 6 && k / splits >= 4096;
+  return tm < 160 && (tiles_m >= 6 || (tm == 128 && tiles_m == 4));
 }
 
 template <int OUT, int TM, bool NT, bool TCH = false>
@@ -547,7 +557,7 @@ template <int OUT, int TM>
 static int launch_ring(hipStream_t s, const void* A, int a_tiled, const void* Wp, const int32_t* m_dev, int mu, int n, int k,
                        int splits, float* Cf, void* Cb, const int32_t* row_map, size_t ldc, const RopeScatter& rs) {
   if constexpr (TM <= 160) {                          // one round of workgroups: hinted
-    if (touches_weights(sl_cdiv(mu, TM), sl_cdiv(n, TILE), splits, TM))
+    if (touches_weights(sl_cdiv(mu, TM), sl_cdiv(n, TILE), splits, TM, k))
       return launch_ring_hint<OUT, TM, true, true>(s, A, a_tiled, Wp, m_dev, mu, n, k, splits, Cf, Cb, row_map, ldc, rs);
   }
   return stream_weights(sl_cdiv(mu, TM), sl_cdiv(n, TILE), splits, TM)

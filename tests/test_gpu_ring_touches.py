@@ -15,13 +15,18 @@ def _touches(m_upper, n, k):
     """The rule, restated."""
     kernel, splits, height, cols, _ = B.sl_linear_plan(m_upper, n, k)
     tiles = -(-m_upper // height)
-    one_round = 8 * tiles * -(-(-(-n // cols)) // 8) * splits <= 256
-    return kernel == 1 and one_round and height <= 160 and (tiles >= 6 or (height == 128 and tiles == 4))
+    columns = -(-n // cols)
+    one_round = 8 * tiles * -(-columns // 8) * splits <= 256
+    short = height == 128 and splits > 1 and k // splits <= 1024 and tiles * columns * splits >= 192
+    if height == 160:
+        return kernel == 1 and one_round and tiles >= 6 and k // splits >= 4096
+    return kernel == 1 and one_round and not short and height < 160 and (tiles >= 6 or (height == 128 and tiles == 4))
 
 
 @pytest.mark.parametrize("n,k,m_upper,ms", [
     (12288, 4096, 512, [512, 130, 1]),          # 128 x 4; with few rows one sharer is left, or none but the tile itself
-    (4096, 2048, 1024, [1023]),                 # 128 x 8, two splits
+    (4096, 4096, 1024, [1023, 257]),            # 128 x 8, two splits; three sharers, the fewest that touch
+    (4096, 8192, 1280, [1279, 500]),            # 160 x 8, two splits: the tallest tiles that touch
     (8192 - 160, 384, 600, [600, 255]),         # a ragged last column tile
     (8192 - 32, 256, 640, [640]),               # the shortest ring, one chunk to touch
     (1024, 512, 2048, [2040]),                  # more row tiles than column blocks
