@@ -59,6 +59,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
   const int split = blockIdx.x % splits, wg = blockIdx.x / splits;
   const int tm = (wg >> 3) % tiles_m, tn = (wg >> 3) / tiles_m * 8 + (wg & 7), m0 = tm * NA * 16;
   if (tn >= tiles_n || (tm > 0 && m0 >= *m_dev)) return;
+  if (OUT == 3 && rs.kc == nullptr && tn * HB >= 4 * rs.H) return;        // queries only: a slice of keys or values
   const int k_split = k / splits, steps = k_split / WK_STEP;
   const int K16 = k / 16, NF = n / 16;
 
@@ -223,7 +224,6 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
   constexpr bool EARLY = NA <= 8;                     // all of a lane's table rows at once, where registers are free
   float4 tab[EARLY ? PASSES : 1][HB][2];
   if constexpr (OUT == 3) {
-    if (rs.kc == nullptr && tn * HB >= 4 * rs.H) return;         // queries only (uniform over the workgroup)
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
       seq[p] = max(gid[p], 0) / rs.N;
