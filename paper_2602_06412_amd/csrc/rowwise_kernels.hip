@@ -300,9 +300,9 @@ __global__ __launch_bounds__(kRowThreads) void add_rmsnorm_vec_kernel(const bf16
   }
 }
 // The same for rows of 2049 .. 4096 columns and at most four planes: a launch of few rows is a chain of memory latencies, in the
-// kernel above row count, first chunk, second chunk, gain.  Here all of a thread's two chunks (x, planes, gain) are asked for
-// before the row count is looked at; rows between it and the bound lie in the buffers.  Same sums in the same order.  Two
-// add + norm launches of 4096 columns, four planes: 16 rows 13.6 -> 12.4 us, 128 rows 16.8 -> 15.6, 512 rows 25.7 -> 24.8.
+// kernel above row count, first chunk, second chunk, gain.  Here the loads of both of a thread's chunks are under way
+// together behind the row count.  Same sums in the same order.  Two add + norm launches of 4096 columns, four
+// planes: 16 rows 13.6 -> 12.4 us, 128 rows 16.8 -> 15.6, 512 rows 25.7 -> 24.8.
 template <bool ADD, bool TILED>
 __global__ __launch_bounds__(kRowThreads) void add_rmsnorm_row_kernel(const bf16_t* src, bf16_t* x, const float* __restrict__ delta,
                                                                       int S, size_t sstride, const int32_t* __restrict__ m_dev,
@@ -310,6 +310,7 @@ __global__ __launch_bounds__(kRowThreads) void add_rmsnorm_row_kernel(const bf16
                                                                       bf16_t* __restrict__ h) {
   __shared__ float sh[kRowThreads / 64];
   const int r = blockIdx.x;
+  if (r >= *m_dev) return;
   bf16_t* xr = x + (size_t)r * d;
   const bf16_t* sr = ADD ? xr : src + (size_t)r * d;
   int c[2];
@@ -329,7 +330,6 @@ __global__ __launch_bounds__(kRowThreads) void add_rmsnorm_row_kernel(const bf16
     }
     gv[j] = *reinterpret_cast<const bf16x8_t*>(gain + c[j]);
   }
-  if (r >= *m_dev) return;
   float v[2][8], ssq = 0.f;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
@@ -691,7 +691,7 @@ int slk_embed_rmsnorm(hipStream_t s, int dtype, const void* emb, const int32_t* 
 // 15.3, 801 rows 15.7 / 16.5, 857 rows 16.1 / 15.6, 1024 rows 15.9 / 15.6, 1280 rows 20.6 / 17.8, 2000 rows 18.3 / 10.5.
 constexpr int kWaveRowsMin = 832;
 // two chunks per thread; more planes than four would take the registers of a second workgroup per SIMD.  Past two workgroups
-// per CU the launch is no chain of latencies any more: the two norms of a block, early loads against the kernel above, us, 528
+// per CU the launch is no chain of latencies any more: the two norms of a block, this kernel against the one above, us, 528
 // rows 26.9 / 27.9, 560 rows 28.8 / 29.5, 600 rows 30.7 / 29.7, 700 rows 30.6 / 29.7, 740 rows 31.2 / 30.2.
 constexpr int kRowKernelMax = 576;
 static bool row_kernel_takes(int m_upper, int d, int S) {
