@@ -1,6 +1,7 @@
-// The projection GEMM of launches bounded by more than 32 rows (inside a layer more than 512, where gemm_wavek.hip takes
-// the shape): one TM x 256 output tile per workgroup and CU, TM any multiple of 32 from 64 to 256.  Four waves, one per SIMD; each owns all TM rows of 64 columns (up to 256
-// accumulator registers), so a weight fragment is wanted by exactly one wave.
+// The projection GEMM of launches bounded by more than 32 rows (where gemm_wavek.hip takes a layer's shape: Q|K|V of more than
+// 384 rows, the other projections of more than 512, gate|up not of 961 to 1024): one TM x 256 output tile per workgroup and CU, TM
+// any multiple of 32 from 64 to 256.  Four waves, one per SIMD; each owns all TM rows of 64 columns (up to 256 accumulator
+// registers), so a weight fragment is wanted by exactly one wave.
 //
 //  * Weights go global -> registers: a ring of DB k-tiles (32 deep) of B fragments per wave.  They never touch LDS,
 //    which the four waves need for the activations: with both operands in LDS and eight (TM/2) x 64 waves (the form
@@ -186,9 +187,9 @@ __device__ __forceinline__ void ring_tile(
   };
   Frag af[R];
 
-  // Touches (TCH; share > 2 row tiles that hold rows run side by side on one XCD and want the same weights): a lane reads four bytes of a
-  // 128-byte line, a wave the 64 lines of 32 columns and four k-tiles, two such chunks ahead of the loads of the k-tile it is
-  // issued in.  Chunk p's 8 column blocks are dealt over the 4 share waves; t_x counts down to this wave's next one.
+  // Touches (TCH; share > 2 row tiles that hold rows run side by side on one XCD and want the same weights): a lane reads four
+  // bytes of a 128-byte line, a wave the 64 lines of 32 columns and four k-tiles, two such chunks ahead of the loads of the k-tile
+  // it is issued in.  Chunk p's 8 column blocks are dealt over the 4 share waves; t_x counts down to this wave's next one.
   // They count in vmcnt like any load and make its waits, which ignore them, no looser.  Kernels of their own: in the others the
   // few scalar instructions cost (gate|up of 700 rows, 160-row tiles that never touch, 124 -> 130 us).
   const uint32_t t_voff = (uint32_t)lane * 128u;

@@ -1,5 +1,6 @@
-// The layer's projections of at most 512 rows.  Up to 256 rows one workgroup per column slice takes ALL rows, its four waves a
-// quarter of the reduction each; above, see the second kernel.
+// The layer's projections of at most 512 rows (Q|K|V: 384; gate|up also 961 to 1024).  Up to 256 rows one workgroup per column
+// slice takes ALL rows (Q|K|V from 81 rows on: half of them), its four waves a quarter of the reduction each; above, see the second
+// kernel.
 //
 // What bounds these launches is the number of 128-byte lines a CU has under way: about 256 of them, whatever the depth of
 // the rings, so a line that misses L2 (625 ns) moves at 52 GB/s per CU, one that hits at 125, a mixture at 45 to 68.  A tile
@@ -8,7 +9,7 @@
 //
 //  * With the waves along k a wave wants every activation fragment of its k-tiles and nobody else does: fragments go
 //    global -> LDS -> registers inside the wave, with no barrier in the k loop, each read from LDS once.
-//  * Weights go global -> registers, each fragment wanted by one wave of the whole launch (non-temporal).  They are asked for
+//  * Weights go global -> registers, each fragment wanted by one wave per row tile (non-temporal).  They are asked for
 //    in one go at the end of a k-step, together with nothing else: hits queue behind misses, so misses in bursts cost one
 //    latency per 256 lines (8 misses and 20 hits a burst 68 GB/s per CU, 2 and 4: 55).
 //  * At the end the four waves' sums meet in LDS, 64 rows at a time; row block 4 p + w is added up and finished by
