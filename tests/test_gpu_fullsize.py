@@ -31,8 +31,10 @@ def test_c2_full_size_sampled_rows():
         rng = np.random.default_rng(0)
         prev_rows = {}
         active = np.arange(N)
-        # 820 and 300 rows: a ragged last row tile; 420 and 213 rows: gate|up tiles of 224 and 128 rows under the fused
-        # SwiGLU, Q|K|V once as tiles of 96 rows under the fused RoPE and once split over k
+        # 1024 rows: gate|up by 2 x 2 waves in two rounds, the rest on ring tiles; 820: ring tiles, a ragged last one; 420: Q|K|V on
+        # ring tiles of 96 rows with RoPE, gate|up, Out and down by 2 x 2 waves; 300: Q|K|V with the waves along k, the rest by
+        # 2 x 2; 213 and 16: all with the waves along k.  (Ring tiles under SwiGLU at few rows and Q|K|V split over k:
+        # tests/test_gpu_ring_layers.py.)
         for t, M in ((1, 1024), (2, 820), (3, 420), (4, 300), (5, 213), (6, 16)):
             # the active set only ever shrinks (locks are permanent): nested subsets
             active = active if M == len(active) else active[wl.active_positions(50 + M, len(active), M)]
