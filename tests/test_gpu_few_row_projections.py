@@ -9,6 +9,8 @@ from paper_2602_06412_amd import binding as B
 from paper_2602_06412_amd import workloads as wl
 from tests.gpu_util import DEV, weights_to_device
 from tests.layer_check import check_layers
+from tests.test_gpu_loose_bounds import check_bound
+from tests.test_wavek_forms_cpu import GATE_UP, PLANES, form
 
 pytestmark = pytest.mark.gpu
 
@@ -25,10 +27,7 @@ OUT_DOWN = wl.Shape("few-rows-planes", 1, 2688, 16, 128, 2048, 1056, "bf16")
     (1, 300, [80]),
     (1, 300, [81]),
     (1, 300, [97]),
-    # every slot: V leaves in whole blocks.  (At two sequences of 64 slots the oracle's two evaluations happen to lie 2.5e-3
-    # apart in the median, and this library's rows 3.5e-3 from the first, by these launches and by the ring kernel's alike;
-    # at 128 slots both are 3.3e-3 to 3.7e-3 and 2.4e-3.)
-    (2, 128, [128, 128]),
+    (2, 128, [128, 128]),       # every slot: V leaves in whole blocks
     (3, 120, [103, 1, 120]),
     (1, 300, [256]),
     (1, 300, [257]),            # gate|up: two row tiles and 2 x 2 waves
@@ -38,6 +37,34 @@ OUT_DOWN = wl.Shape("few-rows-planes", 1, 2688, 16, 128, 2048, 1056, "bf16")
 ])
 def test_qkv_and_gate_up(batch, N, rows):
     check_layers(QKV_GATE_UP, batch, N, rows)
+
+
+def test_whole_blocks_of_short_sequences():
+    """64 slots each: one oracle evaluation is too few to tell how far two correct ones lie apart (tests/layer_check.py)."""
+    check_layers(QKV_GATE_UP, 2, 64, [64, 64], evaluations=8)
+
+
+# 5 trips of the deepest operand ring and 10 of the shorter one in Q|K|V, gate|up and down, 2 and 4 in Out; a reduction that is
+# not a power of two; column slices that leave CUs idle.  One row count for each height of each form.
+LONG = wl.Shape("few-rows-long", 1, 2560, 32, 128, 10240, 1056, "bf16")
+LONG_ROWS = [9, 31, 48, 62, 80, 95, 112, 127, 153, 192, 221, 256, 300, 381, 440, 512]
+
+
+@pytest.mark.parametrize("rows", LONG_ROWS)
+def test_every_height_over_several_trips(rows):
+    check_layers(LONG, 1, rows + 9, [rows], evaluations=2)
+
+
+@pytest.mark.parametrize("d,heads,d_ff", [
+    (128, 2, 7808),             # gate|up in two steps of 64 (the other projections need k in whole 128s)
+    (384, 2, 7808),             # six
+    (2560, 2, 512),             # Out in one step, down in two
+    (2560, 6, 1280),            # three, the ring's depth, and five
+])
+def test_two_by_two_waves_in_few_steps(d, heads, d_ff):
+    takes = [form(GATE_UP, 300, d_ff, d), form(PLANES, 300, d, heads * 128), form(PLANES, 300, d, d_ff)]
+    assert [f[0] for f in takes] == ([2, 0, 0] if d < 2560 else [0, 2, 2])
+    check_layers(wl.Shape("few-steps", 1, d, heads, 128, d_ff, 1056, "bf16"), 1, 300, [300], evaluations=2)
 
 
 @pytest.mark.parametrize("rows", [[961], [1024]])
@@ -50,23 +77,11 @@ def test_out_and_down(rows):
     check_layers(OUT_DOWN, 1, 260 if rows[0] <= 256 else 520, rows)
 
 
-def test_device_side_row_count_below_the_bound():
-    """m < m_upper: the rows below it as with the tight bound, the rest of the output untouched; in the two-row-tile form
-    the second tile lies wholly beyond it."""
-    sess = B.Session(QKV_GATE_UP, weights_to_device(wl.make_weights(QKV_GATE_UP, seed=1)), 1, 300)
-    x = wl.gaussian_rows(1, 200, QKV_GATE_UP.d_model, "bf16").to(DEV)
-    idx = torch.arange(0, 300, dtype=torch.int32, device=DEV)[:200].contiguous()
-    for m in (0, 40, 199):
-        md = torch.tensor([m], dtype=torch.int32, device=DEV)
-        outs = []
-        for _ in range(2):
-            out = torch.full_like(x, -7.0)
-            B.sl_forward_layers(sess.ctx, x, out, idx, md, 200, 0, 1, sess.workspace)
-            torch.cuda.synchronize()
-            outs.append(out)
-        assert torch.equal(outs[0], outs[1]) and bool((outs[0][m:] == -7.0).all())
-        assert bool(torch.isfinite(outs[0][:m].float()).all()) and not bool((outs[0][:m] == -7.0).all(1).any())
-    sess.close()
+@pytest.mark.parametrize("m,m_upper", [(0, 200), (40, 200), (199, 200), (260, 300), (299, 300)])
+def test_device_side_row_count_below_the_bound(m, m_upper):
+    """The rows below it and their K and V as with the tight bound, the rest of the output and of the cache untouched; in
+    forms of two row tiles the second lies wholly or partly beyond the count."""
+    check_bound(QKV_GATE_UP, 300, m, m_upper)
 
 
 @pytest.mark.parametrize("locked", [60, 150])

@@ -1,6 +1,7 @@
 """Host-side check of the projection launch plans (no GPU): every kernel form that a LLaDA-8B-shaped
-projection can reach for some number of active rows is one that tests/test_gpu_linear.py launches, with
-NaN-filled outputs, on the GPU.  The weight-stream kernel's forms (rows per block, columns per tile,
+projection can reach through sl_linear_forward for some number of active rows (in a layer too, where the few-row
+kernels do not take the launch; theirs: tests/test_wavek_forms_cpu.py) is one that tests/test_gpu_linear.py
+launches, with NaN-filled outputs, on the GPU.  The weight-stream kernel's forms (rows per block, columns per tile,
 k-splits) matter most: its operand ring is filled by inline-assembly loads with hand-counted waits, so a
 form no test reaches would be a form nobody has seen produce every partial sum."""
 import pytest

@@ -1,6 +1,6 @@
 """Which form a layer's projection of few rows is launched in (no GPU; not part of the C ABI, called by its C++ name): every form
-covers its rows, is one that is compiled, and, at the LLaDA-8B shapes, is one that the GPU tests of the file below launch with
-several trips of its operand rings (each form is a kernel of its own, with its own hand-counted waits)."""
+covers its rows, is one that is compiled, and, at the LLaDA-8B shapes, is one that tests/test_gpu_few_row_projections.py launches
+with several trips of its operand rings (each form is a kernel of its own, with its own hand-counted waits)."""
 import ctypes as C
 
 import pytest
@@ -44,3 +44,22 @@ def test_limits():
     assert form(QKV, 384, H, D)[0] == 1 and form(QKV, 385, H, D)[0] == 0
     assert [form(GATE_UP, mu, DFF, D)[0] for mu in (256, 257, 512, 513, 960, 961, 1024)] == [1, 2, 2, 0, 0, 2, 2]
     assert [form(PLANES, mu, D, DFF)[0] for mu in (256, 257, 512, 513)] == [1, 2, 2, 0]
+
+
+def test_every_reachable_form_runs_its_steady_loop_in_the_gpu_tests():
+    from tests.test_gpu_few_row_projections import LONG, LONG_ROWS
+    d, hd, dff = LONG.d_model, LONG.n_heads * 128, LONG.d_ff
+    tested = {}
+    for name, (projection, width, k) in {"q|k|v": (QKV, LONG.n_heads, d), "gate|up": (GATE_UP, dff, d), "out": (PLANES, d, hd),
+                                         "down": (PLANES, d, dff)}.items():
+        for mu in LONG_ROWS:
+            kernel, blocks, cols, _ = form(projection, mu, width, k)
+            if kernel:
+                step, depth = (128, 4 if blocks <= 8 else 2) if kernel == 1 else (64, 3)
+                trips = k // (4 if projection == PLANES else 1) // step / depth
+                key = (projection, kernel, blocks, cols)
+                tested[key] = max(trips, tested.get(key, 0))
+    for name, (projection, width, k) in LLADA.items():
+        for mu in range(1, 1100):
+            kernel, blocks, cols, _ = form(projection, mu, width, k)
+            assert kernel == 0 or tested.get((projection, kernel, blocks, cols), 0) >= 3, (name, mu, kernel, blocks, cols)
