@@ -550,7 +550,7 @@ static int launch_wave22(hipStream_t s, const void* A, const void* Wp, const int
   static unsigned long long lds_ok = 0;
   SL_ALLOW_DYNAMIC_LDS(lds_ok, kern, sh);
   const int tiles_m = sl_cdiv(mu, NA * 16), tiles_n = sl_cdiv(n, 32 * NBK);
-  hipLaunchKernelGGL(kern, dim3(8 * sl_cdiv(tiles_n, 8) * tiles_m * splits), dim3(256), sh, s, (const bf16_t*)A, (const bf16_t*)Wp, n, k,
+  hipLaunchKernelGGL(kern, dim3(8 * sl_cdiv(tiles_n, 8) * (tiles_m == 3 ? 4 : tiles_m) * splits), dim3(256), sh, s, (const bf16_t*)A, (const bf16_t*)Wp, n, k,
                      splits, m_dev, mu, Cf, (bf16_t*)Cb, ldc, tiles_n);
   SL_LAUNCH_CHECK();
   return SL_OK;

@@ -14,12 +14,12 @@ def _tile(wg, row_tiles, splits):
     return tuple(out)
 
 
-@pytest.mark.parametrize("launched,tiles_n,splits", [(2, 128, 1), (4, 128, 1), (4, 115, 1), (2, 32, 4), (2, 21, 4), (2, 1, 1)])
+@pytest.mark.parametrize("launched,tiles_n,splits", [(2, 128, 1), (3, 128, 1), (4, 128, 1), (4, 115, 1), (2, 32, 4), (2, 21, 4), (2, 1, 1)])
 @pytest.mark.parametrize("row_tiles", [1, 2, 3, 4])
 def test_order(launched, tiles_n, splits, row_tiles):
     if row_tiles > launched:
         pytest.skip("no more row tiles than the launch has")
-    grid = 8 * -(-tiles_n // 8) * launched * splits
+    grid = 8 * -(-tiles_n // 8) * (4 if launched == 3 else launched) * splits
     tiles = [_tile(wg, row_tiles, splits) for wg in range(grid)]
     working = [tm < row_tiles and tn < tiles_n for tm, tn, _ in tiles]
     got = [t for t, w in zip(tiles, working) if w]
