@@ -610,11 +610,18 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
   };
   FragA k0[16], v0[16], k1[16], v1[16];       // two register sets, the next tile is requested before the current one is used
   int t = t_lo + wave;                        // this wave's tiles: wave, wave + 4, ..
-  int b = 0, row0 = -1, row_end = 0;
+  int row0 = -1, row_end = 0;
+  // workgroups past the rows leave (uniformly) before their first load: under a bound far above the row count most do (200 rows of
+  // N = 512 bounded by 512: 12.3 us with a key tile asked for ahead of the test, 11.4 behind it)
   if (B == 1) {
     // one sequence: its row range is known without a search, LDS and a barrier (16 rows, N = 512 10.3 -> 9.9 us; 457 rows,
-    // N = 1024 29.8 -> 28.5)
-    if ((int)blockIdx.y * QTT < M) { row0 = blockIdx.y * QTT; row_end = M; }
+    // N = 1024 29.8 -> 28.5).  The loads in each branch: behind both, the address of a sequence that is not a constant costs 0.2 us
+    // (24 rows of N = 512 7.9 -> 8.1; two sequences of 2048, split 15.7 -> 16.2).
+    if ((int)blockIdx.y * QTT >= M) return;
+    row0 = blockIdx.y * QTT;
+    row_end = M;
+    head_of(0);
+    if (t < t_hi) load_kv(t, k0, v0);
   } else {
     if (tid <= B) {
       int lo = 0, hi = M;
@@ -626,19 +633,17 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
       cu[tid] = lo;
     }
     __syncthreads();
-    int tile = blockIdx.y;
+    int b = 0, tile = blockIdx.y;
     for (; b < B; ++b) {
       const int cnt = cu[b + 1] - cu[b];
       const int nt = (cnt + QTT - 1) / QTT;
       if (tile < nt) { row0 = cu[b] + tile * QTT; row_end = cu[b + 1]; break; }
       tile -= nt;
     }
+    if (row0 < 0) return;
+    head_of(b);
+    if (t < t_hi) load_kv(t, k0, v0);
   }
-  // uniform across the workgroup, and before its first load: under a bound far above the row count most workgroups leave here
-  // (200 rows of N = 512 bounded by 512: 12.3 us with a key tile asked for ahead of this line, 11.4 behind it)
-  if (row0 < 0) return;
-  head_of(b);
-  if (t < t_hi) load_kv(t, k0, v0);
 
   // every wave holds the same 32 queries: lane = query (lane & 31), dims ks*16 + (lane>>5)*8 .. +7
   const int my_row = row0 + (lane & 31);
