@@ -134,6 +134,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
     else asm volatile("" : "+v"(acc[a][b]));
   };
 
+  const int count = *m_dev;                           // asked for ahead of the loads, waited for behind them
 #pragma unroll
   for (int u = 0; u < RD; ++u) {
     fetch_b(u);
@@ -141,17 +142,18 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
     for (int a = 0; a < NA; ++a) fetch_a(u, a);
     pa += K_STEP;
   }
-  const int M = min(*m_dev, m_upper);
+  const int M = min(count, m_upper);
   if (M <= 0) {                                       // uniform; nothing of the prologue's may still be on its way
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     return;
   }
   // 16-row blocks past the count: from here on the tile's first block in their place (lines that are on their way anyway), so
   // that a bound above the count costs no more reads (one block at N = 512, bound 160: 1 row 136 -> 115 us, 33 rows 141 -> 124; bound
-  // 256: no row 141 -> 32, 33 rows 161 -> 143; tight bounds the same within 0.5 %)
+  // 256: no row 141 -> 32, 33 rows 161 -> 143; tight bounds the same within 0.5 %).  Not in a second row tile, which would run ahead of
+  // the first and leave it without the weight lines both want (200 rows bounded by 384 212 -> 216)
 #pragma unroll
   for (int a = 1; a < NA; ++a)
-    if (m0 + a * 16 >= M) a_voff[a] = a_voff[0];
+    if (tm == 0 && a * 16 >= M) a_voff[a] = a_voff[0];
 #pragma unroll
   for (int a = 0; a < NA; ++a)
 #pragma unroll
