@@ -526,8 +526,10 @@ static bool stream_weights(int tiles_m, int tiles_n, int splits, int tm) {
 // 576 .. 2048 rows) gain 6 % on average, up to 23 %.  Four tiles of 128 rows gain as well (n = 3072 .. 16384, k = 2048 .. 12288: 4 % on
 // average, Q|K|V of 512 rows 58 -> 51), other heights and fewer sharers do not: Q|K|V of 544 rows (128 x 5) 63.5 -> 66, 704 rows
 // (160 x 5) 73 -> 75, 960 rows (192 x 5) 83.5 -> 86, gate|up of 512 rows (256 x 2) 84 -> 92; 96-row tiles of four or five gain 2 to 4 us in
-// Q|K|V of 390 to 430 rows and the launches behind them lose it.  Tall tiles have fewer lines to wait for per MFMA and gain only in
-// long reductions: 160 x 8 k = 512 to 2048 14.3 -> 14.9 to 36.3 -> 36.9, Out of 1280 rows 40.7 -> 41.7; down of 1280 rows 103 -> 101.
+// Q|K|V of 390 to 430 rows and the launches behind them lose it.  Tall tiles have fewer lines to wait for per MFMA and lose over
+// short reductions (160 x 8, n = 8192, k = 512 and 1024 14.3 -> 14.9 and 21.4 -> 22.9); over longer ones they gain or are equal within the
+// runs of one size (down of 1280 rows 103 -> 101; Out of 1280 rows alone 40.4 -> 41.3, but six layers of 600 rows bounded by 1280 2655 ->
+// 2642).
 // 128-row tiles over a short reduction, split so that they fill the chip, lose too: n = 4096, k = 2048 in two of 1024 rows 22.7 -> 23.9,
 // n = 7168 of 416 rows 21.1 -> 22.4, n = 3072 in four 15.8 -> 16.7; with fewer workgroups they gain (n = 5120 in two, 512 rows 21.5 ->
 // 20.7), and so do shorter tiles (n = 2048 in two, 64 x 14 16.7 -> 15.0).
@@ -535,7 +537,7 @@ static bool stream_weights(int tiles_m, int tiles_n, int splits, int tm) {
 static bool touches_weights(int tiles_m, int tiles_n, int splits, int tm, int k) {
   if (ring_slots(tiles_m, tiles_n, splits) > 256) return false;
   if (tm == 128 && splits > 1 && k / splits <= 1024 && tiles_m * tiles_n * splits >= 192) return false;
-  if (tm == 160) return tiles_m >= 6 && k / splits >= 4096;
+  if (tm == 160) return tiles_m >= 6 && k / splits >= 2048;
   return tm < 160 && (tiles_m >= 6 || (tm == 128 && tiles_m == 4));
 }
 

@@ -19,7 +19,7 @@ def _touches(m_upper, n, k):
     one_round = 8 * tiles * -(-columns // 8) * splits <= 256
     short = height == 128 and splits > 1 and k // splits <= 1024 and tiles * columns * splits >= 192
     if height == 160:
-        return kernel == 1 and one_round and tiles >= 6 and k // splits >= 4096
+        return kernel == 1 and one_round and tiles >= 6 and k // splits >= 2048
     return kernel == 1 and one_round and not short and height < 160 and (tiles >= 6 or (height == 128 and tiles == 4))
 
 
