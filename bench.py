@@ -13,9 +13,9 @@ recompute beside the active-row ratio (the algorithmic work kept, Sec. 2.4).  Th
 configs 4 (B=1, N=2048) and 3 (B=1, N=512) and, on one layer, config 2 (N=1024, M in
 {1024,512,256,64,16}).  All inputs are seeded, synthetic and resident in HBM before any timed region.
 
-    python bench.py [--gpus 1] [--steps K] [--warmup W] [--only c5,c4,c3,c2] [--points P]
+    python bench.py [--gpus 1] [--steps K] [--warmup W] [--only c5,c4,c3,c2] [--points P] [--details FILE]
 
-Prints one JSON line."""
+Prints one JSON line of a few KB; the per-kernel split of every sampled step goes to --details."""
 import argparse
 import json
 import os
@@ -208,6 +208,7 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-probes", action="store_true", help="skip the peak and clock probes")
     ap.add_argument("--c2-sweep", type=str, default="1024,512,256,64,16")
+    ap.add_argument("--details", type=str, default=None, help="file for the whole result: every sample with its per-kernel split")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run one 1 GiB elementwise copy kernel, for scaling rocprofv3 FETCH_SIZE/WRITE_SIZE")
     args = ap.parse_args()
@@ -231,7 +232,7 @@ def main():
     d, V = shape.d_model, shape.vocab
 
     w = wl.make_weights(shape, args.seed, device="cuda")
-    log = lambda row: print(json.dumps(row), file=sys.stderr, flush=True)
+    log = lambda row: print("%5d rows  %.3f ms" % (row["M"], row["ms"]), file=sys.stderr, flush=True)
 
     # ---- headline: config 5, every row active, exactly K timed steps after W warm-up steps ----
     r5 = ScheduleRunner("c5", w, args.seed)
@@ -320,7 +321,19 @@ def main():
         "sweep": sweeps,
         "c2": c2,
     }
-    print(json.dumps(out))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(short(out)))
+
+
+def short(out):
+    """The result line: of each sampled step its row count and latency, of each list of samples no more.  Whoever keeps only the
+    end of a run's output (16 KB, say) then still has the whole line."""
+    out = dict(out, sweep={k: [{f: r[f] for f in ("M", "ms")} for r in rows] for k, rows in out["sweep"].items()})
+    if out["c2"]:
+        out["c2"] = dict(out["c2"], sweep=[{f: r[f] for f in ("M", "ms", "gemm_mfma_frac", "gemm_hbm_frac")} for r in out["c2"]["sweep"]])
+    return out
 
 
 def cpu_baseline(shape, w, seed):

@@ -25,3 +25,20 @@ def test_traffic_is_read_from_the_committed_counter_summary():
 def test_more_than_one_gpu_is_refused_with_a_message():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode != 0 and "one GPU" in r.stderr
+
+
+def test_the_result_line_is_short():
+    """With as many samples as the default run makes, each with its per-kernel split, the line stays below 8 KB, headline first."""
+    sys.path.insert(0, ROOT)
+    import json
+    import bench
+    row = {"M": 8192, "M_over_N": 1.0, "ms": 90.1234, "rows_per_s": 90909, "kernels": {str(i): {"us": 1234.5, "mfma_frac": 0.1234, "hbm_frac": 0.1234}
+                                                                                      for i in range(10)},
+           "gemm_mfma_frac": 0.1234, "gemm_hbm_frac": 0.1234}
+    out = {"metric": "m" * 80, "value": 1.0, "config": {"workload": "w" * 900}, "roofline": {"per_kernel": row["kernels"], "note": "n" * 700},
+           "cpu_baseline": {"sample": "s" * 1200}, "achievable": {"note": "a" * 500}, "latency_vs_active_fraction": {k: "l" * 400 for k in "abc"},
+           "sweep": {k: [row] * 7 for k in ("c5", "c4", "c3")}, "c2": {"workload": "x" * 100, "sweep": [row] * 5}}
+    line = json.dumps(bench.short(out))
+    assert len(line) < 8000 and line.startswith('{"metric"') and len(json.dumps(out)) > 2 * len(line)
+    assert bench.short(dict(out, c2=None))["c2"] is None
+    assert [r["M"] for r in bench.short(out)["sweep"]["c4"]] == [8192] * 7
