@@ -358,11 +358,12 @@ template <int OUT, int NA, int NBK> struct W22Cfg {
 // XCD x owns the column tiles 8 c + x; the row tiles and splits of one column tile follow each other.  Only row tiles that hold
 // rows are counted, so the workgroups without work are the last ones: an XCD's workgroups go to its four shader engines in turn,
 // and with every fourth one working they all went to one engine's eight CUs, two to a CU (gate|up of 16 rows bounded by 1024 116 us,
-// of 300 rows 128; now 62 and 76).  Three count as four: 600 rows 131 us, in threes 138.
+// of 300 rows 128; now 62 and 76).  Three count as four: 600 rows 131 us, in threes 138.  One to four row tiles and a power of two of
+// splits: every workgroup waits for the count before its first load, so no divisions behind it.
 struct W22Tile { int tm, tn, split; };
 __host__ __device__ inline W22Tile w22_tile(int wg, int row_tiles, int splits) {
-  const int per = row_tiles == 3 ? 4 : row_tiles, xcd = wg & 7, j = wg >> 3, group = j / per;
-  return W22Tile{j % per, group / splits * 8 + xcd, group % splits};
+  const int sh = row_tiles > 2 ? 2 : row_tiles - 1, xcd = wg & 7, j = wg >> 3, group = j >> sh;
+  return W22Tile{j & ((1 << sh) - 1), (group >> __builtin_ctz(splits)) * 8 + xcd, group & (splits - 1)};
 }
 void slk_wave22_tile(int wg, int row_tiles, int splits, int* out) {     // for tests
   const W22Tile t = w22_tile(wg, row_tiles, splits);
@@ -552,6 +553,7 @@ static int launch_wave22(hipStream_t s, const void* A, const void* Wp, const int
   static unsigned long long lds_ok = 0;
   SL_ALLOW_DYNAMIC_LDS(lds_ok, kern, sh);
   const int tiles_m = sl_cdiv(mu, NA * 16), tiles_n = sl_cdiv(n, 32 * NBK);
+  if (tiles_m > 4 || splits < 1 || (splits & (splits - 1))) return SL_EINVAL;         // what w22_tile numbers
   hipLaunchKernelGGL(kern, dim3(8 * sl_cdiv(tiles_n, 8) * (tiles_m == 3 ? 4 : tiles_m) * splits), dim3(256), sh, s, (const bf16_t*)A, (const bf16_t*)Wp, n, k,
                      splits, m_dev, mu, Cf, (bf16_t*)Cb, ldc, tiles_n);
   SL_LAUNCH_CHECK();
