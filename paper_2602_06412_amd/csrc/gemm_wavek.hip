@@ -11,7 +11,12 @@
 //    global -> LDS -> registers inside the wave, with no barrier in the k loop, each read from LDS once.
 //  * Weights go global -> registers, each fragment wanted by one wave per row tile (non-temporal).  They are asked for
 //    in one go at the end of a k-step, together with nothing else: hits queue behind misses, so misses in bursts cost one
-//    latency per 256 lines (8 misses and 20 hits a burst 68 GB/s per CU, 2 and 4: 55).
+//    latency per 256 lines (8 misses and 20 hits a burst 68 GB/s per CU, 2 and 4: 55).  A barrier ahead of them keeps the four
+//    waves' bursts one: without it the waves drift apart and the lines of one hold up the hits of the others (a block at N = 512,
+//    us: 64 rows 117.7 -> 115.9, 96 133.6 -> 128.6, 128 147.1 -> 136.9, 160 166.0 -> 150.6, 224 185.1 -> 168.5, 256 190.8 ->
+//    177.4; with one to three row blocks nearly all lines are misses, 40 rows 107.3 -> 107.7, and there is none).  Four to eight
+//    row blocks ask for two steps' weights together (80 rows 125.2 -> 123.9, 128 139.9 -> 137.5); with more the rings hold no more
+//    than two steps of activations (224 rows equal, 256 179.0 -> 184.1).
 //  * At the end the four waves' sums meet in LDS, 64 rows at a time; row block 4 p + w is added up and finished by
 //    wave w.
 #include "mfma_tile.h"
@@ -23,14 +28,17 @@ constexpr int WK_STEP = WK_K * WK_WAVES;              // k per step of the workg
 // NA 16-row blocks, NBK 16-column blocks; RD steps of a wave in its rings.
 template <int OUT, int NA, int NBK> struct WkCfg {
   static constexpr int RD = NA <= 8 ? 4 : 2;
+  static constexpr int BURST = NA >= 4 && NA <= 8 ? 2 : 1;                  // steps whose weights are asked for together
   static constexpr int P = NA + NBK;                  // loads per wave and step
+  // loads younger than those of an even, an odd step when it begins, in the order in which the loop issues them
+  static constexpr int EVEN = BURST == 2 ? 3 * NBK + 2 * NA : (RD - 1) * P, ODD = BURST == 2 ? 2 * NBK + 3 * NA : (RD - 1) * P;
   static constexpr int R = NA < 4 ? NA : 4;           // activation fragments read ahead
   static constexpr int RING = WK_WAVES * RD * NA * 1024;
   static constexpr int PASS = WK_WAVES * (WK_WAVES - 1) * NBK * 1024;       // sums that change waves in one pass of 64 rows
   static constexpr int BUFS = NA > 4 ? 2 : 1;
   static constexpr int EPI = BUFS * PASS + (OUT == 3 ? WK_WAVES * 16 * VUNIT * 2 : 0);
   static constexpr int LDS = RING > EPI ? RING : EPI;
-  static_assert((RD - 1) * P <= 63 && LDS <= 160 * 1024, "wait counts, LDS");
+  static_assert(EVEN <= 63 && ODD <= 63 && (BURST == 1 || RD == 4) && LDS <= 160 * 1024, "wait counts, LDS");
 };
 
 template <int V> struct WkInt { static constexpr int value = V; };
@@ -51,7 +59,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp, int n, int k, int splits, const int32_t* __restrict__ m_dev,
     int m_upper, float* __restrict__ Cf, bf16_t* __restrict__ Cb, size_t ldc, int tiles_m, int tiles_n, RopeScatter rs) {
   typedef WkCfg<OUT, NA, NBK> WC;
-  constexpr int RD = WC::RD, P = WC::P, R = WC::R, HB = NBK / 2;
+  constexpr int RD = WC::RD, P = WC::P, R = WC::R, HB = NBK / 2, BURST = WC::BURST;
   extern __shared__ Frag lds[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int g4 = lane >> 4, row_in = lane & 15;
@@ -137,10 +145,11 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
   const int count = *m_dev;                           // asked for ahead of the loads, waited for behind them
 #pragma unroll
   for (int u = 0; u < RD; ++u) {
-    fetch_b(u);
+    if (BURST == 1) fetch_b(u);
 #pragma unroll
     for (int a = 0; a < NA; ++a) fetch_a(u, a);
     pa += K_STEP;
+    if (BURST == 2 && u % 2 == 1) { fetch_b(u - 1); fetch_b(u); }
   }
   const int M = min(count, m_upper);
   if (M <= 0) {                                       // uniform; nothing of the prologue's may still be on its way
@@ -180,16 +189,19 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
     wk_landed<decltype(younger)::value>(fb[v]);
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto weights = [&](int v) {
-    fetch_b(v);
+  auto weights = [&](int v) {                         // a burst, of slot v and those before it
+    if constexpr (NA >= 4) asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+    for (int b = BURST - 1; b >= 0; --b) fetch_b(v - b);
     __builtin_amdgcn_sched_barrier(0);
   };
   for (int s = 0; s + RD < steps; s += RD) {
 #pragma unroll
     for (int u = 0; u < RD; ++u) {
-      landed(WkInt<(RD - 1) * P>{}, u);
+      if (u % 2 == 0) landed(WkInt<WC::EVEN>{}, u);
+      else landed(WkInt<WC::ODD>{}, u);
       step(WkInt<1>{}, u, u);
-      weights(u);
+      if (u % BURST == BURST - 1) weights(u);
     }
   }
   // the flat ids of the rows this lane will finish (none past the row count: the array may end there), behind the last
@@ -204,12 +216,12 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
     }
   }
   // the last RD steps fetch nothing; after the last wait no load is in flight
-  landed(WkInt<(RD - 1) * P>{}, 0);
+  landed(WkInt<WC::EVEN>{}, 0);
   step(WkInt<0>{}, 0, 0);
-  landed(WkInt<(RD - 2) * P>{}, 1);
+  landed(WkInt<BURST == 2 ? 2 * P : (RD - 2) * P>{}, 1);
   step(WkInt<0>{}, 1, 1);
   if constexpr (RD == 4) {
-    landed(WkInt<P>{}, 2);
+    landed(WkInt<BURST == 2 ? NBK : P>{}, 2);
     step(WkInt<0>{}, 2, 2);
     landed(WkInt<0>{}, 3);
     step(WkInt<0>{}, 3, 3);
