@@ -278,11 +278,29 @@ extern "C" int sl_workspace_bytes(const sl_ctx* ctx, int32_t batch, int32_t n_se
 // ---- the restricted forward ------------------------------------------------------------------------
 #define SL_TRY(expr) do { const int rc_ = (expr); if (rc_ != SL_OK) return rc_; } while (0)
 
+// Whether layer l's row-wise work goes into its projections (fp32 layers of few tiles): decided by sizes and alignment
+// of all its launches together, so that the launches around them agree on who norms the rows.
+static bool layer_fused(const sl_ctx* ctx, const Workspace& ws, int mu, int l) {
+  const sl_config& c = ctx->cfg;
+  if (ctx->use_mfma || c.dtype != SL_F32) return false;
+  const sl_layer_weights& L = ctx->layers[l];
+  const int d = c.d_model, hd = c.n_heads * c.d_head;
+  uintptr_t bits = (uintptr_t)ws.x;
+  for (const void* p : {L.attn_norm, L.wq, L.wk, L.wv, L.wo, L.ffn_norm, L.w_gate, L.w_up, L.w_down}) bits |= (uintptr_t)p;
+  return slk_generic_fused(mu, hd, d, 3, bits) && slk_generic_fused(mu, d, hd, 1, bits) && slk_generic_fused(mu, c.d_ff, d, 1, bits) &&
+         slk_generic_fused(mu, d, c.d_ff, 1, bits);
+}
+static bool head_fused(const sl_ctx* ctx, const Workspace& ws, int mu, const void* logits) {
+  return layer_fused(ctx, ws, mu, ctx->cfg.n_layers - 1) &&
+         slk_generic_fused(mu, ctx->cfg.vocab, ctx->cfg.d_model, 1, (uintptr_t)ctx->plain.final_norm | (uintptr_t)ctx->plain.lm_head | (uintptr_t)logits);
+}
+
 // Layers [lo, hi) on the rows held in ws.x, with ws.h = RMSNorm(ws.x) by layer lo's attention
 // gain on entry.  On exit ws.x is the block output and ws.h its RMSNorm by the next gain
-// (layer hi's attention gain, or the final gain after the last layer).
+// (layer hi's attention gain, or the final gain after the last layer), unless need_h is false: then the rows' norm may be
+// left to whoever reads ws.x.
 static int run_layers(sl_ctx* ctx, hipStream_t s, const Workspace& ws, const int32_t* active_idx,
-                      const int32_t* m_dev, int mu, int lo, int hi) {
+                      const int32_t* m_dev, int mu, int lo, int hi, bool need_h) {
   const sl_config& c = ctx->cfg;
   const int dt = c.dtype, d = c.d_model, H = c.n_heads, dh = c.d_head, hd = H * dh, dff = c.d_ff;
   const void* rope_tab = ctx->kv;
@@ -293,8 +311,22 @@ static int run_layers(sl_ctx* ctx, hipStream_t s, const Workspace& ws, const int
       SL_TRY(sl_mfma_layer(ctx, s, l, ws.x, ws.h, ws.q, ws.o, ws.a, ws.f32, ws.attn, active_idx, m_dev, mu, next_gain));
       continue;
     }
-    // Q, K, V projections of the active rows (fp32 results side by side)
     const void* qkv[3] = {L.wq, L.wk, L.wv};
+    if (layer_fused(ctx, ws, mu, l)) {
+      const bool probe = ctx->probe_read_only;
+      SL_RUN(ctx, s, SL_PROF_GEMM_QKV, slk_generic_norm_qkv_rope(s, ws.x, L.attn_norm, c.rms_eps, qkv, m_dev, mu, H, dh, d, active_idx,
+                                                                 ctx->n_seq, ctx->n_pad, rope_tab, ws.q, probe ? nullptr : kv_k_layer(ctx, l),
+                                                                 probe ? nullptr : kv_v_layer(ctx, l)));
+      SL_RUN(ctx, s, SL_PROF_ATTENTION, slk_attention_generic(s, dt, ws.q, kv_k_layer(ctx, l), kv_v_layer(ctx, l), active_idx, m_dev, mu, H,
+                                                              dh, ctx->n_seq, ctx->n_pad, ws.o));
+      SL_RUN(ctx, s, SL_PROF_GEMM_OUT, slk_generic_residual(s, ws.o, L.wo, m_dev, mu, d, hd, ws.x));
+      SL_RUN(ctx, s, SL_PROF_GEMM_GATE_UP, slk_generic_norm_swiglu(s, ws.x, L.ffn_norm, c.rms_eps, L.w_gate, L.w_up, m_dev, mu, dff, d, ws.a));
+      SL_RUN(ctx, s, SL_PROF_GEMM_DOWN, slk_generic_residual(s, ws.a, L.w_down, m_dev, mu, d, dff, ws.x));
+      if (l + 1 < hi ? !layer_fused(ctx, ws, mu, l + 1) : need_h)      // whoever comes next reads the normed rows
+        SL_RUN(ctx, s, SL_PROF_ADD_NORM, slk_rmsnorm(s, dt, ws.x, nullptr, m_dev, mu, d, next_gain, c.rms_eps, ws.h, 0));
+      continue;
+    }
+    // Q, K, V projections of the active rows (fp32 results side by side)
     SL_RUN(ctx, s, SL_PROF_GEMM_QKV, slk_gemm_generic(s, dt, ws.h, qkv, 3, m_dev, mu, hd, d, ws.f32, nullptr, nullptr, 3 * (size_t)hd));
     // RoPE; live K/V overwrite the rows' own cache slots (locked slots are never touched)
     SL_RUN(ctx, s, SL_PROF_ROPE_KV, slk_rope_kv_write(s, dt, ws.f32, 1, 0, active_idx, m_dev, mu, H, dh, ctx->n_seq, ctx->n_pad, rope_tab, ws.q,
@@ -339,7 +371,7 @@ extern "C" int sl_forward_layers(sl_ctx* ctx, void* stream, const void* x_in, vo
   if (direct) ws.x = (char*)x_out;
   SL_TRY(slk_rmsnorm(s, c.dtype, x_in, in == (uintptr_t)ws.x ? nullptr : ws.x, m_dev, m_upper, c.d_model,
                      ctx->layers[layer_lo].attn_norm, c.rms_eps, ws.h, ctx->use_mfma));
-  SL_TRY(run_layers(ctx, s, ws, active_idx, m_dev, m_upper, layer_lo, layer_hi));
+  SL_TRY(run_layers(ctx, s, ws, active_idx, m_dev, m_upper, layer_lo, layer_hi, false));
   return direct ? SL_OK : slk_copy_rows(s, c.dtype, ws.x, x_out, m_dev, m_upper, c.d_model);
 }
 
@@ -536,13 +568,17 @@ static int step_impl(sl_ctx* ctx, void* stream, int32_t* tokens, uint8_t* masked
   // block input of the active rows + first LN
   SL_RUN(ctx, s, SL_PROF_EMBED_NORM, slk_embed_rmsnorm(s, c.dtype, ctx->plain.emb, tokens, active_idx, m_dev, m_upper, c.d_model, c.vocab,
                            ctx->layers[0].attn_norm, c.rms_eps, ws.x, ws.h, ctx->use_mfma));
-  SL_TRY(run_layers(ctx, s, ws, active_idx, m_dev, m_upper, 0, c.n_layers));
   // logits of the active rows, written to their rows of this step's posterior buffer
   void *cur = nullptr, *prev = nullptr;
   sl_logits_ptr(ctx, t, &cur);
   sl_logits_ptr(ctx, t - 1, &prev);
+  const bool norm_in_head = head_fused(ctx, ws, m_upper, cur);
+  SL_TRY(run_layers(ctx, s, ws, active_idx, m_dev, m_upper, 0, c.n_layers, !norm_in_head));
   if (ctx->use_mfma)
     SL_RUN(ctx, s, SL_PROF_LM_HEAD, sl_mfma_lm_head(ctx, s, ws.h, active_idx, m_dev, m_upper, cur));
+  else if (norm_in_head)
+    SL_RUN(ctx, s, SL_PROF_LM_HEAD, slk_generic_norm_linear(s, ws.x, ctx->plain.final_norm, c.rms_eps, ctx->plain.lm_head, m_dev, m_upper,
+                                                            c.vocab, c.d_model, cur, active_idx));
   else
     SL_RUN(ctx, s, SL_PROF_LM_HEAD, slk_gemm_generic(s, c.dtype, ws.h, &ctx->plain.lm_head, 1, m_dev, m_upper, c.vocab, c.d_model, nullptr, cur,
                             active_idx, c.vocab));
@@ -626,7 +662,7 @@ extern "C" int sl_unlock_probe(sl_ctx* ctx, void* stream, const int32_t* tokens,
                            ctx->layers[0].attn_norm, c.rms_eps, ws.x, ws.h, ctx->use_mfma));
   // queries only: keys and values of every slot come from the cache, nothing is written
   ctx->probe_read_only = true;
-  const int rc = run_layers(ctx, s, ws, probe_idx, m_dev, m_upper, 0, c.n_layers);
+  const int rc = run_layers(ctx, s, ws, probe_idx, m_dev, m_upper, 0, c.n_layers, true);
   ctx->probe_read_only = false;
   SL_TRY(rc);
   // proxy logits, packed in probe order

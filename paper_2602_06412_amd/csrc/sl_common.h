@@ -293,6 +293,17 @@ int slk_gemm_generic(hipStream_t s, int dtype, const void* A, const void* const*
                      int m_upper, int n, int k, float* C_f32, void* C_T, const int32_t* out_row_map, size_t ldc);
 int slk_gemm_generic_swiglu(hipStream_t s, int dtype, const void* A, const void* w_gate, const void* w_up,
                             const int32_t* m_dev, int m_upper, int dff, int k, void* a);
+// fp32 layers of few tiles without row-wise launches: whether a launch takes its part (bits: the pointers it reads and writes
+// in 16-byte pieces, or'ed); RMSNorm of x ahead of the product, RoPE and the cache scatter or the residual add behind it
+int slk_generic_fused(int m_upper, int n, int k, int nm, uintptr_t bits);
+int slk_generic_norm_qkv_rope(hipStream_t s, const void* x, const void* gain, float eps, const void* const* w, const int32_t* m_dev,
+                              int m_upper, int H, int dh, int k, const int32_t* active_idx, int N, int n_pad, const void* rope_tab,
+                              void* q, void* kc, void* vc);
+int slk_generic_residual(hipStream_t s, const void* A, const void* w, const int32_t* m_dev, int m_upper, int n, int k, void* x);
+int slk_generic_norm_swiglu(hipStream_t s, const void* x, const void* gain, float eps, const void* w_gate, const void* w_up,
+                            const int32_t* m_dev, int m_upper, int dff, int k, void* a);
+int slk_generic_norm_linear(hipStream_t s, const void* x, const void* gain, float eps, const void* w, const int32_t* m_dev, int m_upper,
+                            int n, int k, void* y, const int32_t* out_row_map);
 // attention_generic.hip
 int slk_attention_generic(hipStream_t s, int dtype, const void* q, const void* kc, const void* vc,
                           const int32_t* active_idx, const int32_t* m_dev, int m_upper,
