@@ -568,13 +568,20 @@ __global__ __launch_bounds__(256, 3) void attention_trio_kernel(const bf16_t* __
 // flash recurrence on its own tiles, and merge their (O, max, sum) through LDS, so there is no
 // partial-result buffer and no merge launch.  K and V fragments go global -> registers directly (the
 // cache layouts make every MFMA fragment of a tile one contiguous 1 KiB block: no LDS staging, no
-// barrier in the loop), the next tile's fragments are requested before the current tile is computed.
+// barrier in the loop).  The next tile is asked for fragment by fragment while this one is computed, each into the registers
+// of a fragment that has been read for the last time: 32 loads in a row fill the CU's load queue and the wave stands at
+// their issue (a tile's compute takes 1.65 us and its loads 1.1; in a row 2.1 us, so 1.75).  One block, 32 queries a
+// workgroup: 16 rows of N = 512 96.0 -> 95.4 us, 64 rows of N = 2048 121.7 -> 120.7.
 // Same fragment layouts as the kernels above; P is carried as two halves (hi + lo, 22 bits: the
 // matrix pipe idles here anyway).
 // SPLIT: as above, for sequences whose tiles are too many for four waves; each workgroup leaves its merged sums to
 // attention_merge_kernel.
-constexpr int QTT = 32;          // queries per workgroup of the thin kernel
-template <bool SPLIT>
+// QG = 2: 64 queries, two waves for each 32 of them, which take the key tiles in turn: one round of workgroups where 32
+// queries make two (the two waves that want a tile ask for it together).  One block, both changes: 300 rows of N = 512 206.1 -> 202.9
+// us, 457 rows of N = 1024 264.2 -> 259.1, 512 rows 263.4 -> 257.4, 300 rows of 4 x 800 219.0 -> 210.8.
+template <int V> struct AtInt { static constexpr int value = V; };
+constexpr int QTT = 32;          // queries per workgroup of the thin kernel (QG = 1)
+template <bool SPLIT, int QG>
 __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __restrict__ q,
                                                                 const bf16_t* __restrict__ kc,
                                                                 const bf16_t* __restrict__ vc,
@@ -587,7 +594,10 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
   __shared__ int cu[kMaxBatch + 2];
   constexpr int TILE_F = KT * DH / 8;
   const int M = min(*m_dev, m_upper);
+  static_assert(QG == 1 || (QG == 2 && !SPLIT), "forms");
+  constexpr int KG = 4 / QG, QW = QTT * QG;  // waves that share 32 queries; queries per workgroup
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int kg_w = wave / QG, qg_w = wave % QG;
   const int hh = blockIdx.x;
   const int t_lo = SPLIT ? blockIdx.z * tiles_per_split : 0;
   const int t_hi = SPLIT ? min(n_pad / KT, t_lo + tiles_per_split) : n_pad / KT;
@@ -597,8 +607,9 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
     kg = reinterpret_cast<const FragA*>(kc + head_base) + lane;
     vg = reinterpret_cast<const FragA*>(vc + head_base) + (lane >> 5) * DH + (lane & 31);
   };
+  FragA kf[16], vf[16];
   // fragments of tile t: K block (kb, ks) at (kb*8 + ks)*64 + lane, V^T block (st, mb) at (2*st + lane>>5)*DH + mb*32 + lane&31
-  auto load_kv = [&](int t, FragA (&kf)[16], FragA (&vf)[16]) {
+  auto load_kv = [&](int t) {
     const FragA* kt = kg + (size_t)t * TILE_F;
     const FragA* vt = vg + (size_t)t * TILE_F;
 #pragma unroll
@@ -608,8 +619,7 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
 #pragma unroll
       for (int mb = 0; mb < 4; ++mb) vf[st * 4 + mb] = vt[(2 * st) * DH + mb * 32];
   };
-  FragA k0[16], v0[16], k1[16], v1[16];       // two register sets, the next tile is requested before the current one is used
-  int t = t_lo + wave;                        // this wave's tiles: wave, wave + 4, ..
+  int t = t_lo + kg_w;                        // this wave's tiles: every KG-th
   int row0 = -1, row_end = 0;
   // workgroups past the rows leave (uniformly) before their first load: under a bound far above the row count most do (200 rows of
   // N = 512 bounded by 512: 12.3 us with a key tile asked for ahead of the test, 11.4 behind it)
@@ -617,11 +627,11 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
     // one sequence: its row range is known without a search, LDS and a barrier (16 rows, N = 512 10.3 -> 9.9 us; 457 rows,
     // N = 1024 29.8 -> 28.5).  The loads in each branch: behind both, the address of a sequence that is not a constant costs 0.2 us
     // (24 rows of N = 512 7.9 -> 8.1; two sequences of 2048, split 15.7 -> 16.2).
-    if ((int)blockIdx.y * QTT >= M) return;
-    row0 = blockIdx.y * QTT;
+    if ((int)blockIdx.y * QW >= M) return;
+    row0 = blockIdx.y * QW;
     row_end = M;
     head_of(0);
-    if (t < t_hi) load_kv(t, k0, v0);
+    if (t < t_hi) load_kv(t);
   } else {
     if (tid <= B) {
       int lo = 0, hi = M;
@@ -636,17 +646,17 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
     int b = 0, tile = blockIdx.y;
     for (; b < B; ++b) {
       const int cnt = cu[b + 1] - cu[b];
-      const int nt = (cnt + QTT - 1) / QTT;
-      if (tile < nt) { row0 = cu[b] + tile * QTT; row_end = cu[b + 1]; break; }
+      const int nt = (cnt + QW - 1) / QW;
+      if (tile < nt) { row0 = cu[b] + tile * QW; row_end = cu[b + 1]; break; }
       tile -= nt;
     }
     if (row0 < 0) return;
     head_of(b);
-    if (t < t_hi) load_kv(t, k0, v0);
+    if (t < t_hi) load_kv(t);
   }
 
-  // every wave holds the same 32 queries: lane = query (lane & 31), dims ks*16 + (lane>>5)*8 .. +7
-  const int my_row = row0 + (lane & 31);
+  // a wave holds 32 queries: lane = query (lane & 31), dims ks*16 + (lane>>5)*8 .. +7
+  const int my_row = row0 + qg_w * QTT + (lane & 31);
   const int ld_row = my_row < row_end ? my_row : row_end - 1;
   FragA qf[8];
   {
@@ -662,14 +672,19 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
   float m_run = -INFINITY, l_run = 0.f;
   const float sc = 1.4426950408889634f / sqrtf((float)DH);   // log2(e) / sqrt(d_h)
 
-  auto tile_step = [&](int t, const FragA (&kf)[16], const FragA (&vf)[16]) {
-    f32x16 sv[2];
+  // One tile; `more`: this wave's next one is asked for on the way, K's fragments behind the scores that read them, V's behind the
+  // products.
+  auto tile_step = [&](auto more, int t) {
+    constexpr bool MORE = decltype(more)::value;
+    const FragA* kt_n = kg + (size_t)(t + KG) * TILE_F;
+    const FragA* vt_n = vg + (size_t)(t + KG) * TILE_F;
+    f32x16 sv[2], zero;
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
+    for (int v = 0; v < 16; ++v) zero[v] = 0.f;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) sv[kb][v] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) sv[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb * 8 + ks], qf[ks], sv[kb], 0, 0, 0);
+    for (int i = 0; i < 16; ++i) {
+      const int kb = i & 1, ks = i >> 1;
+      sv[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb * 8 + ks], qf[ks], ks ? sv[kb] : zero, 0, 0, 0);
     }
     if ((t + 1) * KT > N) {                  // register v of block kb is key 32*kb + 8*(v/4) + 4*(lane>>5) + v%4
       const int kbase = t * KT + 4 * (lane >> 5);
@@ -699,44 +714,52 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc_o[i][v] *= alpha;
     }
+    // the second half's probabilities are made between the MFMAs of the first half's product: one wave per SIMD has nobody
+    // else to keep the matrix pipe busy under its vector work
     PFrag ph[4], pl[4];
     float psum = 0.f;
+    auto pair = [&](int kb, int v) {
+      const float pa = __builtin_amdgcn_exp2f(fmaf(sv[kb][v], sc, -mb_));
+      const float pb = __builtin_amdgcn_exp2f(fmaf(sv[kb][v + 1], sc, -mb_));
+      psum += pa + pb;
+      const uint32_t hw = pack_half2(pa, pb);
+      const uint32_t lw = pack_half2_rest(pa, pb, hw);
+      ph[2 * kb + (v >> 3)][(v & 7) >> 1] = hw;
+      pl[2 * kb + (v >> 3)][(v & 7) >> 1] = lw;
+    };
+    auto product = [&](int i) {              // MFMA i of the tile's 32
+      const int st = i >> 3, mb = i & 3;
+      acc_o[mb] = mfma_pv(vf[st * 4 + mb], (i >> 2) & 1 ? pl[st] : ph[st], acc_o[mb]);
+    };
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int v = 0; v < 16; v += 2) {
+      if constexpr (MORE) { kf[v] = kt_n[v * 64]; kf[v + 1] = kt_n[(v + 1) * 64]; }
+      pair(0, v);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
-      for (int v = 0; v < 16; v += 2) {
-        const float pa = __builtin_amdgcn_exp2f(fmaf(sv[kb][v], sc, -mb_));
-        const float pb = __builtin_amdgcn_exp2f(fmaf(sv[kb][v + 1], sc, -mb_));
-        psum += pa + pb;
-        const uint32_t hw = pack_half2(pa, pb);
-        const uint32_t lw = pack_half2_rest(pa, pb, hw);
-        ph[2 * kb + (v >> 3)][(v & 7) >> 1] = hw;
-        pl[2 * kb + (v >> 3)][(v & 7) >> 1] = lw;
-      }
+    for (int v = 0; v < 16; v += 2) {
+      product(v);
+      pair(1, v);
+      product(v + 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     l_run = l_run * alpha + psum;
     m_run = m_new;
 #pragma unroll
-    for (int st = 0; st < 4; ++st) {
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-        acc_o[mb] = mfma_pv(vf[st * 4 + mb], ph[st], acc_o[mb]);
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-        acc_o[mb] = mfma_pv(vf[st * 4 + mb], pl[st], acc_o[mb]);
+    for (int i = 16; i < 32; ++i) {
+      product(i);
+      if constexpr (MORE) {                  // fragment i - 16 has been read for the last time
+        vf[i - 16] = vt_n[2 * ((i - 16) >> 2) * DH + (i & 3) * 32];
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   };
   {
-    while (t < t_hi) {
-      if (t + 4 < t_hi) load_kv(t + 4, k1, v1);
-      tile_step(t, k0, v0);
-      t += 4;
-      if (t >= t_hi) break;
-      if (t + 4 < t_hi) load_kv(t + 4, k0, v0);
-      tile_step(t, k1, v1);
-      t += 4;
-    }
+    for (; t + KG < t_hi; t += KG) tile_step(AtInt<1>{}, t);
+    if (t < t_hi) tile_step(AtInt<0>{}, t);
   }
-  // merge the four waves' partial results: wave w finishes dims 32 w .. 32 w + 31.  Lanes stand side by side in LDS: a
+  // merge the partial results of the KG waves of 32 queries: wave g of them finishes dims 128 / KG * g ..  Lanes stand side by side in LDS: a
   // lane's 64 sums in a row put all lanes on the same banks, 2 us of the launch (16 rows, N = 512: 10.1 -> 8.3 us).
   float4* sh_o = reinterpret_cast<float4*>(lds);                     // [4 waves][16 pieces][64 lanes]
   float2* sh_ml = reinterpret_cast<float2*>(sh_o + 4 * 16 * 64);   // [4][64]
@@ -752,20 +775,21 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
     sh_ml[wave * 64 + lane] = make_float2(m_run * sc, l_tot);         // reference in the exp2 domain (-inf: no tile)
   }
   __syncthreads();
-  float2 ml[4];
+  constexpr int NG = 4 * QG;                  // pieces of four dims
+  float2 ml[KG];
   float mx = -INFINITY;
 #pragma unroll
-  for (int z = 0; z < 4; ++z) { ml[z] = sh_ml[z * 64 + lane]; mx = fmaxf(mx, ml[z].x); }
-  float num[16], den = 0.f;
+  for (int z = 0; z < KG; ++z) { ml[z] = sh_ml[(z * QG + qg_w) * 64 + lane]; mx = fmaxf(mx, ml[z].x); }
+  float num[4 * NG], den = 0.f;
 #pragma unroll
-  for (int v = 0; v < 16; ++v) num[v] = 0.f;
+  for (int v = 0; v < 4 * NG; ++v) num[v] = 0.f;
 #pragma unroll
-  for (int z = 0; z < 4; ++z) {
+  for (int z = 0; z < KG; ++z) {
     const float w = __builtin_amdgcn_exp2f(ml[z].x - mx);
     den = fmaf(w, ml[z].y, den);
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float4 pz = sh_o[(z * 16 + wave * 4 + g) * 64 + lane];
+    for (int g = 0; g < NG; ++g) {
+      const float4 pz = sh_o[((z * QG + qg_w) * 16 + kg_w * NG + g) * 64 + lane];
       num[4 * g] = fmaf(w, pz.x, num[4 * g]);
       num[4 * g + 1] = fmaf(w, pz.y, num[4 * g + 1]);
       num[4 * g + 2] = fmaf(w, pz.z, num[4 * g + 2]);
@@ -789,11 +813,11 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
   const float inv = 1.0f / den;
   if (my_row < row_end) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < NG; ++g) {
       bf16x4 w4;
 #pragma unroll
       for (int e = 0; e < 4; ++e) w4[e] = (__bf16)(num[4 * g + e] * inv);
-      *reinterpret_cast<bf16x4*>(o + afrag_index(my_row, hh * DH + wave * 32 + 8 * g + 4 * (lane >> 5), H * DH)) = w4;
+      *reinterpret_cast<bf16x4*>(o + afrag_index(my_row, hh * DH + kg_w * (8 * NG) + 8 * g + 4 * (lane >> 5), H * DH)) = w4;
     }
   }
 }
@@ -856,13 +880,16 @@ static bool attention_use_trio(int blocks) { return blocks > 256; }
 // short (16 tiles).  Longer sequences: up to one workgroup per CU, with as many splits as that leaves room for (a wave
 // keeps one tile at least) and at most 32 tiles per split.  Measured as one block of the layer, B = 1, the pipelined
 // kernel with its splits against this one, N = 2048: 32 rows 124.6 against 119.6 us (Z = 8), 64 rows 153.0 / 145.8 (4),
-// 128 rows 180.7 / 171.6 (2), 256 rows 228.7 / 225.4 (1); beyond one workgroup per CU it loses (384 rows 260.3 / 267.8).
-// N = 4096, 64 rows 157.9 / 151.3 (4); 256 rows (64 tiles per split) 237.5 / 237.7.
+// 128 rows 180.7 / 171.6 (2), 256 rows 228.7 / 225.4 (1); N = 4096, 64 rows 157.9 / 151.3 (4), 256 rows (64 tiles per split)
+// 237.5 / 237.7.  Up to two workgroups per CU it then takes 64 queries each, where 32 tiles or fewer are to be walked: N = 2048,
+// 320 rows 226.1 / 224.1, 384 rows 237.7 / 234.9, 480 rows 276.2 / 273.4, N = 1100, 300 rows 218.0 / 212.4.  Beyond that it loses to the
+// three-per-CU kernel: N = 1024, 600 rows 317.5 / 326.6, 800 rows 369.5 / 377.8.
+constexpr int kThinOneRound = 256, kThinPairs = 512;          // workgroups of 32 queries
 static int attention_thin_splits(int m_upper, int B, int H, int n_pad, int* tiles_per_split) {
   const int n_tiles = n_pad / KT, blocks = (sl_cdiv(m_upper, QTT) + B - 1) * H;
   *tiles_per_split = n_tiles;
-  if (n_tiles <= 16) return blocks <= 512 ? 1 : 0;
-  if (blocks > 256) return 0;
+  if (n_tiles <= 16) return blocks <= kThinPairs ? 1 : 0;
+  if (blocks > kThinOneRound) return blocks <= kThinPairs && n_tiles <= 32 ? 1 : 0;
   const int Z = 256 / blocks < sl_cdiv(n_tiles, 4) ? 256 / blocks : sl_cdiv(n_tiles, 4);
   *tiles_per_split = sl_cdiv(n_tiles, Z);
   return *tiles_per_split <= 32 ? sl_cdiv(n_tiles, *tiles_per_split) : 0;
@@ -914,12 +941,20 @@ int slk_attention_mfma(hipStream_t s, const void* q, const void* kc, const void*
   const int Zt = attention_thin_splits(m_upper, B, H, n_pad, &tps);
   if (Zt == 1 || (Zt > 1 && scratch)) {
     const size_t sh_thin = (size_t)(4 * 64 * 64 + 4 * 64 * 2) * sizeof(float);
-    static unsigned long long lds_thin[2] = {0, 0};
-    SL_ALLOW_DYNAMIC_LDS(lds_thin[0], attention_thin_kernel<false>, sh_thin);
-    SL_ALLOW_DYNAMIC_LDS(lds_thin[1], attention_thin_kernel<true>, sh_thin);
+    static unsigned long long lds_thin[3] = {0, 0, 0};
+    SL_ALLOW_DYNAMIC_LDS(lds_thin[0], (attention_thin_kernel<false, 1>), sh_thin);
+    SL_ALLOW_DYNAMIC_LDS(lds_thin[1], (attention_thin_kernel<true, 1>), sh_thin);
+    SL_ALLOW_DYNAMIC_LDS(lds_thin[2], (attention_thin_kernel<false, 2>), sh_thin);
+    if (Zt == 1 && (sl_cdiv(m_upper, QTT) + B - 1) * H > kThinOneRound) {
+      hipLaunchKernelGGL((attention_thin_kernel<false, 2>), dim3(H, sl_cdiv(m_upper, 2 * QTT) + B - 1, 1), dim3(256), sh_thin, s,
+                         (const bf16_t*)q, (const bf16_t*)kc, (const bf16_t*)vc, active_idx, m_dev, m_upper, B, H, N, n_pad, (bf16_t*)o, tps,
+                         (float*)nullptr, (float*)nullptr);
+      SL_LAUNCH_CHECK();
+      return SL_OK;
+    }
     float* po = Zt > 1 ? scratch : nullptr;
     float* pml = Zt > 1 ? scratch + (size_t)Zt * m_upper * H * DH : nullptr;
-    hipLaunchKernelGGL(Zt > 1 ? attention_thin_kernel<true> : attention_thin_kernel<false>,
+    hipLaunchKernelGGL((Zt > 1 ? attention_thin_kernel<true, 1> : attention_thin_kernel<false, 1>),
                        dim3(H, sl_cdiv(m_upper, QTT) + B - 1, Zt), dim3(256), sh_thin, s, (const bf16_t*)q, (const bf16_t*)kc,
                        (const bf16_t*)vc, active_idx, m_dev, m_upper, B, H, N, n_pad, (bf16_t*)o, tps, po, pml);
     SL_LAUNCH_CHECK();
