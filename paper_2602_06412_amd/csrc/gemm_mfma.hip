@@ -373,7 +373,10 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(
       if (row >= M) continue;
       const float g = acc[0][0][v];
       const float u = NBW == 1 ? up_sh[((wave >> 1) * 16 + v) * 64 + lane] : acc[0][NBW - 1][v];
-      Cb[afrag_index(row, c, (int)ldc)] = (bf16_t)silu_mul(g, u);
+      const float gs[1] = {g}, us[1] = {u};
+      float y[1];
+      silu_mul(gs, us, y);
+      Cb[afrag_index(row, c, (int)ldc)] = (bf16_t)y[0];
     }
     return;
   }

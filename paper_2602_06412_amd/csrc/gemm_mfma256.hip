@@ -392,12 +392,14 @@ __device__ __forceinline__ void ring_tile(
 #pragma unroll
     for (int a = 0; a < NA; ++a) {
       const int row = m0 + a * 16 + row_in;
-      f32x4 v[2];
+      float gs[8], us[8], y[8];
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[b][e] = silu_mul(acc[a][b][e], acc[a][b + 2][e]);
-      const uint4 o = pack_swap(v[0], v[1]);
+      for (int e = 0; e < 8; ++e) {
+        gs[e] = acc[a][e >> 2][e & 3];
+        us[e] = acc[a][(e >> 2) + 2][e & 3];
+      }
+      silu_mul(gs, us, y);
+      const uint4 o = pack_swap(f32x4{y[0], y[1], y[2], y[3]}, f32x4{y[4], y[5], y[6], y[7]});
       if (row < M && c < (n >> 1)) *reinterpret_cast<uint4*>(Cb + afrag_index(row, c, (int)ldc)) = o;
     }
     return;

@@ -294,12 +294,19 @@ __global__ __launch_bounds__(256, 1) void gemm_wavek_kernel(
         if (row < M && col < n) *reinterpret_cast<f32x4*>(Cf + ((size_t)split * m_upper + row) * ldc + col) = c[b];
       }
     } else if constexpr (OUT == 2) {
+      float gs[4 * HB], us[4 * HB], y[4 * HB];
+#pragma unroll
+      for (int e = 0; e < 4 * HB; ++e) {
+        gs[e] = c[e >> 2][e & 3];
+        us[e] = c[(e >> 2) + HB][e & 3];
+      }
+      silu_mul(gs, us, y);
 #pragma unroll
       for (int b = 0; b < HB; ++b) {
         const int col = (tn * HB + b) * 16 + 4 * g4;
         bf16x4 v;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (bf16_t)silu_mul(c[b][e], c[b + HB][e]);
+        for (int e = 0; e < 4; ++e) v[e] = (bf16_t)y[b * 4 + e];
         if (row < M && col < (n >> 1)) *reinterpret_cast<bf16x4*>(Cb + afrag_index(row, col, (int)ldc)) = v;
       }
     } else {
@@ -544,12 +551,19 @@ __global__ __launch_bounds__(256, 1) void gemm_wave22_kernel(
           if (row < M && col < n) *reinterpret_cast<f32x4*>(Cf + ((size_t)split * m_upper + row) * ldc + col) = c[h][b];
         }
       } else if constexpr (OUT == 2) {
+        float gs[4 * HB], us[4 * HB], y[4 * HB];
+#pragma unroll
+        for (int e = 0; e < 4 * HB; ++e) {
+          gs[e] = c[h][e >> 2][e & 3];
+          us[e] = c[h][(e >> 2) + HB][e & 3];
+        }
+        silu_mul(gs, us, y);
 #pragma unroll
         for (int b = 0; b < HB; ++b) {
           const int col = ((tn * 2 + cg) * HB + b) * 16 + 4 * g4;
           bf16x4 v;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = (bf16_t)silu_mul(c[h][b][e], c[h][b + HB][e]);
+          for (int e = 0; e < 4; ++e) v[e] = (bf16_t)y[b * 4 + e];
           if (row < M && col < (n >> 1)) *reinterpret_cast<bf16x4*>(Cb + afrag_index(row, col, (int)ldc)) = v;
         }
       }

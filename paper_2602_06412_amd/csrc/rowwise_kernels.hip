@@ -187,8 +187,7 @@ __global__ __launch_bounds__(256) void swiglu_vec_kernel(const float* __restrict
 #pragma unroll
     for (int e = 0; e < 8; ++e) { g[e] += t[e]; u[e] += v[e]; }
   }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = silu_mul(g[e], u[e]);
+  silu_mul(g, u, o);
   st8(a + afrag_index(r, c, dff), o);
 }
 
