@@ -8,7 +8,7 @@
 // gate|up projection of 224 rows (70 us), 224 x 96 on 256 CUs 2.6 MB, of which only 0.8 come from HBM.
 //
 //  * With the waves along k a wave wants every activation fragment of its k-tiles and nobody else does: fragments go
-//    global -> LDS -> registers inside the wave, with no barrier in the k loop, each read from LDS once.
+//    global -> LDS -> registers inside the wave, with no barrier on their way, each read from LDS once.
 //  * Weights go global -> registers, each fragment wanted by one wave per row tile (non-temporal).  They are asked for
 //    in one go at the end of a k-step, together with nothing else: hits queue behind misses, so misses in bursts cost one
 //    latency per 256 lines (8 misses and 20 hits a burst 68 GB/s per CU, 2 and 4: 55).  A barrier ahead of them keeps the four
