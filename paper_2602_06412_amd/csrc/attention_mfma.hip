@@ -576,12 +576,15 @@ __global__ __launch_bounds__(256, 3) void attention_trio_kernel(const bf16_t* __
 // matrix pipe idles here anyway).
 // SPLIT: as above, for sequences whose tiles are too many for four waves; each workgroup leaves its merged sums to
 // attention_merge_kernel.
-// QG = 2: 64 queries, two waves for each 32 of them, which take the key tiles in turn: one round of workgroups where 32
-// queries make two (the two waves that want a tile ask for it together).  One block, both changes: 300 rows of N = 512 206.1 -> 202.9
-// us, 457 rows of N = 1024 264.2 -> 259.1, 512 rows 263.4 -> 257.4, 300 rows of 4 x 800 219.0 -> 210.8.
+// PAIRS: 64 queries, two waves for each 32 of them: one round of workgroups where 32 queries make two (the two waves that want
+// a tile ask for it together).  One block, this and the loads inside the tile together: 300 rows of N = 512 206.1 -> 202.9
+// us, 457 rows of N = 1024 264.2 -> 259.1, 512 rows 263.4 -> 257.4, 300 rows of 4 x 800 219.0 -> 210.8.  A wave makes two states
+// of every fourth tile, one behind the other, where it could make one of every second: so a row's sums are made of the same four
+// states whatever form its launch takes, and its result does not depend on the bound or on the other rows, bit by bit (equal
+// times: 457 rows of N = 1024 258.7 before and 258.6 after, 300 rows of N = 512 200.9 and 201.8, 512 rows 243.3 and 243.8).
 template <int V> struct AtInt { static constexpr int value = V; };
-constexpr int QTT = 32;          // queries per workgroup of the thin kernel (QG = 1)
-template <bool SPLIT, int QG>
+constexpr int QTT = 32;          // queries per workgroup of the thin kernel; PAIRS: 64
+template <bool SPLIT, bool PAIRS>
 __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __restrict__ q,
                                                                 const bf16_t* __restrict__ kc,
                                                                 const bf16_t* __restrict__ vc,
@@ -590,14 +593,12 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
                                                                 int H, int N, int n_pad, bf16_t* __restrict__ o,
                                                                 int tiles_per_split, float* __restrict__ part_o,
                                                                 float* __restrict__ part_ml) {
-  extern __shared__ FragA lds[];             // the merge: partial O [4 waves][16][64 lanes] float4 | (m, l) [4][64]
+  extern __shared__ FragA lds[];             // the merge: partial O [4 states, PAIRS 8][16][64 lanes] float4 | (m, l) [4, 8][64]
   __shared__ int cu[kMaxBatch + 2];
   constexpr int TILE_F = KT * DH / 8;
   const int M = min(*m_dev, m_upper);
-  static_assert(QG == 1 || (QG == 2 && !SPLIT), "forms");
-  constexpr int KG = 4 / QG, QW = QTT * QG;  // waves that share 32 queries; queries per workgroup
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int kg_w = wave / QG, qg_w = wave % QG;
+  static_assert(!(PAIRS && SPLIT), "forms");
+  const int tid = threadIdx.x, wave = PAIRS ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6, lane = tid & 63;
   const int hh = blockIdx.x;
   const int t_lo = SPLIT ? blockIdx.z * tiles_per_split : 0;
   const int t_hi = SPLIT ? min(n_pad / KT, t_lo + tiles_per_split) : n_pad / KT;
@@ -619,7 +620,9 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
 #pragma unroll
       for (int mb = 0; mb < 4; ++mb) vf[st * 4 + mb] = vt[(2 * st) * DH + mb * 32];
   };
-  int t = t_lo + kg_w;                        // this wave's tiles: every KG-th
+  constexpr int qw = PAIRS ? 2 * QTT : QTT;   // queries per workgroup
+  constexpr bool two = PAIRS;                 // 64: two states per wave, waves 2 z + g for queries 32 g ..
+  int t = t_lo + (two ? wave >> 1 : wave);    // this wave's first tile
   int row0 = -1, row_end = 0;
   // workgroups past the rows leave (uniformly) before their first load: under a bound far above the row count most do (200 rows of
   // N = 512 bounded by 512: 12.3 us with a key tile asked for ahead of the test, 11.4 behind it)
@@ -627,8 +630,8 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
     // one sequence: its row range is known without a search, LDS and a barrier (16 rows, N = 512 10.3 -> 9.9 us; 457 rows,
     // N = 1024 29.8 -> 28.5).  The loads in each branch: behind both, the address of a sequence that is not a constant costs 0.2 us
     // (24 rows of N = 512 7.9 -> 8.1; two sequences of 2048, split 15.7 -> 16.2).
-    if ((int)blockIdx.y * QW >= M) return;
-    row0 = blockIdx.y * QW;
+    if ((int)blockIdx.y * qw >= M) return;
+    row0 = blockIdx.y * qw;
     row_end = M;
     head_of(0);
     if (t < t_hi) load_kv(t);
@@ -646,8 +649,8 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
     int b = 0, tile = blockIdx.y;
     for (; b < B; ++b) {
       const int cnt = cu[b + 1] - cu[b];
-      const int nt = (cnt + QW - 1) / QW;
-      if (tile < nt) { row0 = cu[b] + tile * QW; row_end = cu[b + 1]; break; }
+      const int nt = (cnt + qw - 1) / qw;
+      if (tile < nt) { row0 = cu[b] + tile * qw; row_end = cu[b + 1]; break; }
       tile -= nt;
     }
     if (row0 < 0) return;
@@ -656,6 +659,7 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
   }
 
   // a wave holds 32 queries: lane = query (lane & 31), dims ks*16 + (lane>>5)*8 .. +7
+  const int qg_w = two ? wave & 1 : 0;
   const int my_row = row0 + qg_w * QTT + (lane & 31);
   const int ld_row = my_row < row_end ? my_row : row_end - 1;
   FragA qf[8];
@@ -665,19 +669,24 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
     for (int ks = 0; ks < 8; ++ks) qf[ks] = *reinterpret_cast<const FragA*>(qp + ks * 16);
   }
   f32x16 acc_o[4];
+  float m_run, l_run;
+  auto clear = [&]() {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc_o[i][v] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
+      for (int v = 0; v < 16; ++v) acc_o[i][v] = 0.f;
+    m_run = -INFINITY;
+    l_run = 0.f;
+  };
+  clear();
   const float sc = 1.4426950408889634f / sqrtf((float)DH);   // log2(e) / sqrt(d_h)
 
   // One tile; `more`: this wave's next one is asked for on the way, K's fragments behind the scores that read them, V's behind the
   // products.
-  auto tile_step = [&](auto more, int t) {
+  auto tile_step = [&](auto more, int t, int t_next) {
     constexpr bool MORE = decltype(more)::value;
-    const FragA* kt_n = kg + (size_t)(t + KG) * TILE_F;
-    const FragA* vt_n = vg + (size_t)(t + KG) * TILE_F;
+    const FragA* kt_n = kg + (size_t)t_next * TILE_F;
+    const FragA* vt_n = vg + (size_t)t_next * TILE_F;
     f32x16 sv[2], zero;
 #pragma unroll
     for (int v = 0; v < 16; ++v) zero[v] = 0.f;
@@ -755,48 +764,89 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
       }
     }
   };
-  {
-    for (; t + KG < t_hi; t += KG) tile_step(AtInt<1>{}, t);
-    if (t < t_hi) tile_step(AtInt<0>{}, t);
-  }
-  // merge the partial results of the KG waves of 32 queries: wave g of them finishes dims 128 / KG * g ..  Lanes stand side by side in LDS: a
-  // lane's 64 sums in a row put all lanes on the same banks, 2 us of the launch (16 rows, N = 512: 10.1 -> 8.3 us).
-  float4* sh_o = reinterpret_cast<float4*>(lds);                     // [4 waves][16 pieces][64 lanes]
-  float2* sh_ml = reinterpret_cast<float2*>(sh_o + 4 * 16 * 64);   // [4][64]
-  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-  {
-    float4* po = sh_o + wave * 16 * 64 + lane;
+  // a state (O, max, sum) covers every fourth tile.  The merge: lanes stand side by side in LDS, as a lane's 64 sums in a row put
+  // all lanes on the same banks, 2 us of the launch (16 rows, N = 512: 10.1 -> 8.3 us).
+  constexpr int STATES = PAIRS ? 8 : 4;
+  float4* sh_o = reinterpret_cast<float4*>(lds);                           // [STATES][16 pieces][64 lanes]
+  float2* sh_ml = reinterpret_cast<float2*>(sh_o + STATES * 16 * 64);      // [STATES][64]
+  auto leave = [&](int z) {
+    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    float4* po = sh_o + z * 16 * 64 + lane;
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
       for (int g = 0; g < 4; ++g)
         po[(mb * 4 + g) * 64] =
             make_float4(acc_o[mb][4 * g], acc_o[mb][4 * g + 1], acc_o[mb][4 * g + 2], acc_o[mb][4 * g + 3]);
-    sh_ml[wave * 64 + lane] = make_float2(m_run * sc, l_tot);         // reference in the exp2 domain (-inf: no tile)
-  }
-  __syncthreads();
-  constexpr int NG = 4 * QG;                  // pieces of four dims
-  float2 ml[KG];
-  float mx = -INFINITY;
-#pragma unroll
-  for (int z = 0; z < KG; ++z) { ml[z] = sh_ml[(z * QG + qg_w) * 64 + lane]; mx = fmaxf(mx, ml[z].x); }
-  float num[4 * NG], den = 0.f;
-#pragma unroll
-  for (int v = 0; v < 4 * NG; ++v) num[v] = 0.f;
-#pragma unroll
-  for (int z = 0; z < KG; ++z) {
-    const float w = __builtin_amdgcn_exp2f(ml[z].x - mx);
-    den = fmaf(w, ml[z].y, den);
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      const float4 pz = sh_o[((z * QG + qg_w) * 16 + kg_w * NG + g) * 64 + lane];
-      num[4 * g] = fmaf(w, pz.x, num[4 * g]);
-      num[4 * g + 1] = fmaf(w, pz.y, num[4 * g + 1]);
-      num[4 * g + 2] = fmaf(w, pz.z, num[4 * g + 2]);
-      num[4 * g + 3] = fmaf(w, pz.w, num[4 * g + 3]);
+    sh_ml[z * 64 + lane] = make_float2(m_run * sc, l_tot);         // reference in the exp2 domain (-inf: no tile)
+  };
+  if constexpr (!PAIRS) {
+    for (; t + 4 < t_hi; t += 4) tile_step(AtInt<1>{}, t, t + 4);
+    if (t < t_hi) tile_step(AtInt<0>{}, t, 0);
+    leave(wave);
+  } else {
+    int z = t;                                // the wave's first state (t_lo is 0); of two, the second is z + 2
+    bool follows = two && z + 2 < t_hi;       // a state with tiles comes behind this one
+    for (;;) {
+      const int t_next = t + 4 < t_hi ? t + 4 : follows ? z + 2 : t_hi;
+      if (t_next >= t_hi) break;
+      tile_step(AtInt<1>{}, t, t_next);
+      if (t + 4 >= t_hi) {
+        leave(qg_w * 4 + z);
+        clear();
+        z += 2;
+        follows = false;
+      }
+      t = t_next;
+    }
+    if (t < t_hi) tile_step(AtInt<0>{}, t, 0);
+    leave(qg_w * 4 + z);
+    if (two && z < 2) {                       // the second state has no tile
+      clear();
+      leave(qg_w * 4 + z + 2);
     }
   }
+  __syncthreads();
+  // a wave finishes 4 NG dims of its 32 queries, from piece g0 on; the four states are added in the same order whoever made them
+  float num[16 * (PAIRS ? 2 : 1)], den = 0.f, mx = -INFINITY;
+  auto merge = [&](auto pieces, int g0) {
+    constexpr int NG = decltype(pieces)::value;
+    const int s0 = qg_w * 4;
+    float2 ml[4];
+#pragma unroll
+    for (int z = 0; z < 4; ++z) { ml[z] = sh_ml[(s0 + z) * 64 + lane]; mx = fmaxf(mx, ml[z].x); }
+#pragma unroll
+    for (int v = 0; v < 4 * NG; ++v) num[v] = 0.f;
+#pragma unroll
+    for (int z = 0; z < 4; ++z) {
+      const float w = __builtin_amdgcn_exp2f(ml[z].x - mx);
+      den = fmaf(w, ml[z].y, den);
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const float4 pz = sh_o[((s0 + z) * 16 + g0 + g) * 64 + lane];
+        num[4 * g] = fmaf(w, pz.x, num[4 * g]);
+        num[4 * g + 1] = fmaf(w, pz.y, num[4 * g + 1]);
+        num[4 * g + 2] = fmaf(w, pz.z, num[4 * g + 2]);
+        num[4 * g + 3] = fmaf(w, pz.w, num[4 * g + 3]);
+      }
+    }
+  };
+  auto finish = [&](auto pieces, int g0) {
+    constexpr int NG = decltype(pieces)::value;
+    merge(pieces, g0);
+    const float inv = 1.0f / den;
+    if (my_row < row_end) {
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        bf16x4 w4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w4[e] = (__bf16)(num[4 * g + e] * inv);
+        *reinterpret_cast<bf16x4*>(o + afrag_index(my_row, hh * DH + (g0 + g) * 8 + 4 * (lane >> 5), H * DH)) = w4;
+      }
+    }
+  };
   if constexpr (SPLIT) {
+    merge(AtInt<4>{}, wave * 4);
     if (my_row < row_end) {
       const size_t slot = ((size_t)blockIdx.z * m_upper + my_row) * H + hh;
       float* po = part_o + slot * DH + wave * 32 + 4 * (lane >> 5);
@@ -808,17 +858,10 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
         part_ml[slot * 2 + 1] = den;
       }
     }
-    return;
-  }
-  const float inv = 1.0f / den;
-  if (my_row < row_end) {
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      bf16x4 w4;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) w4[e] = (__bf16)(num[4 * g + e] * inv);
-      *reinterpret_cast<bf16x4*>(o + afrag_index(my_row, hh * DH + kg_w * (8 * NG) + 8 * g + 4 * (lane >> 5), H * DH)) = w4;
-    }
+  } else if (PAIRS && two) {
+    finish(AtInt<8>{}, (wave >> 1) * 8);
+  } else {
+    finish(AtInt<4>{}, wave * 4);
   }
 }
 
@@ -942,11 +985,11 @@ int slk_attention_mfma(hipStream_t s, const void* q, const void* kc, const void*
   if (Zt == 1 || (Zt > 1 && scratch)) {
     const size_t sh_thin = (size_t)(4 * 64 * 64 + 4 * 64 * 2) * sizeof(float);
     static unsigned long long lds_thin[3] = {0, 0, 0};
-    SL_ALLOW_DYNAMIC_LDS(lds_thin[0], (attention_thin_kernel<false, 1>), sh_thin);
-    SL_ALLOW_DYNAMIC_LDS(lds_thin[1], (attention_thin_kernel<true, 1>), sh_thin);
-    SL_ALLOW_DYNAMIC_LDS(lds_thin[2], (attention_thin_kernel<false, 2>), sh_thin);
+    SL_ALLOW_DYNAMIC_LDS(lds_thin[0], (attention_thin_kernel<false, false>), sh_thin);
+    SL_ALLOW_DYNAMIC_LDS(lds_thin[1], (attention_thin_kernel<true, false>), sh_thin);
+    SL_ALLOW_DYNAMIC_LDS(lds_thin[2], (attention_thin_kernel<false, true>), 2 * sh_thin);
     if (Zt == 1 && (sl_cdiv(m_upper, QTT) + B - 1) * H > kThinOneRound) {
-      hipLaunchKernelGGL((attention_thin_kernel<false, 2>), dim3(H, sl_cdiv(m_upper, 2 * QTT) + B - 1, 1), dim3(256), sh_thin, s,
+      hipLaunchKernelGGL((attention_thin_kernel<false, true>), dim3(H, sl_cdiv(m_upper, 2 * QTT) + B - 1, 1), dim3(256), 2 * sh_thin, s,
                          (const bf16_t*)q, (const bf16_t*)kc, (const bf16_t*)vc, active_idx, m_dev, m_upper, B, H, N, n_pad, (bf16_t*)o, tps,
                          (float*)nullptr, (float*)nullptr);
       SL_LAUNCH_CHECK();
@@ -954,7 +997,7 @@ int slk_attention_mfma(hipStream_t s, const void* q, const void* kc, const void*
     }
     float* po = Zt > 1 ? scratch : nullptr;
     float* pml = Zt > 1 ? scratch + (size_t)Zt * m_upper * H * DH : nullptr;
-    hipLaunchKernelGGL((Zt > 1 ? attention_thin_kernel<true, 1> : attention_thin_kernel<false, 1>),
+    hipLaunchKernelGGL((Zt > 1 ? attention_thin_kernel<true, false> : attention_thin_kernel<false, false>),
                        dim3(H, sl_cdiv(m_upper, QTT) + B - 1, Zt), dim3(256), sh_thin, s, (const bf16_t*)q, (const bf16_t*)kc,
                        (const bf16_t*)vc, active_idx, m_dev, m_upper, B, H, N, n_pad, (bf16_t*)o, tps, po, pml);
     SL_LAUNCH_CHECK();
