@@ -576,14 +576,36 @@ __global__ __launch_bounds__(256, 3) void attention_trio_kernel(const bf16_t* __
 // matrix pipe idles here anyway).
 // SPLIT: as above, for sequences whose tiles are too many for four waves; each workgroup leaves its merged sums to
 // attention_merge_kernel.
-// PAIRS: 64 queries, two waves for each 32 of them: one round of workgroups where 32 queries make two (the two waves that want
-// a tile ask for it together).  One block, this and the loads inside the tile together: 300 rows of N = 512 206.1 -> 202.9
-// us, 457 rows of N = 1024 264.2 -> 259.1, 512 rows 263.4 -> 257.4, 300 rows of 4 x 800 219.0 -> 210.8.  A wave makes two states
-// of every fourth tile, one behind the other, where it could make one of every second: so a row's sums are made of the same four
-// states whatever form its launch takes, and its result does not depend on the bound or on the other rows, bit by bit (equal
-// times: 457 rows of N = 1024 258.7 before and 258.6 after, 300 rows of N = 512 200.9 and 201.8, 512 rows 243.3 and 243.8).
+// PAIRS: 32 queries per workgroup or 64, two waves for each 32 of them: one round of workgroups where 32 queries make two (the
+// two waves that want a tile ask for it together).  One block, 64 queries and the loads inside the tile together: 300 rows of
+// N = 512 206.1 -> 202.9 us, 457 rows of N = 1024 264.2 -> 259.1, 512 rows 263.4 -> 257.4, 300 rows of 4 x 800 219.0 -> 210.8.  A
+// wave then makes two states of every fourth tile, one behind the other, where it could make one of every second: so a row's sums are
+// made of the same four states in both forms, and its result is the same bit by bit (equal times: 457 rows of N = 1024 258.7 before and
+// 258.6 after, 300 rows of N = 512 200.9 and 201.8, 512 rows 243.3 and 243.8).
+// Which of the two is decided on the device, by the tiles that hold rows (thin_pairs): the host knows a bound only, which counts a
+// part-filled tile for every sequence but one.  One block, 64 queries wherever the bound exceeds a round -> decided here: 16 rows of
+// N = 512 bounded by 512 206.4 -> 203.4 us, 2 x 1024 with 96 and 160 rows 189.7 -> 186.7, 4 x 1024 with 50 rows each 179.2 -> 176.2, 6 x 20
+// and 150 rows of 7 x 1024 228.9 -> 222.2, 4 x 2048 with 50 each 190.8 -> 183.4, 200 rows of N = 2048 bounded by 512 244.6 -> 234.1; where
+// a tile of 32 is full of other sequences' keys (8 x 512, 160 rows) the launch waits for memory in either form, 159.9 and 159.6.
 template <int V> struct AtInt { static constexpr int value = V; };
-constexpr int QTT = 32;          // queries per workgroup of the thin kernel; PAIRS: 64
+// sum over the lanes up to this one
+__device__ inline int wave_prefix_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // row_shr:1, :2, :4, :8 within 16 lanes
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);      // lane 15 of a row to the odd rows behind it,
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);      // lane 31 to the upper half
+  return v;
+}
+constexpr int QTT = 32;          // queries per workgroup of the thin kernel; PAIRS: or 64
+constexpr int kThinOneRound = 256, kThinPairs = 512;          // workgroups of 32 queries
+// Whether the rows' tiles of 64 (t64 per head) are taken instead of those of 32 (t32), in a grid of `rows` workgroups per head: where
+// 32 make more than one round and 64 do not (12 x 512 with ten rows each, two rounds of either: 154.7 us with 64, 152.1 with 32),
+// or where the grid has no place for all tiles of 32.
+__host__ __device__ inline bool thin_pairs(int t32, int t64, int H, int rows) {
+  return t32 * H > kThinOneRound && (t64 * H <= kThinOneRound || t32 > rows);
+}
 template <bool SPLIT, bool PAIRS>
 __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __restrict__ q,
                                                                 const bf16_t* __restrict__ kc,
@@ -620,21 +642,30 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
 #pragma unroll
       for (int mb = 0; mb < 4; ++mb) vf[st * 4 + mb] = vt[(2 * st) * DH + mb * 32];
   };
-  constexpr int qw = PAIRS ? 2 * QTT : QTT;   // queries per workgroup
-  constexpr bool two = PAIRS;                 // 64: two states per wave, waves 2 z + g for queries 32 g ..
-  int t = t_lo + (two ? wave >> 1 : wave);    // this wave's first tile
+  int t = t_lo + wave;                        // this wave's first tile
   int row0 = -1, row_end = 0;
+  int qw = QTT;                               // queries per workgroup
+  bool two = false;                           // 64: two states per wave, waves 2 z + g for queries 32 g ..
+  auto start = [&]() {
+    if constexpr (PAIRS) {
+      two = qw != QTT;
+      if (two) t = wave >> 1;
+    }
+    if (t < t_hi) load_kv(t);
+  };
   // workgroups past the rows leave (uniformly) before their first load: under a bound far above the row count most do (200 rows of
   // N = 512 bounded by 512: 12.3 us with a key tile asked for ahead of the test, 11.4 behind it)
   if (B == 1) {
     // one sequence: its row range is known without a search, LDS and a barrier (16 rows, N = 512 10.3 -> 9.9 us; 457 rows,
     // N = 1024 29.8 -> 28.5).  The loads in each branch: behind both, the address of a sequence that is not a constant costs 0.2 us
     // (24 rows of N = 512 7.9 -> 8.1; two sequences of 2048, split 15.7 -> 16.2).
+    if constexpr (PAIRS)
+      if (thin_pairs(sl_cdiv_dev(M, QTT), sl_cdiv_dev(M, 2 * QTT), H, gridDim.y)) qw = 2 * QTT;
     if ((int)blockIdx.y * qw >= M) return;
     row0 = blockIdx.y * qw;
     row_end = M;
     head_of(0);
-    if (t < t_hi) load_kv(t);
+    start();
   } else {
     if (tid <= B) {
       int lo = 0, hi = M;
@@ -646,16 +677,40 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
       cu[tid] = lo;
     }
     __syncthreads();
-    int b = 0, tile = blockIdx.y;
-    for (; b < B; ++b) {
-      const int cnt = cu[b + 1] - cu[b];
-      const int nt = (cnt + qw - 1) / qw;
-      if (tile < nt) { row0 = cu[b] + tile * qw; row_end = cu[b + 1]; break; }
-      tile -= nt;
+    int b = 0;
+    if constexpr (PAIRS) {                    // lane = sequence, 64 at a time: the tiles of all of them, and this workgroup's
+      auto locate = [&](int queries) {
+        int tiles = 0;
+        qw = queries;
+        row0 = -1;
+        for (int b0 = 0; b0 < B; b0 += 64) {
+          const int c0 = cu[min(b0 + lane, B)], c1 = cu[min(b0 + lane + 1, B)], nt = (c1 - c0 + qw - 1) / qw;
+          const int up_to = wave_prefix_sum(nt), tile = (int)blockIdx.y - tiles;
+          const unsigned long long here = __ballot(tile < up_to);
+          if (here != 0 && row0 < 0) {
+            const int l = __ffsll(here) - 1;
+            b = b0 + l;
+            row0 = __builtin_amdgcn_readlane(c0, l) + (tile - __builtin_amdgcn_readlane(up_to - nt, l)) * qw;
+            row_end = __builtin_amdgcn_readlane(c1, l);
+          }
+          tiles += __builtin_amdgcn_readlane(up_to, 63);
+        }
+        return tiles;
+      };
+      const int t32 = locate(QTT);
+      if (t32 * H > kThinOneRound && !thin_pairs(t32, locate(2 * QTT), H, gridDim.y)) locate(QTT);
+    } else {
+      int tile = blockIdx.y;
+      for (; b < B; ++b) {
+        const int cnt = cu[b + 1] - cu[b];
+        const int nt = (cnt + QTT - 1) / QTT;
+        if (tile < nt) { row0 = cu[b] + tile * QTT; row_end = cu[b + 1]; break; }
+        tile -= nt;
+      }
     }
     if (row0 < 0) return;
     head_of(b);
-    if (t < t_hi) load_kv(t);
+    start();
   }
 
   // a wave holds 32 queries: lane = query (lane & 31), dims ks*16 + (lane>>5)*8 .. +7
@@ -924,10 +979,12 @@ static bool attention_use_trio(int blocks) { return blocks > 256; }
 // keeps one tile at least) and at most 32 tiles per split.  Measured as one block of the layer, B = 1, the pipelined
 // kernel with its splits against this one, N = 2048: 32 rows 124.6 against 119.6 us (Z = 8), 64 rows 153.0 / 145.8 (4),
 // 128 rows 180.7 / 171.6 (2), 256 rows 228.7 / 225.4 (1); N = 4096, 64 rows 157.9 / 151.3 (4), 256 rows (64 tiles per split)
-// 237.5 / 237.7.  Up to two workgroups per CU it then takes 64 queries each, where 32 tiles or fewer are to be walked: N = 2048,
-// 320 rows 226.1 / 224.1, 384 rows 237.7 / 234.9, 480 rows 276.2 / 273.4, N = 1100, 300 rows 218.0 / 212.4.  Beyond that it loses to the
+// 237.5 / 237.7.  Up to two workgroups per CU by the bound it takes 32 or 64 queries each, where 32 tiles or fewer are to be walked: N = 2048,
+// 320 rows 226.1 / 224.1, 384 rows 237.7 / 234.9, 480 rows 276.2 / 273.4, N = 1100, 300 rows 218.0 / 212.4; batches of even sequences:
+// 2 x 1100, 300 rows 220.2 / 214.7, 2 x 2048, 300 rows 230.2 / 227.9, 450 rows 283.1 / 279.0, 4 x 1600, 200 rows 193.8 / 183.0, 4 x 2048,
+// 300 rows 236.1 / 230.0, 8 x 2048, 64 rows 151.6 / 150.4, 288 rows 257.3 / 254.0, 12 x 1500, 60 rows 165.6 / 166.1; bounds far above the
+// rows, N = 2048: 16 rows bounded by 384 184.8 / 176.9, 64 by 512 226.7 / 216.7.  Beyond that it loses to the
 // three-per-CU kernel: N = 1024, 600 rows 317.5 / 326.6, 800 rows 369.5 / 377.8.
-constexpr int kThinOneRound = 256, kThinPairs = 512;          // workgroups of 32 queries
 static int attention_thin_splits(int m_upper, int B, int H, int n_pad, int* tiles_per_split) {
   const int n_tiles = n_pad / KT, blocks = (sl_cdiv(m_upper, QTT) + B - 1) * H;
   *tiles_per_split = n_tiles;
@@ -937,6 +994,25 @@ static int attention_thin_splits(int m_upper, int B, int H, int n_pad, int* tile
   *tiles_per_split = sl_cdiv(n_tiles, Z);
   return *tiles_per_split <= 32 ? sl_cdiv(n_tiles, *tiles_per_split) : 0;
 }
+
+// Workgroups per head of an unsplit thin launch that may take 64 queries each, 0 where the bound is one round of 32 anyway: room
+// for every row within the bound at 64, and at 32 for every distribution that then makes one round.
+static int attention_thin_pair_tiles(int m_upper, int B, int H) {
+  const int tiles32 = sl_cdiv(m_upper, QTT) + B - 1, tiles64 = sl_cdiv(m_upper, 2 * QTT) + B - 1;
+  if (tiles32 * H <= kThinOneRound) return 0;
+  const int round = tiles32 < kThinOneRound / H ? tiles32 : kThinOneRound / H;
+  return tiles64 > round ? tiles64 : round;
+}
+// for tests: key splits of the thin kernel (0: another kernel's launch), workgroups per head, whether they may take 64 queries; and
+// whether they do
+void slk_attention_thin_form(int m_upper, int B, int H, int n_pad, int* out) {
+  int tps;
+  out[0] = attention_thin_splits(m_upper, B, H, n_pad, &tps);
+  out[1] = out[0] == 1 ? attention_thin_pair_tiles(m_upper, B, H) : 0;
+  out[2] = out[1] != 0;
+  if (!out[2]) out[1] = sl_cdiv(m_upper, QTT) + B - 1;
+}
+int slk_attention_thin_pairs(int t32, int t64, int H, int rows) { return thin_pairs(t32, t64, H, rows); }
 
 // Key-split plan for a launch bounded by m_upper rows: the keys are split just far enough to
 // give every CU one workgroup of the pipelined kernel (LDS rings, 370 registers per lane: one per
@@ -988,8 +1064,8 @@ int slk_attention_mfma(hipStream_t s, const void* q, const void* kc, const void*
     SL_ALLOW_DYNAMIC_LDS(lds_thin[0], (attention_thin_kernel<false, false>), sh_thin);
     SL_ALLOW_DYNAMIC_LDS(lds_thin[1], (attention_thin_kernel<true, false>), sh_thin);
     SL_ALLOW_DYNAMIC_LDS(lds_thin[2], (attention_thin_kernel<false, true>), 2 * sh_thin);
-    if (Zt == 1 && (sl_cdiv(m_upper, QTT) + B - 1) * H > kThinOneRound) {
-      hipLaunchKernelGGL((attention_thin_kernel<false, true>), dim3(H, sl_cdiv(m_upper, 2 * QTT) + B - 1, 1), dim3(256), 2 * sh_thin, s,
+    if (const int tiles = Zt == 1 ? attention_thin_pair_tiles(m_upper, B, H) : 0) {
+      hipLaunchKernelGGL((attention_thin_kernel<false, true>), dim3(H, tiles, 1), dim3(256), 2 * sh_thin, s,
                          (const bf16_t*)q, (const bf16_t*)kc, (const bf16_t*)vc, active_idx, m_dev, m_upper, B, H, N, n_pad, (bf16_t*)o, tps,
                          (float*)nullptr, (float*)nullptr);
       SL_LAUNCH_CHECK();

@@ -25,6 +25,20 @@ def test_pairs(batch, N, rows):
     check_block(SHAPE, batch, N, rows)
 
 
+# four heads, so that the workgroups' tiles are searched for among more than 64 tiles or sequences
+FEW_HEADS = wl.Shape("thin-pairs-4", 1, 256, 4, 128, 256, 1056, "bf16")
+
+
+@pytest.mark.parametrize("batch,N,rows", [
+    (3, 1000, [1000, 980, 80]),         # 66 tiles of 32, 34 of 64
+    (70, 60, [1] * 70),                 # two rounds of either: 32 queries
+    (70, 100, [33] * 40 + [1] * 30),    # 110 tiles of 32 in a grid of 91: 64 queries
+    (66, 130, [1] * 60 + [130, 2, 40, 1, 33, 64]),        # rows behind the first 64 sequences
+])
+def test_pairs_among_many_sequences(batch, N, rows):
+    check_block(FEW_HEADS, batch, N, rows)
+
+
 @pytest.mark.parametrize("N,rows", [(300, [65, 190]), (1020, [1, 255]), (230, [33, 33, 33, 97])])
 def test_results_do_not_depend_on_the_form(N, rows):
     """Probes of the same rows over the same keys, alone (one round of workgroups of 32 queries) and beside the other sequences' (64
