@@ -18,12 +18,16 @@
 // rows of A on its way through k, so it sums their squares and scales its results by the norm it would have waited for
 // (NORM; the gain goes into the operand); Q|K|V rotates and scatters its own columns (MODE 2); Out and down add to the
 // residual in place (RES).  The tiny model's step (2 blocks, 72 rows): 21 launches -> 15,
-// 86.2 -> 71.6 us; 300 rows of 4 x 256 slots 123.4 -> 102.8.
+// 88.5 -> 77.2 us; 300 rows of 4 x 256 slots 118.1 -> 103.5, 600 rows 157.6 -> 139.8.
 #include "sl_common.h"
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int KC = 16;    // k per chunk: four instructions
+// Chunks in flight per wave.  Twelve for reductions of at most 768, a wave's whole share at once, leave room for 2 to 4 workgroups per
+// CU where four leave it for 5 to 8 (us for a step of two blocks with four, with twelve: d = 512, 300 rows 222.4 / 252.7 in bf16 and 198.6 /
+// 214.9 in fp32, d = 264, 600 fp32 rows 137.4 / 179.8, 72 rows 82 / 85; d = 256, 72 rows 77.2 / 78.1; only d = 768, 16 rows 100.3 / 97.6).
+constexpr int UC = 4;
 
 // four consecutive elements; zeros past the row's end (k % 4 == 0 on the vector path, so a piece is whole or absent)
 template <typename T, bool VEC>
@@ -60,8 +64,8 @@ struct GenericRope {          // MODE 2: where Q|K|V goes (as slk_rope_kv_write)
 // MODE 0: matrix z of the launch -> columns z * n .. of C_f32 / C_T.  MODE 1: w[0] = gate, w[1] = up: C_T =
 // silu(gate) * up.  MODE 2: matrix z is q, k or v: 16 columns of a head's first half and those they rotate with, RoPE and
 // the scatter.  RES: C_T += the product.  MB x MB blocks of 16 x 16 per wave; KS waves share a tile's k-chunks (MB == 1: 4,
-// else 1), UC chunks of each in flight.
-template <typename T, int MODE, int MB, bool VEC, bool NORM, bool RES, int UC>
+// else 1).
+template <typename T, int MODE, int MB, bool VEC, bool NORM, bool RES>
 __global__ __launch_bounds__(256) void gemm_generic_kernel(const T* __restrict__ A, GenericMats mats,
                                                            const int32_t* __restrict__ m_dev, int m_upper, int n,
                                                            int k, float* __restrict__ C_f32, T* __restrict__ C_T,
@@ -239,10 +243,6 @@ static bool small_tiles(int m_upper, int n, int nm) {
   const long small = (long)sl_cdiv(n, 16) * sl_cdiv(m_upper, 16) * nm, big = (long)sl_cdiv(n, 64) * sl_cdiv(m_upper, 64) * nm;
   return small <= 1024 || big < 192;
 }
-// The chunks that each of four waves has in flight: all of them where that is no more than 12, which makes the launch one
-// load latency instead of one per four chunks (72 x 256 x 688, 11 chunks a wave: 5.2 us, now 5.0 with
-// the residual add; longer reductions keep the registers for more workgroups).
-static bool deep(int k) { return k > 4 * 4 * KC && k <= 12 * 4 * KC; }
 
 template <typename T, int MODE>
 static int launch_generic(hipStream_t s, const void* A, const GenericMats& mats, int nm, const int32_t* m_dev, int m_upper,
@@ -251,12 +251,12 @@ static int launch_generic(hipStream_t s, const void* A, const GenericMats& mats,
   uintptr_t bits = (uintptr_t)A | (uintptr_t)C_f32 | (uintptr_t)C_T;
   for (int i = 0; i < (MODE == 1 ? 2 : nm); ++i) bits |= (uintptr_t)mats.w[i];
   const bool vec = bits % 16 == 0 && k % 8 == 0 && n % 8 == 0 && ldc % 8 == 0;
-#define GO(MB, VEC, UC)                                                                                               \
-  hipLaunchKernelGGL((gemm_generic_kernel<T, MODE, MB, VEC, false, false, UC>),                                       \
+#define GO(MB, VEC)                                                                                                   \
+  hipLaunchKernelGGL((gemm_generic_kernel<T, MODE, MB, VEC, false, false>),                                           \
                      dim3(sl_cdiv(n, MB == 1 ? 16 : 64), sl_cdiv(m_upper, MB == 1 ? 16 : 64), nm), dim3(256), 0, s,   \
                      (const T*)A, mats, m_dev, m_upper, n, k, C_f32, (T*)C_T, out_row_map, ldc, GenericNorm{}, GenericRope{})
-  if (small_tiles(m_upper, n, nm)) { if (!vec) GO(1, false, 4); else if (deep(k)) GO(1, true, 12); else GO(1, true, 4); }
-  else { if (vec) GO(2, true, 4); else GO(2, false, 4); }
+  if (small_tiles(m_upper, n, nm)) { if (vec) GO(1, true); else GO(1, false); }
+  else { if (vec) GO(2, true); else GO(2, false); }
 #undef GO
   SL_LAUNCH_CHECK();
   return SL_OK;
@@ -290,13 +290,8 @@ int slk_generic_fused(int m_upper, int n, int k, int nm, uintptr_t bits) {
 template <int MODE, bool NORM, bool RES>
 static int launch_fused(hipStream_t s, const float* A, const GenericMats& mats, int tiles, int nm, const int32_t* m_dev, int m_upper,
                         int n, int k, float* C, const int32_t* out_row_map, const GenericNorm& norm, const GenericRope& rope) {
-  const dim3 grid(tiles, sl_cdiv(m_upper, 16), nm);
-  if (deep(k))
-    hipLaunchKernelGGL((gemm_generic_kernel<float, MODE, 1, true, NORM, RES, 12>), grid, dim3(256), 0, s, A, mats, m_dev, m_upper, n, k,
-                       (float*)nullptr, C, out_row_map, (size_t)n, norm, rope);
-  else
-    hipLaunchKernelGGL((gemm_generic_kernel<float, MODE, 1, true, NORM, RES, 4>), grid, dim3(256), 0, s, A, mats, m_dev, m_upper, n, k,
-                       (float*)nullptr, C, out_row_map, (size_t)n, norm, rope);
+  hipLaunchKernelGGL((gemm_generic_kernel<float, MODE, 1, true, NORM, RES>), dim3(tiles, sl_cdiv(m_upper, 16), nm), dim3(256), 0, s, A,
+                     mats, m_dev, m_upper, n, k, (float*)nullptr, C, out_row_map, (size_t)n, norm, rope);
   SL_LAUNCH_CHECK();
   return SL_OK;
 }
