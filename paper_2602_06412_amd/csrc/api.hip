@@ -296,9 +296,9 @@ static bool head_fused(const sl_ctx* ctx, const Workspace& ws, int mu, const voi
 }
 
 // Layers [lo, hi) on the rows held in ws.x, with ws.h = RMSNorm(ws.x) by layer lo's attention
-// gain on entry.  On exit ws.x is the block output and ws.h its RMSNorm by the next gain
-// (layer hi's attention gain, or the final gain after the last layer), unless need_h is false: then the rows' norm may be
-// left to whoever reads ws.x.
+// gain on entry (a fused layer norms ws.x itself and does not read it).  On exit ws.x is the block output and ws.h its RMSNorm
+// by the next gain (layer hi's attention gain, or the final gain after the last layer), unless need_h is false: then the rows'
+// norm may be left to whoever reads ws.x.
 static int run_layers(sl_ctx* ctx, hipStream_t s, const Workspace& ws, const int32_t* active_idx,
                       const int32_t* m_dev, int mu, int lo, int hi, bool need_h) {
   const sl_config& c = ctx->cfg;
