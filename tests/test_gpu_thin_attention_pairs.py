@@ -9,19 +9,30 @@ from paper_2602_06412_amd import binding as B
 from paper_2602_06412_amd import workloads as wl
 from tests.gpu_util import DEV, weights_to_device
 from tests.test_gpu_thin_attention_split import check_block
+from tests.test_thin_attention_grid_cpu import form, queries
 
 pytestmark = pytest.mark.gpu
 
 SHAPE = wl.Shape("thin-pairs", 1, 512, 32, 128, 512, 1056, "bf16")
 
 
-@pytest.mark.parametrize("batch,N,rows", [
-    (5, 60, [33, 60, 1, 32, 60]),       # one key tile: two of the four waves have none
-    (1, 300, [257]),                    # five tiles, the last one ragged; the last workgroup holds one row
-    (2, 1020, [288, 33]),
-    (1, 2040, [289]),                   # 32 tiles
+def taken(shape, batch, N, rows):
+    """queries per workgroup of a launch whose bound is the row count"""
+    splits, grid, may = form(sum(rows), batch, shape.n_heads, -(-N // 64) * 64)
+    assert splits == 1 and may
+    return queries(rows, shape.n_heads, grid)[1]
+
+
+@pytest.mark.parametrize("batch,N,rows,width", [
+    (5, 60, [33, 60, 1, 32, 60], 32),   # one round of 32 queries, under a bound of more; one key tile: three of the four waves have none
+    (5, 60, [33, 60, 33, 32, 60], 64),  # one key tile: two of the four waves have none, and none has a second state
+    (8, 150, [33, 60, 32, 1, 33, 33, 33, 33], 64),        # three tiles: one of the pairs' second states has none
+    (1, 300, [257], 64),                # five tiles, the last one ragged; the last workgroup holds one row
+    (2, 1020, [288, 33], 64),
+    (1, 2040, [289], 64),               # 32 tiles
 ])
-def test_pairs(batch, N, rows):
+def test_pairs(batch, N, rows, width):
+    assert taken(SHAPE, batch, N, rows) == width
     check_block(SHAPE, batch, N, rows)
 
 
@@ -29,13 +40,14 @@ def test_pairs(batch, N, rows):
 FEW_HEADS = wl.Shape("thin-pairs-4", 1, 256, 4, 128, 256, 1056, "bf16")
 
 
-@pytest.mark.parametrize("batch,N,rows", [
-    (3, 1000, [1000, 980, 80]),         # 66 tiles of 32, 34 of 64
-    (70, 60, [1] * 70),                 # two rounds of either: 32 queries
-    (70, 100, [33] * 40 + [1] * 30),    # 110 tiles of 32 in a grid of 91: 64 queries
-    (66, 130, [1] * 60 + [130, 2, 40, 1, 33, 64]),        # rows behind the first 64 sequences
+@pytest.mark.parametrize("batch,N,rows,width", [
+    (3, 1000, [1000, 980, 80], 64),     # 66 tiles of 32, 34 of 64
+    (70, 60, [1] * 70, 32),             # two rounds of either
+    (70, 100, [33] * 40 + [1] * 30, 64),                  # 110 tiles of 32 in a grid of 91
+    (66, 130, [1] * 60 + [130, 2, 40, 1, 33, 64], 64),    # rows behind the first 64 sequences; 74 tiles of 32 in a grid of 71
 ])
-def test_pairs_among_many_sequences(batch, N, rows):
+def test_pairs_among_many_sequences(batch, N, rows, width):
+    assert taken(FEW_HEADS, batch, N, rows) == width
     check_block(FEW_HEADS, batch, N, rows)
 
 
@@ -45,7 +57,7 @@ def test_results_do_not_depend_on_the_form(N, rows):
     queries each, a row bound of more than one round): a row's partial sums are the same four and are added in the same order, so
     the logits are the same bit by bit.  The projections' launches follow the bound, which is equal."""
     batch, total = len(rows), sum(rows)
-    assert -(-total // 32) * SHAPE.n_heads <= 256 < sum(-(-r // 32) for r in rows) * SHAPE.n_heads
+    assert not form(total, 1, SHAPE.n_heads, -(-N // 64) * 64)[2] and taken(SHAPE, batch, N, rows) == 64
     w = wl.make_weights(SHAPE, seed=4, norm_gain_jitter=0.05)
     lay = w["layers"][0]
     lay["wq"], lay["wo"], lay["w_down"] = lay["wq"] * 4, lay["wo"] * 64, lay["w_down"] * 0
