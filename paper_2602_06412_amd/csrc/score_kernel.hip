@@ -168,7 +168,8 @@ __global__ __launch_bounds__(NT) void score_kernel(const T* __restrict__ cur, in
     // Sixteen states at once would take 96 registers of every thread, and with them the second workgroup of 1024 threads per
     // CU: three at a time it has room (43), and 257 to 512 bf16 rows are one round of workgroups instead of two (lock test of
     // 260 rows 52.4 -> 49.4 us, 330 53.5 -> 51.0, 400 55.3 -> 52.6, 512 58.5 -> 55.9; up to 256 rows equal).  fp32 rows, twice
-    // as long, do better one workgroup at a time (512 rows 89.6 against 91.6).
+    // as long, do better one workgroup at a time (one against two per CU: 260 rows 71.7 / 71.1, 330 74.8 / 75.2, 400 76.7 / 79.7, 460 82.4 /
+    // 86.7, 512 90.3 / 94.0).
     constexpr int AT_ONCE = sizeof(T) == 2 ? 3 : NT / 64;
 #pragma unroll AT_ONCE
     for (int w = 1; w < NT / 64; ++w) acc_merge(t, sh[w]);
