@@ -24,10 +24,6 @@
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int KC = 16;    // k per chunk: four instructions
-// Chunks in flight per wave.  Twelve for reductions of at most 768, a wave's whole share at once, leave room for 2 to 4 workgroups per
-// CU where four leave it for 5 to 8 (us for a step of two blocks with four, with twelve: d = 512, 300 rows 222.4 / 252.7 in bf16 and 198.6 /
-// 214.9 in fp32, d = 264, 600 fp32 rows 137.4 / 179.8, 72 rows 82 / 85; d = 256, 72 rows 77.2 / 78.1; only d = 768, 16 rows 100.3 / 97.6).
-constexpr int UC = 4;
 
 // four consecutive elements; zeros past the row's end (k % 4 == 0 on the vector path, so a piece is whole or absent)
 template <typename T, bool VEC>
@@ -64,8 +60,8 @@ struct GenericRope {          // MODE 2: where Q|K|V goes (as slk_rope_kv_write)
 // MODE 0: matrix z of the launch -> columns z * n .. of C_f32 / C_T.  MODE 1: w[0] = gate, w[1] = up: C_T =
 // silu(gate) * up.  MODE 2: matrix z is q, k or v: 16 columns of a head's first half and those they rotate with, RoPE and
 // the scatter.  RES: C_T += the product.  MB x MB blocks of 16 x 16 per wave; KS waves share a tile's k-chunks (MB == 1: 4,
-// else 1).
-template <typename T, int MODE, int MB, bool VEC, bool NORM, bool RES>
+// else 1), UC chunks of each in flight.
+template <typename T, int MODE, int MB, bool VEC, bool NORM, bool RES, int UC>
 __global__ __launch_bounds__(256) void gemm_generic_kernel(const T* __restrict__ A, GenericMats mats,
                                                            const int32_t* __restrict__ m_dev, int m_upper, int n,
                                                            int k, float* __restrict__ C_f32, T* __restrict__ C_T,
@@ -252,7 +248,7 @@ static int launch_generic(hipStream_t s, const void* A, const GenericMats& mats,
   for (int i = 0; i < (MODE == 1 ? 2 : nm); ++i) bits |= (uintptr_t)mats.w[i];
   const bool vec = bits % 16 == 0 && k % 8 == 0 && n % 8 == 0 && ldc % 8 == 0;
 #define GO(MB, VEC)                                                                                                   \
-  hipLaunchKernelGGL((gemm_generic_kernel<T, MODE, MB, VEC, false, false>),                                           \
+  hipLaunchKernelGGL((gemm_generic_kernel<T, MODE, MB, VEC, false, false, 4>),                                        \
                      dim3(sl_cdiv(n, MB == 1 ? 16 : 64), sl_cdiv(m_upper, MB == 1 ? 16 : 64), nm), dim3(256), 0, s,   \
                      (const T*)A, mats, m_dev, m_upper, n, k, C_f32, (T*)C_T, out_row_map, ldc, GenericNorm{}, GenericRope{})
   if (small_tiles(m_upper, n, nm)) { if (vec) GO(1, true); else GO(1, false); }
@@ -287,11 +283,20 @@ int slk_generic_fused(int m_upper, int n, int k, int nm, uintptr_t bits) {
   return small_tiles(m_upper, n, nm) && bits % 16 == 0 && k % 8 == 0 && n % 8 == 0;
 }
 
+// The chunks that each of the four waves has in flight: all of them, where that is nine to twelve (reductions of 513 to 768) and no CU
+// gets a second workgroup.  Three load latencies are then one, and the registers that takes (109 to 212, room for 2 to 4 workgroups
+// where four chunks leave it for 5 to 8) cost nothing: launches of 33 to 256 workgroups 0.3 to 0.6 us less of 5 to 10 (80 workgroups,
+// k = 688 5.2 -> 4.8, k = 768, Q|K|V 9.6 -> 9.1); up to 512 two latencies are fewer registers' worth (Q|K|V, k = 512 7.6 -> 8.0, k = 264
+// 5.3 -> 6.0), and launches of more workgroups lose a round (steps of 300 rows, d = 512 198.6 -> 214.9 us, 600 rows, d = 264 137.4 -> 179.8).
+static bool deep(long workgroups, int k) { return workgroups <= 256 && k > 2 * 4 * 4 * KC && k <= 12 * 4 * KC; }
+
 template <int MODE, bool NORM, bool RES>
 static int launch_fused(hipStream_t s, const float* A, const GenericMats& mats, int tiles, int nm, const int32_t* m_dev, int m_upper,
                         int n, int k, float* C, const int32_t* out_row_map, const GenericNorm& norm, const GenericRope& rope) {
-  hipLaunchKernelGGL((gemm_generic_kernel<float, MODE, 1, true, NORM, RES>), dim3(tiles, sl_cdiv(m_upper, 16), nm), dim3(256), 0, s, A,
-                     mats, m_dev, m_upper, n, k, (float*)nullptr, C, out_row_map, (size_t)n, norm, rope);
+  const dim3 grid(tiles, sl_cdiv(m_upper, 16), nm);
+  const auto kernel = deep((long)tiles * grid.y * nm, k) ? gemm_generic_kernel<float, MODE, 1, true, NORM, RES, 12>
+                                                         : gemm_generic_kernel<float, MODE, 1, true, NORM, RES, 4>;
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, A, mats, m_dev, m_upper, n, k, (float*)nullptr, C, out_row_map, (size_t)n, norm, rope);
   SL_LAUNCH_CHECK();
   return SL_OK;
 }

@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shifts", [(0, 0, 0), (0, 1, 0), (1, 0, 1)])          # elements off alignment: layer 0, layer 1, head
-@pytest.mark.parametrize("d,heads,dh,d_ff,rows", [(248, 3, 32, 264, 70), (264, 2, 64, 768, 17), (256, 1, 128, 688, 16), (40, 1, 256, 776, 1)])
+@pytest.mark.parametrize("d,heads,dh,d_ff,rows", [(248, 3, 32, 264, 70), (264, 2, 64, 768, 17), (256, 1, 128, 688, 16), (40, 1, 256, 776, 1),
+                                              (520, 2, 256, 768, 33), (768, 17, 32, 1000, 16)])    # nine to twelve chunks a wave at once
 def test_fused_layers(d, heads, dh, d_ff, rows, shifts):
     shape = wl.Shape("fused", 2, d, heads, dh, d_ff, 136, "fp32")
     w = wl.make_weights(shape, seed=6, norm_gain_jitter=0.05)
