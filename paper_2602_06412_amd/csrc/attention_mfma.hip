@@ -779,7 +779,8 @@ __global__ __launch_bounds__(256, 1) void attention_thin_kernel(const bf16_t* __
         for (int v = 0; v < 16; ++v) acc_o[i][v] *= alpha;
     }
     // the second half's probabilities are made between the MFMAs of the first half's product: one wave per SIMD has nobody
-    // else to keep the matrix pipe busy under its vector work
+    // else to keep the matrix pipe busy under its vector work (one block, medians of seven runs, ahead of them -> between: 16 rows
+    // 95.1 -> 94.9 us, 300 rows of N = 512 200.7 -> 200.0; 457 rows and 256 rows of N = 2048 equal)
     PFrag ph[4], pl[4];
     float psum = 0.f;
     auto pair = [&](int kb, int v) {

@@ -76,8 +76,9 @@ __host__ __device__ inline size_t act_index(int row, int col, int K) {
 // correction.  16 vector instructions instead of 27, and as close to the exact value, over 2^23 arguments each in -87 .. 87,
 // -60 .. 30, -8 .. 8 and -1 .. 1: at most 2.64, 2.66, 2.06 and 1.98 ulp of fp32 (root mean square 0.349, 0.422, 0.481, 0.476),
 // all equal to those of the library's.  (Two instructions less, without the product's rounding, 21 ulp; the rest's two
-// parts added into one product, root mean square 0.425 for 0.422.)  Contraction would undo the exact steps.  One block, us: 224
-// rows 164.4 -> 163.4, 457 255.0 -> 252.2, 1280 469.0 -> 465.9, 4654 1638.7 -> 1623.3, 8192 2641 -> 2622.
+// parts added into one product, root mean square 0.425 for 0.422.)  Contraction would undo the exact steps.  One block, us, medians
+// of seven runs of each in turn (their quartiles lie within 0.1 %, of 8192 rows 0.3 %): 224 rows 165.0 -> 164.3, 457 253.9 -> 252.3,
+// 857 397.4 -> 395.6, 1280 474.5 -> 469.5, 4654 1640.9 -> 1626.6, 8192 2667.5 -> 2644.5.
 constexpr float kSiluFast = 87.0f;
 __device__ inline float silu_mul_fast(float g, float u) {
 #pragma clang fp contract(off)
