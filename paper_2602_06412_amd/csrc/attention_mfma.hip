@@ -577,16 +577,16 @@ __global__ __launch_bounds__(256, 3) void attention_trio_kernel(const bf16_t* __
 // SPLIT: as above, for sequences whose tiles are too many for four waves; each workgroup leaves its merged sums to
 // attention_merge_kernel.
 // PAIRS: 32 queries per workgroup or 64, two waves for each 32 of them: one round of workgroups where 32 queries make two (the
-// two waves that want a tile ask for it together).  One block, 64 queries and the loads inside the tile together: 300 rows of
-// N = 512 206.1 -> 202.9 us, 457 rows of N = 1024 264.2 -> 259.1, 512 rows 263.4 -> 257.4, 300 rows of 4 x 800 219.0 -> 210.8.  A
-// wave then makes two states of every fourth tile, one behind the other, where it could make one of every second: so a row's sums are
-// made of the same four states in both forms, and its result is the same bit by bit (equal times: 457 rows of N = 1024 258.7 before and
-// 258.6 after, 300 rows of N = 512 200.9 and 201.8, 512 rows 243.3 and 243.8).
+// two waves that want a tile ask for it together).  One block, 32 -> 64 queries, medians of seven runs: 300 rows of N = 512 201.2 -> 198.1
+// us, of N = 1024 210.7 -> 207.5, of 4 x 800 214.6 -> 207.3, 288 rows of 8 x 1024 218.5 -> 215.3, 457 rows of N = 1024 253.3 -> 251.7, 512
+// rows of N = 512 238.6 -> 237.0.  A wave then makes two states of every fourth tile, one behind the other, where it could make one of
+// every second: so a row's sums are made of the same four states in both forms, and its result is the same bit by bit (against one
+// state: 457 rows 258.7 -> 258.6, 300 rows of N = 512 200.9 -> 201.8, 512 rows 243.3 -> 243.8).
 // Which of the two is decided on the device, by the tiles that hold rows (thin_pairs): the host knows a bound only, which counts a
 // part-filled tile for every sequence but one.  One block, 64 queries wherever the bound exceeds a round -> decided here: 16 rows of
 // N = 512 bounded by 512 206.4 -> 203.4 us, 2 x 1024 with 96 and 160 rows 189.7 -> 186.7, 4 x 1024 with 50 rows each 179.2 -> 176.2, 6 x 20
 // and 150 rows of 7 x 1024 228.9 -> 222.2, 4 x 2048 with 50 each 190.8 -> 183.4, 200 rows of N = 2048 bounded by 512 244.6 -> 234.1; where
-// a tile of 32 is full of other sequences' keys (8 x 512, 160 rows) the launch waits for memory in either form, 159.9 and 159.6.
+// the keys and values of a batch are what is waited for (8 x 512, 160 rows) the forms are equal, 159.9 and 159.6.
 template <int V> struct AtInt { static constexpr int value = V; };
 // sum over the lanes up to this one
 __device__ inline int wave_prefix_sum(int v) {
